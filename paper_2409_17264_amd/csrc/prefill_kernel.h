@@ -583,19 +583,25 @@ struct Ring {
   uint32_t lds_addr;  // the same place as an LDS byte address, for the tile loads
 };
 
-// Walks tiles [kt_a, kt_b) through the 4-stage ring.  Self-contained: starts with
-// no load in flight and ends with none.
+// Walks tiles [kt_a, kt_b) through the 4-stage ring; every row of the workgroup sees the
+// tiles below kt_mid in full.  Self-contained: starts with no load in flight and ends with
+// none.
 //
 // Iteration `cur` runs RowBlock::fused(): the softmax and P*V of tile cur together
 // with the Q*K^T of tile cur+1, whose scores it hands to the next iteration in
 // registers (two score sets, used alternately).  So at the barrier that opens
 // iteration cur, tile cur+1 must have landed, tile cur+2 is in flight, and tile cur+3
 // is issued into the stage of tile cur-1, which everybody left at that barrier.
-template <int D, int NW, int NS, bool MASK>
+//
+// The masked tiles follow the unmasked ones in the same pipeline.  Ring stages are
+// compile-time, so the change-over happens between groups of NS tiles: up to NS-1 fully
+// visible tiles take the masked form, which costs each about a fifth more; draining the ring
+// and filling it again at the exact tile (as two walks) costs 3 to 4 tiles' time.
+template <int D, int NW, int NS>
 __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args, ConstI32Ptr pt,
-                                          int kt_a, int kt_b, int kv_total, int kv_head,
-                                          const Ring& ring, const TileLoader<D, NW>& ld,
-                                          int wave, int lane) {
+                                          int kt_a, int kt_mid, int kt_b, int kv_total,
+                                          int kv_head, const Ring& ring,
+                                          const TileLoader<D, NW>& ld, int wave, int lane) {
   using G = TileGeom<D, NW>;
   static_assert(NS == 4, "stages: tile cur, cur+1, cur+2 (in flight), cur+3 (being issued)");
   static_assert(kWarmTiles % NS == 0, "the walk's head is a whole number of ring rounds");
@@ -603,6 +609,8 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
   if (kt_a >= kt_b) return;
   const int half = lane >> 5;
   const int last = kt_b - 1;
+  // tiles [kt_a, kt_u) take the unmasked form
+  const int kt_u = kt_mid >= kt_b ? kt_b : kt_a + (kt_mid - kt_a) / NS * NS;
   // prologue: tiles kt_a .. kt_a+2 (clamped: a repeated tile is loaded again, harmlessly)
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
@@ -616,15 +624,15 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
   f32x16 s0[2], s1[2];  // scores of the even / odd tiles (counted from kt_a)
   ring_barrier<2 * G::kLoadsPerWaveTile>();  // tile kt_a has landed, for everyone
   rb.template qk<2>(ring.base, s0);
-  if (!MASK) {
+  if (kt_u > kt_a) {
     float mx = -INFINITY;
 #pragma unroll
     for (int f = 0; f < 32; ++f) mx = fmaxf(mx, s0[f >> 4][f & 15]);
     rb.template update_reference<false>(mx);
   }
   // One group of NS iterations starting at tile kt (stage numbers are compile-time).
-  auto group = [&](int kt, auto spec) {
-    constexpr bool kSpeculate = decltype(spec)::value;
+  auto group = [&](int kt, auto mask, auto spec) {
+    constexpr bool kMask = decltype(mask)::value, kSpeculate = decltype(spec)::value;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int cur = kt + s;
@@ -638,11 +646,11 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
         const char* k_next = ring.base + ((s + 1) % NS) * kTile;
         const char* v_cur = ring.base + s * kTile;  // + the bias in rb.v_off
         if (s & 1)
-          rb.template fused<MASK, true, kSpeculate>(k_next, v_cur, s1, s0, cur * G::kTileKeys,
-                                                    half);
+          rb.template fused<kMask, true, kSpeculate>(k_next, v_cur, s1, s0, cur * G::kTileKeys,
+                                                     half);
         else
-          rb.template fused<MASK, true, kSpeculate>(k_next, v_cur, s0, s1, cur * G::kTileKeys,
-                                                    half);
+          rb.template fused<kMask, true, kSpeculate>(k_next, v_cur, s0, s1, cur * G::kTileKeys,
+                                                     half);
         // The scalar load of the next page id goes HERE, after the tile's last LDS read has
         // been consumed and before the barrier: scalar loads and LDS reads share one
         // counter and scalar loads return out of order, so with one in flight every wait for
@@ -655,23 +663,29 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
     }
   };
   int kt = kt_a;
-  if constexpr (!MASK) {
-    // The speculation check of fused() cannot pass before a lane's sum is 16 times what two
-    // slices bring: not in the first 8 tiles of a walk of diffuse rows, and with 64 lanes
-    // voting and the odd large score, rarely in the first twenty.  A failed check costs a
-    // multiple of what the row maximum costs when it is taken up front, so the head of the
-    // walk takes it up front.
-    for (; kt < last && kt < kt_a + kWarmTiles; kt += NS) group(kt, std::false_type{});
-  }
-  for (; kt < last; kt += NS) group(kt, std::true_type{});
+  const int end_u = min(kt_u, last);
+  // The speculation check of fused() cannot pass before a lane's sum is 16 times what two
+  // slices bring: not in the first 8 tiles of a walk of diffuse rows, and with 64 lanes
+  // voting and the odd large score, rarely in the first twenty.  A failed check costs a
+  // multiple of what the row maximum costs when it is taken up front, so the head of the
+  // walk takes it up front.
+  for (; kt < end_u && kt < kt_a + kWarmTiles; kt += NS)
+    group(kt, std::false_type{}, std::false_type{});
+  for (; kt < end_u; kt += NS) group(kt, std::false_type{}, std::true_type{});
+  for (; kt < last; kt += NS) group(kt, std::true_type{}, std::false_type{});
   // the last tile: its scores are in registers, its V tile landed with its K tile
-  {
+  auto final_tile = [&](auto mask) {
+    constexpr bool kMask = decltype(mask)::value;
     const char* v_last = ring.base + ((last - kt_a) % NS) * kTile;  // + the bias in rb.v_off
     if ((last - kt_a) & 1)
-      rb.template fused<MASK, false>(nullptr, v_last, s1, s0, last * G::kTileKeys, half);
+      rb.template fused<kMask, false>(nullptr, v_last, s1, s0, last * G::kTileKeys, half);
     else
-      rb.template fused<MASK, false>(nullptr, v_last, s0, s1, last * G::kTileKeys, half);
-  }
+      rb.template fused<kMask, false>(nullptr, v_last, s0, s1, last * G::kTileKeys, half);
+  };
+  if (kt_u == kt_b)
+    final_tile(std::false_type{});
+  else
+    final_tile(std::true_type{});
   ring_barrier<0>();
 }
 
@@ -736,10 +750,8 @@ __global__ void __launch_bounds__(512) prefill_kernel(const AttnArgs args) {
   ConstI32Ptr pt = (ConstI32Ptr)(args.page_table + sd.pt_off);
   TileLoader<D, NW> loader;
   loader.init(wave, lane);
-  run_tiles<D, NW, NS, false>(rb, args, pt, kt_begin, kt_mid, kv_total, kv_head, stages, loader,
-                              wave, lane);
-  run_tiles<D, NW, NS, true>(rb, args, pt, kt_mid, kt_end, kv_total, kv_head, stages, loader,
-                             wave, lane);
+  run_tiles<D, NW, NS>(rb, args, pt, kt_begin, kt_mid, kt_end, kv_total, kv_head, stages, loader,
+                       wave, lane);
 
   const bool direct = sd.n_split == 1;
   float* o_base = direct ? args.out : args.part_o;
