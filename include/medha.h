@@ -89,7 +89,9 @@ typedef struct medha_kv_cache {
  *   workspace        dev, 256-byte aligned, at least
  *                    medha_chunked_prefill_workspace_bytes(...) bytes; contents
  *                    are scratch (split-KV partials); may be NULL when that
- *                    size is <= 256 (nothing is split).
+ *                    size is <= 256 (nothing is split).  A smaller one is refused
+ *                    only below what the plan with the fewest partials takes; in
+ *                    between, the fastest plan that fits it is used.
  *
  * Work is split over query tiles and, when those are too few to fill the GPU,
  * also over KV ranges whose partials are merged on the same stream.  Sequence
@@ -116,9 +118,9 @@ size_t medha_chunked_prefill_workspace_bytes(const int32_t* prefix_len, const in
  * part of the library's device image (every GPU the library runs on holds its own copy
  * until the process ends).  The call allocates nothing and calls no allocating routine;
  * its first call on a device looks the array's address up (make that call outside a
- * graph capture).  A batch whose workspace need, as reported by
- * medha_chunked_prefill_workspace_bytes, exceeds MEDHA_NOALLOC_SCRATCH_BYTES is
- * refused with MEDHA_ERR_WORKSPACE and nothing is enqueued.  All calls on one GPU share
+ * graph capture).  The plan is the fastest one whose partials fit the array; a batch that
+ * could not do with MEDHA_NOALLOC_SCRATCH_BYTES of workspace is refused with
+ * MEDHA_ERR_WORKSPACE and nothing is enqueued.  All calls on one GPU share
  * that GPU's array: calls that overlap on one GPU (different streams, or graphs
  * replayed concurrently) race on it and must be serialised by the caller.  Nothing in
  * the array has to start at zero: every partial is written before it is read.

@@ -161,8 +161,9 @@ hipError_t launch_plan(const LaunchPlan& lp, bool split_keys, int d, AttnArgs& a
 int run_plan(const Plan& plan, const void* q, const medha_kv_cache* kv, const int32_t* page_table,
              int h_q, float softmax_scale, float* out, float* lse, void* workspace,
              size_t workspace_bytes, void* hip_stream) {
-  if (plan.part_rows > 0) {
-    if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < plan.bytes)
+  if (plan.part_rows > 0 || plan.min_part_rows > 0) {
+    if (workspace == nullptr || !aligned(workspace, 256) ||
+        workspace_bytes < plan.min_bytes || workspace_bytes < plan.bytes)
       return MEDHA_ERR_WORKSPACE;
   }
   char* ws = static_cast<char*>(workspace);
@@ -191,6 +192,32 @@ int check_kv(const medha_kv_cache* kv, int h_q) {
   return check_heads(h_q, kv->num_kv_heads, kv->head_dim, kv->page_size);
 }
 
+// The part of a caller's workspace a plan may count on: none of a missing or misaligned one.
+size_t usable_bytes(const void* workspace, size_t bytes) {
+  return workspace != nullptr && aligned(workspace, 256) ? bytes : 0;
+}
+
+// Scratch of a chunked-prefill call: what its fastest plan takes, or the least it can do with
+// (`least`).  0 for invalid arguments.
+size_t prefill_workspace(const int32_t* prefix_len, const int32_t* chunk_len, int32_t batch,
+                         int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                         bool least) {
+  if (batch < 0 || (batch > 0 && (prefix_len == nullptr || chunk_len == nullptr))) return 0;
+  if (check_heads(num_q_heads, num_kv_heads, head_dim, kPageSize) != MEDHA_OK) return 0;
+  std::vector<SeqInput> seqs(batch);
+  int64_t row = 0;
+  for (int b = 0; b < batch; ++b) {
+    if (prefix_len[b] < 0 || chunk_len[b] < 1) return 0;
+    if ((int64_t)prefix_len[b] + chunk_len[b] > INT32_MAX) return 0;
+    seqs[b] = SeqInput{0, (int32_t)row, (int32_t)row, chunk_len[b], prefix_len[b]};
+    row += chunk_len[b];
+    if (row > INT32_MAX) return 0;
+  }
+  const Plan plan =
+      make_plan(seqs.data(), batch, num_q_heads, num_kv_heads, head_dim, current_num_cus());
+  return least ? plan.min_bytes : plan.workspace_bytes();
+}
+
 }  // namespace
 }  // namespace medha
 
@@ -214,19 +241,8 @@ const char* medha_strerror(int code) {
 size_t medha_chunked_prefill_workspace_bytes(const int32_t* prefix_len, const int32_t* chunk_len,
                                              int32_t batch, int32_t num_q_heads,
                                              int32_t num_kv_heads, int32_t head_dim) {
-  if (batch < 0 || (batch > 0 && (prefix_len == nullptr || chunk_len == nullptr))) return 0;
-  if (check_heads(num_q_heads, num_kv_heads, head_dim, kPageSize) != MEDHA_OK) return 0;
-  std::vector<SeqInput> seqs(batch);
-  int64_t row = 0;
-  for (int b = 0; b < batch; ++b) {
-    if (prefix_len[b] < 0 || chunk_len[b] < 1) return 0;
-    if ((int64_t)prefix_len[b] + chunk_len[b] > INT32_MAX) return 0;
-    seqs[b] = SeqInput{0, (int32_t)row, (int32_t)row, chunk_len[b], prefix_len[b]};
-    row += chunk_len[b];
-    if (row > INT32_MAX) return 0;
-  }
-  return make_plan(seqs.data(), batch, num_q_heads, num_kv_heads, head_dim, current_num_cus())
-      .bytes;
+  return prefill_workspace(prefix_len, chunk_len, batch, num_q_heads, num_kv_heads, head_dim,
+                           false);
 }
 
 int medha_chunked_prefill_attn(const void* q, const medha_kv_cache* kv, const int32_t* page_table,
@@ -256,7 +272,7 @@ int medha_chunked_prefill_attn(const void* q, const medha_kv_cache* kv, const in
     if (row > INT32_MAX) return MEDHA_ERR_INVALID_ARG;
   }
   const Plan plan = make_plan(seqs.data(), batch, num_q_heads, kv->num_kv_heads, kv->head_dim,
-                              current_num_cus());
+                              current_num_cus(), usable_bytes(workspace, workspace_bytes));
   return run_plan(plan, q, kv, page_table, num_q_heads, softmax_scale, out, lse, workspace,
                   workspace_bytes, hip_stream);
 }
@@ -270,8 +286,8 @@ int medha_chunked_prefill_attn_noalloc(const void* q, const medha_kv_cache* kv,
   // The size check comes first so that an oversized batch is refused whatever else is wrong
   // with it; medha_chunked_prefill_attn validates everything again.
   if (batch > 0 && kv != nullptr && prefix_len != nullptr && chunk_len != nullptr) {
-    const size_t need = medha_chunked_prefill_workspace_bytes(
-        prefix_len, chunk_len, batch, num_q_heads, kv->num_kv_heads, kv->head_dim);
+    const size_t need = prefill_workspace(prefix_len, chunk_len, batch, num_q_heads,
+                                          kv->num_kv_heads, kv->head_dim, true);
     if (need > (size_t)MEDHA_NOALLOC_SCRATCH_BYTES) return MEDHA_ERR_WORKSPACE;
   }
   int rc = MEDHA_OK;
@@ -293,7 +309,7 @@ size_t medha_decode_partial_workspace_bytes(const int32_t* kv_len, int32_t items
     seqs[i] = SeqInput{0, 0, i, 1, kv_len[i] - 1};
   }
   return make_plan(seqs.data(), items, num_q_heads, num_kv_heads, head_dim, current_num_cus())
-      .bytes;
+      .workspace_bytes();
 }
 
 int medha_decode_partial_attn(const void* q, int32_t num_queries, const medha_kv_cache* kv,
@@ -321,7 +337,7 @@ int medha_decode_partial_attn(const void* q, int32_t num_queries, const medha_kv
     seqs[i] = SeqInput{page_table_offs[i], q_index[i], i, 1, kv_len[i] - 1};
   }
   const Plan plan = make_plan(seqs.data(), items, num_q_heads, kv->num_kv_heads, kv->head_dim,
-                              current_num_cus());
+                              current_num_cus(), usable_bytes(workspace, workspace_bytes));
   return run_plan(plan, q, kv, page_table, num_q_heads, softmax_scale, out_partial, lse_partial,
                   workspace, workspace_bytes, hip_stream);
 }
@@ -335,13 +351,14 @@ size_t medha_chunk_partial_workspace_bytes(const int32_t* chunk_len, const int32
   int64_t row = 0;
   for (int i = 0; i < items; ++i) {
     if (chunk_len[i] < 1 || kv_len[i] < 0) return 0;
-    // the plan depends on the row count and the key count only
+    // (which rows see which keys can only shift the choice of KV ranges, and a call keeps to
+    // ranges whose partials fit the workspace it is given)
     seqs[i] = SeqInput{0, 0, (int32_t)row, chunk_len[i], kv_len[i] - 1, kv_len[i]};
     row += chunk_len[i];
     if (row > INT32_MAX) return 0;
   }
   return make_plan(seqs.data(), items, num_q_heads, num_kv_heads, head_dim, current_num_cus())
-      .bytes;
+      .workspace_bytes();
 }
 
 int medha_chunk_partial_attn(const void* q, int32_t num_tokens, const medha_kv_cache* kv,
@@ -381,7 +398,7 @@ int medha_chunk_partial_attn(const void* q, int32_t num_tokens, const medha_kv_c
     if (row > INT32_MAX) return MEDHA_ERR_INVALID_ARG;
   }
   const Plan plan = make_plan(seqs.data(), items, num_q_heads, kv->num_kv_heads, kv->head_dim,
-                              current_num_cus());
+                              current_num_cus(), usable_bytes(workspace, workspace_bytes));
   return run_plan(plan, q, kv, page_table, num_q_heads, softmax_scale, out_partial, lse_partial,
                   workspace, workspace_bytes, hip_stream);
 }

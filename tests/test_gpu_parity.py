@@ -511,6 +511,29 @@ def test_small_chunk_long_prefix_many_way_split(h_q, h_kv, d, prefix, chunk):
     check(out, lse, ro, rl, f"small chunk hq{h_q} d{d} P{prefix} c{chunk} split{e[0].n_split}")
 
 
+# ------------------------------------------------------------ plans and the workspace at hand
+def test_plan_keeps_to_the_workspace_it_is_given():
+    """47 row tiles: the query reports what the fastest plan takes, and a call with less (down to
+    6 KV ranges, the fewest-partials rule's need) takes other ranges with the same results."""
+    h_q, chunk = 8, 1500
+    b = wl.make_prefill_batch("budget", h_q, 1, 128, [21000], [chunk], seed=91)
+    need = medha.chunked_prefill_workspace_bytes(b.prefix_len, b.chunk_len, h_q, 1, 128)
+    row = chunk * h_q * 129 * 4
+    assert need >= 6 * row
+    b = to_dev(b)
+    rows = edge_rows(b, 5, 6, 6, 8, 8)
+    ro, rl = oracle_prefill(b, rows)
+    pt = torch.from_numpy(b.page_table).cuda()
+    for nbytes in sorted({6 * row + 512, 8 * row, need}):
+        ws = torch.full((nbytes + 4096,), 0xff, dtype=torch.uint8, device="cuda")
+        out, lse = medha.chunked_prefill_attn(b.q, b.k_pool, b.v_pool, pt, b.page_table_offs,
+                                              b.prefix_len, b.chunk_len, b.scale,
+                                              workspace=ws[:nbytes])
+        torch.cuda.synchronize()
+        assert bool((ws[nbytes:] == 0xff).all())
+        check(out.cpu().numpy()[rows], lse.cpu().numpy()[rows], ro, rl, f"workspace of {nbytes}")
+
+
 # ------------------------------------------------------------ softmax scale values
 @pytest.mark.parametrize("d,prefix", [(128, 64 * 20 + 7), (128, 64 * 23), (64, 64 * 22 - 1)])
 def test_walks_that_end_around_the_exact_route_warm_up(d, prefix):

@@ -129,6 +129,23 @@ def test_plans_of_ragged_batches():
     assert e[0].n_split == 1
 
 
+@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,d", [
+    ([300007], [1500], 8, 1, 128),            # 47 row tiles: 6 ranges would be 282 workgroups
+    ([65000] * 4, [600] * 4, 8, 1, 128),      # 4 x 19
+    ([20011], [777], 32, 8, 64),              # 8 x 13
+    ([50000], [4864], 8, 1, 128),             # 152: more than half the device, unsplit
+    ([9000], [33], 8, 1, 128),                # the small workgroups
+])
+def test_row_split_launches_fill_whole_rounds_of_the_device(prefix, chunk, h_q, h_kv, d):
+    """Time of the planned launch in tiles, workgroups of one length each: no more than 1.15 times
+    the tiles spread evenly over 256 compute units plus a fixed cost of 12 tiles a round."""
+    e, grid, _ = _check_plan(prefix, chunk, h_q, h_kv, d, 256)
+    slots = 512 if d == 64 and e[0].rows_per_wg == 128 else 256
+    rounds = -(-grid // slots)
+    tiles = sum(h_kv * x.n_row_tiles * -(-(p + c) // 64) for x, p, c in zip(e, prefix, chunk))
+    assert rounds * max(x.tiles_per_split for x in e) <= 1.15 * tiles / slots + 12 * rounds
+
+
 def test_bench_refuses_more_than_one_gpu_and_finds_its_traffic_figures():
     import subprocess
     import sys
