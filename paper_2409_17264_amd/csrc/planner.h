@@ -117,6 +117,20 @@ inline int64_t kv_tiles_of(const SeqDesc& sd, int tile_keys) {
   return std::max<int64_t>(1, ceil_div((int64_t)sd.kv_len, tile_keys));
 }
 
+// Tiles that row tile rt of a sequence walks.
+inline int64_t tiles_at(const SeqDesc& sd, const ModeShape& sh, int gqa, int64_t rt) {
+  const int64_t last_tok =
+      (std::min((int64_t)sd.chunk_len * gqa, (rt + 1) * sh.rows_per_wg) - 1) / gqa;
+  const int64_t keys = std::min<int64_t>(sd.kv_len, (int64_t)sd.prefix_len + last_tok + 1);
+  return ceil_div(std::max<int64_t>(0, keys), sh.tile_keys);
+}
+
+// Whether the causal triangle makes the walks of its row tiles differ by more than a sixteenth.
+inline bool uneven_walks(const SeqDesc& sd, const ModeShape& sh, int gqa) {
+  const int64_t t_last = tiles_at(sd, sh, gqa, sd.n_row_tiles - 1);
+  return t_last - tiles_at(sd, sh, gqa, 0) > t_last / 16;
+}
+
 // KV ranges of a sequence when no range is longer than `steps` tiles nor shorter than min_tiles.
 inline void split_by_steps(const SeqDesc& sd, int tile_keys, int64_t steps, int min_tiles,
                            int64_t& n_split, int64_t& tps) {
@@ -148,29 +162,37 @@ inline double launch_us(const LaunchPlan& lp, int h_kv, int gqa, int num_cus, co
     int64_t n_split, tps;
     split_by_steps(sd, sh.tile_keys, steps, min_tiles, n_split, tps);
     if (n_split > 1) part += n_split * sd.chunk_len;
-    // tiles the first and the last row tile see; in between they grow evenly (the causal
-    // triangle), which up to 8 classes of row tiles stand for
+    // up to 8 classes of row tiles stand for a causal triangle
     const int64_t n_rt = sd.n_row_tiles;
-    auto tiles_at = [&](int64_t rt) {
-      const int64_t last_tok =
-          (std::min((int64_t)sd.chunk_len * gqa, (rt + 1) * sh.rows_per_wg) - 1) / gqa;
-      const int64_t keys = std::min<int64_t>(sd.kv_len, (int64_t)sd.prefix_len + last_tok + 1);
-      return ceil_div(std::max<int64_t>(0, keys), sh.tile_keys);
+    const int64_t t_last = tiles_at(sd, sh, gqa, n_rt - 1);
+    const int64_t classes = uneven_walks(sd, sh, gqa) ? std::min<int64_t>(n_rt, 8) : 1;
+    // Workgroups of the fullest die (see decode_slot_dealt): its whole groups, one of every 8, and an
+    // eighth, rounded up, of what the others hold.
+    const int64_t all = h_kv * n_split, dealt = all / kXcds;
+    int64_t before = 0;
+    auto add = [&](int64_t tiles, int64_t count, bool whole) {
+      if (tiles <= 0) return;
+      int64_t n = count;
+      if (!whole) {
+        n = ceil_div(before + count, kXcds) - ceil_div(before, kXcds);
+        before += count;
+      }
+      if (n > 0) groups.push_back(WalkGroup{wc.fixed_us + (double)tiles * wc.tile_us, n});
     };
-    const int64_t t_last = tiles_at(n_rt - 1);
-    const int64_t classes = t_last - tiles_at(0) <= t_last / 16 ? 1 : std::min<int64_t>(n_rt, 8);
-    int64_t before = 0;  // workgroups counted so far: a die gets an eighth of them, rounded up
-    auto add = [&](double us, int64_t count) {
-      const int64_t n = ceil_div(before + count, kXcds) - ceil_div(before, kXcds);
-      before += count;
-      if (n > 0) groups.push_back(WalkGroup{us, n});
-    };
+    if (classes == 1) {
+      if (t_last >= tps) add(tps, n_rt * h_kv * (t_last / tps), false);
+      add(t_last % tps, n_rt * h_kv, false);
+      continue;
+    }
     for (int64_t c = classes; c-- > 0;) {
       const int64_t lo = c * n_rt / classes, hi = (c + 1) * n_rt / classes;
-      const int64_t t = classes == 1 ? t_last : tiles_at((lo + hi) / 2);
-      const int64_t count = (hi - lo) * h_kv;
-      if (t / tps > 0) add(wc.fixed_us + (double)tps * wc.tile_us, count * (t / tps));
-      if (t % tps > 0) add(wc.fixed_us + (double)(t % tps) * wc.tile_us, count);
+      const int64_t t = tiles_at(sd, sh, gqa, (lo + hi) / 2);
+      for (int64_t g = 0; g < dealt && (g * kXcds / h_kv) * tps < t; ++g)
+        add(std::min(tps, t - (g * kXcds / h_kv) * tps), hi - lo, true);
+      const int64_t from = dealt * kXcds;  // the other groups: (split, heads of it)
+      for (int64_t sp = from / h_kv; sp < n_split && sp * tps < t; ++sp)
+        add(std::min(tps, t - sp * tps), (hi - lo) * (h_kv - std::max<int64_t>(0, from - sp * h_kv)),
+            false);
     }
   }
   const int64_t machines = std::max<int64_t>(1, num_cus / kXcds) * wc.wgs_per_cu;
@@ -236,7 +258,7 @@ inline int64_t choose_steps(const LaunchPlan& lp, int h_kv, int gqa, int num_cus
 
 // Cuts the KV axis of each sequence into ranges of at most `steps` tiles (never below
 // `min_tiles`), orders the sequences and hands out workgroup slots and partial rows.
-inline void plan_launch(LaunchPlan& lp, int h_kv, int64_t steps, int min_tiles,
+inline void plan_launch(LaunchPlan& lp, int h_kv, int gqa, int64_t steps, int min_tiles,
                         int64_t& part_rows) {
   const ModeShape sh = lp.shape;
   for (SeqDesc& sd : lp.descs) {
@@ -244,6 +266,7 @@ inline void plan_launch(LaunchPlan& lp, int h_kv, int64_t steps, int min_tiles,
     split_by_steps(sd, sh.tile_keys, steps, min_tiles, n_split, tps);
     sd.n_split = (int)n_split;
     sd.tiles_per_split = (int)tps;
+    sd.dealt = sd.n_row_tiles > 1 && uneven_walks(sd, sh, gqa);
   }
   // Longest workgroups first: the hardware hands workgroups out in slot order, so the short
   // ones fill the launch's tail instead of a long one starting last (the order of the
@@ -346,9 +369,9 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
                               row_bytes, fit - keys_rows);
   }
   if (!plan.rows.descs.empty())
-    plan_launch(plan.rows, h_kv, rows_steps, kMinTiles, plan.part_rows);
+    plan_launch(plan.rows, h_kv, gqa, rows_steps, kMinTiles, plan.part_rows);
   if (!plan.keys.descs.empty())
-    plan_launch(plan.keys, h_kv, keys_steps, kMinTiles, plan.part_rows);
+    plan_launch(plan.keys, h_kv, gqa, keys_steps, kMinTiles, plan.part_rows);
 
   plan.off_part_o = 0;
   plan.off_part_lse = partial_o_bytes(plan.part_rows, h_q, head_dim);

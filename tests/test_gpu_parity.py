@@ -534,6 +534,23 @@ def test_plan_keeps_to_the_workspace_it_is_given():
         check(out.cpu().numpy()[rows], lse.cpu().numpy()[rows], ro, rl, f"workspace of {nbytes}")
 
 
+# ------------------------------------------------------------ prompts and first chunks
+@pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk", [
+    (8, 1, 128, [0], [1300]),                 # 41 row tiles dealt one by one, in KV ranges
+    (8, 2, 64, [300], [900]),                 # 15 row tiles: runs
+    (32, 8, 128, [0, 40, 0], [700, 130, 1]),  # a group per die; only the last sequence turned
+    (12, 3, 64, [64, 0], [1500, 600]),        # 3 groups of 24 and 10
+])
+def test_prompts_whose_walks_differ(h_q, h_kv, d, prefix, chunk):
+    """No or little prefix: row tiles walk different numbers of keys, and the slots are dealt out
+    so that every die gets the same mix."""
+    b = wl.make_prefill_batch("uneven", h_q, h_kv, d, prefix, chunk, seed=sum(chunk),
+                              poison_unused=True)
+    ro, rl = oracle_prefill(b)
+    out, lse = gpu_prefill(to_dev(b))
+    check(out, lse, ro, rl, f"prompts hq{h_q} hkv{h_kv} d{d} {prefix} {chunk}")
+
+
 # ------------------------------------------------------------ softmax scale values
 @pytest.mark.parametrize("d,prefix", [(128, 64 * 20 + 7), (128, 64 * 23), (64, 64 * 22 - 1)])
 def test_walks_that_end_around_the_exact_route_warm_up(d, prefix):

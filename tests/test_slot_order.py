@@ -1,0 +1,58 @@
+"""Order in which the row-split kernel's workgroups take their work (CPU): the kernel's own slot
+functions, compiled for the host."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = "/opt/rocm/bin/hipcc"
+
+SOURCE = r"""
+#include <cstdio>
+#include <set>
+#include "common.h"
+using namespace medha;
+int main() {
+  for (int h : {1, 2, 3, 4, 8, 12})
+    for (int ns : {1, 2, 3, 5, 8, 17})
+      for (int n = 1; n <= 260; n = n < 70 ? n + 1 : n + 19) {
+        const int items = h * ns * n, slots = 8 * ((items + 7) / 8);
+        std::set<int> seen;
+        long work[8] = {}, all = 0;
+        int count[8] = {};
+        for (int u = 0; u < slots; ++u) {
+          const SlotItem a = decode_slot_dealt(u, h, ns, n);
+          if (!a.valid) continue;
+          if (a.kv_head < 0 || a.kv_head >= h || a.split < 0 || a.split >= ns || a.row_tile < 0 ||
+              a.row_tile >= n || !seen.insert((a.split * h + a.kv_head) * n + a.row_tile).second) {
+            std::printf("bad slot %d of h %d ns %d n %d\n", u, h, ns, n);
+            return 1;
+          }
+          if (a.split == 0) work[u % 8] += a.row_tile + 1;  // the full ranges of a triangle
+          all += a.split == 0 ? a.row_tile + 1 : 0;
+          ++count[u % 8];
+        }
+        if ((int)seen.size() != items) { std::printf("lost: h %d ns %d n %d\n", h, ns, n); return 1; }
+        // many row tiles that the dies share: no die has more than its part and two tiles a group
+        if (n >= 64 && h * ns < 8)
+          for (int d = 0; d < 8; ++d)
+            if (work[d] > all / 8 + 2L * h * n) { std::printf("uneven: h %d ns %d n %d\n", h, ns, n); return 1; }
+      }
+  std::puts("ok");
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_dealt_slots_cover_every_item_once_and_evenly(tmp_path):
+    src, exe = str(tmp_path / "slots.hip"), str(tmp_path / "slots")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    res = subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Wno-inline-asm",
+                          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I",
+                          os.path.join(ROOT, "paper_2409_17264_amd", "csrc"), src, "-o", exe],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-3000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and "ok" in run.stdout, run.stdout + run.stderr
