@@ -38,6 +38,18 @@ struct DecodeGeom {
   static constexpr int kSplitKeys = kBlockKeys * kWaves;  // planner's KV-split granule (128)
 };
 
+// async_load16 for data that is read once: the non-temporal hint keeps the stream from being
+// allocated in the caches on its way, which is worth a tenth of the rate.  Every key and value
+// of a launch is read by exactly one workgroup here.  Measured: 1M keys in 4 shards, 8 KV heads,
+// 706 -> 643 us with both merges (6.1 -> 6.7 TB/s); 64 decodes of 2K median 135 -> 117 us, 128 of
+// 8K 812 -> 726 us; wider scopes (sc0, sc1) with the hint change nothing.
+__device__ __forceinline__ void async_stream16(const void* gptr, uint32_t lds_addr_uniform) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+               :
+               : "s"(lds_addr_uniform), "v"(gptr)
+               : "m0", "memory");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
@@ -64,8 +76,8 @@ __device__ __forceinline__ void issue_block(const AttnArgs& args, int page0, int
     const int64_t off =
         (((int64_t)page * args.h_kv + kv_head) * kPageSize + (t & 15)) * (D * 2);
     const uint32_t lds_off = j * G::kRowsPerInstr * (D * 2);
-    async_load16(kp + off + Swz<D>::k(row, pos) * 16, k_lds + lds_off);
-    async_load16(vp + off + Swz<D>::v(row, pos) * 16, v_lds + lds_off);
+    async_stream16(kp + off + Swz<D>::k(row, pos) * 16, k_lds + lds_off);
+    async_stream16(vp + off + Swz<D>::v(row, pos) * 16, v_lds + lds_off);
   }
 }
 
