@@ -37,18 +37,16 @@ static_assert(sizeof(AppendArgs) <= 4096, "kernel argument block too large");
 // outside [0, num_pages) is skipped: nothing outside the pools is ever written.
 __global__ void __launch_bounds__(kThreads) kv_append_kernel(const AppendArgs args) {
   const int per_token = args.h_kv * args.words_per_row;
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (idx >= (int64_t)args.total_rows * per_token) return;
+  const int64_t thread = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t total = (int64_t)args.total_rows * per_token;
+  const int64_t idx = min(thread, total - 1);
   const int row = (int)(idx / per_token);
   const int rem = (int)(idx % per_token);
   const int head = rem / args.words_per_row;
   const int word = rem % args.words_per_row;
-  int lo = 0, hi = args.n_seq - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (args.descs[mid].row_rank <= row) lo = mid; else hi = mid - 1;
-  }
-  const AppendDesc sd = args.descs[lo];
+  const int seq = find_last(args.n_seq, row, [&](int i) { return args.descs[i].row_rank; });
+  if (thread >= total) return;
+  const AppendDesc sd = args.descs[seq];
   const int j = row - sd.row_rank;
   const int t = sd.prefix_len + j;
   const int page = args.page_table[sd.pt_off + (t >> 4)];

@@ -99,20 +99,16 @@ template <int D>
 __global__ void __launch_bounds__(kThreads) split_merge_kernel(const MergeArgs args) {
   constexpr int per_row = D / 4;
   const SeqDesc* descs = args.inline_descs;
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t thread = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int64_t total = (int64_t)args.total_rows * args.h_q * per_row;
-  if (idx >= total) return;
+  const int64_t idx = min(thread, total - 1);
   const int d4 = (int)(idx % per_row);
   const int64_t rh = idx / per_row;
   const int head = (int)(rh % args.h_q);
   const int row = (int)(rh / args.h_q);  // rank of the token row among the launch's rows
   // sequences are in launch order; find the one that holds this row
-  int lo = 0, hi = args.n_seq - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (descs[mid].row_rank <= row) lo = mid; else hi = mid - 1;
-  }
-  const SeqDesc sd = descs[lo];
+  const SeqDesc sd = descs[find_last(args.n_seq, row, [&](int i) { return descs[i].row_rank; })];
+  if (thread >= total) return;
   if (sd.n_split == 1) return;
   const int j = row - sd.row_rank;
   const int64_t orow = ((int64_t)sd.out_row + j) * args.h_q + head;
@@ -134,12 +130,7 @@ __global__ void __launch_bounds__(kThreads) split_merge_wide_kernel(const MergeA
   const SeqDesc* descs = args.inline_descs;
   const int head = blockIdx.x % args.h_q;
   const int row = blockIdx.x / args.h_q;  // rank of the token row among the launch's rows
-  int lo = 0, hi = args.n_seq - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (descs[mid].row_rank <= row) lo = mid; else hi = mid - 1;
-  }
-  const SeqDesc sd = descs[lo];
+  const SeqDesc sd = descs[find_last(args.n_seq, row, [&](int i) { return descs[i].row_rank; })];
   if (sd.n_split == 1) return;  // the whole workgroup: written directly by the attention kernel
   const int j = row - sd.row_rank;
   const int d4 = threadIdx.x % per_row;

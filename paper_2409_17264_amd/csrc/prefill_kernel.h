@@ -556,12 +556,7 @@ __device__ __forceinline__ SeqDesc uniform(const SeqDesc& d) {
 
 // Largest i with descs[i].work_start <= slot.
 __device__ __forceinline__ int find_seq_slot(const SeqDesc* descs, int n_seq, int slot) {
-  int lo = 0, hi = n_seq - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (descs[mid].work_start <= slot) lo = mid; else hi = mid - 1;
-  }
-  return lo;
+  return find_last(n_seq, slot, [&](int i) { return descs[i].work_start; });
 }
 
 template <int D, int NW, int NS>
