@@ -38,18 +38,6 @@ struct DecodeGeom {
   static constexpr int kSplitKeys = kBlockKeys * kWaves;  // planner's KV-split granule (128)
 };
 
-// async_load16 for data that is read once: the non-temporal hint keeps the stream from being
-// allocated in the caches on its way, which is worth a tenth of the rate.  Every key and value
-// of a launch is read by exactly one workgroup here.  Measured: 1M keys in 4 shards, 8 KV heads,
-// 706 -> 643 us with both merges (6.1 -> 6.7 TB/s); 64 decodes of 2K median 135 -> 117 us, 128 of
-// 8K 812 -> 726 us; wider scopes (sc0, sc1) with the hint change nothing.
-__device__ __forceinline__ void async_stream16(const void* gptr, uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
-               :
-               : "s"(lds_addr_uniform), "v"(gptr)
-               : "m0", "memory");
-}
-
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");

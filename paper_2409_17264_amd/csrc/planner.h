@@ -66,10 +66,11 @@ struct WalkCost {
   int wgs_per_cu;  // workgroups a compute unit holds at a time
 };
 
-// (measured on long walks; the small workgroups of head dim 64 share a compute unit in pairs)
+// (measured; the small workgroups of head dim 64 share a compute unit in pairs, where one's
+// start and end hide behind the other's walk, at the price of a second copy of the K/V loads)
 inline WalkCost walk_cost(int head_dim, int q_blocks) {
   if (head_dim == 128) return q_blocks == 2 ? WalkCost{1.64, 10.0, 1} : WalkCost{1.2, 10.0, 1};
-  return q_blocks == 2 ? WalkCost{0.9, 10.0, 1} : WalkCost{0.9, 10.0, 2};
+  return q_blocks == 2 ? WalkCost{0.9, 11.0, 1} : WalkCost{0.91, 9.0, 2};
 }
 
 // The merge of a launch's partials: a launch, then bytes at the rate the merge kernel reads
@@ -152,6 +153,16 @@ inline int64_t partial_rows(const LaunchPlan& lp, int64_t steps, int min_tiles) 
   return rows;
 }
 
+// Workgroup slots of a launch split by `steps`.
+inline int64_t workgroups(const LaunchPlan& lp, int h_kv, int64_t steps, int min_tiles) {
+  int64_t n = 0, n_split, tps;
+  for (const SeqDesc& sd : lp.descs) {
+    split_by_steps(sd, lp.shape.tile_keys, steps, min_tiles, n_split, tps);
+    n += kXcds * ceil_div((int64_t)h_kv * sd.n_row_tiles * n_split, kXcds);
+  }
+  return n;
+}
+
 // Estimated time of a row-split launch whose KV ranges are at most `steps` tiles long.
 inline double launch_us(const LaunchPlan& lp, int h_kv, int gqa, int num_cus, const WalkCost& wc,
                         int64_t steps, int min_tiles, int64_t row_bytes) {
@@ -210,8 +221,8 @@ inline double launch_us(const LaunchPlan& lp, int h_kv, int gqa, int num_cus, co
 // partials fit `max_rows` token rows.
 inline int64_t choose_steps(const LaunchPlan& lp, int h_kv, int gqa, int num_cus,
                             const WalkCost& wc, int64_t base, int min_tiles, int64_t row_bytes,
-                            int64_t max_rows) {
-  if ((int)lp.descs.size() > kMaxPlannedSeqs) return base;
+                            int64_t max_rows, double& best_us) {
+  best_us = launch_us(lp, h_kv, gqa, num_cus, wc, base, min_tiles, row_bytes);
   int64_t longest = 1, unsplit = 0;
   for (const SeqDesc& sd : lp.descs) {
     longest = std::max(longest, kv_tiles_of(sd, lp.shape.tile_keys));
@@ -219,17 +230,8 @@ inline int64_t choose_steps(const LaunchPlan& lp, int h_kv, int gqa, int num_cus
   }
   const int64_t slots = (int64_t)num_cus * wc.wgs_per_cu;
   if (unsplit >= kMaxWaves * slots || longest <= min_tiles) return base;
-  auto workgroups = [&](int64_t steps) {
-    int64_t n = 0, n_split, tps;
-    for (const SeqDesc& sd : lp.descs) {
-      split_by_steps(sd, lp.shape.tile_keys, steps, min_tiles, n_split, tps);
-      n += kXcds * ceil_div((int64_t)h_kv * sd.n_row_tiles * n_split, kXcds);
-    }
-    return n;
-  };
   const int64_t allowed = std::min(max_rows, kMaxPartialBytes / row_bytes);
   int64_t best = base, prev = base;
-  double best_us = launch_us(lp, h_kv, gqa, num_cus, wc, base, min_tiles, row_bytes);
   auto consider = [&](int64_t steps) {
     if (steps == prev || partial_rows(lp, steps, min_tiles) > allowed) return;
     prev = steps;
@@ -244,11 +246,11 @@ inline int64_t choose_steps(const LaunchPlan& lp, int h_kv, int gqa, int num_cus
   };
   consider(longest);  // no split at all
   for (int waves = 1; waves <= kMaxWaves; ++waves) {
-    if (workgroups(longest) > waves * slots) continue;
+    if (workgroups(lp, h_kv, longest, min_tiles) > waves * slots) continue;
     int64_t lo = min_tiles, hi = longest;  // the shortest ranges that fit `waves` rounds
     while (lo < hi) {
       const int64_t mid = (lo + hi) / 2;
-      if (workgroups(mid) <= waves * slots) hi = mid; else lo = mid + 1;
+      if (workgroups(lp, h_kv, mid, min_tiles) <= waves * slots) hi = mid; else lo = mid + 1;
     }
     consider(lo);
     if (lo <= min_tiles) break;
@@ -306,12 +308,17 @@ inline void plan_launch(LaunchPlan& lp, int h_kv, int gqa, int64_t steps, int mi
   lp.total_rows = rank;
 }
 
+inline void set_row_tiles(LaunchPlan& lp, int gqa) {
+  for (SeqDesc& sd : lp.descs)
+    sd.n_row_tiles = (int)ceil_div((int64_t)sd.chunk_len * gqa, lp.shape.rows_per_wg);
+}
+
 // The simple rule: ranges short enough for about `target_wgs` equally long workgroups, no
 // split where the row tiles alone are as many.  Also sets the row tiles.
 inline int64_t simple_steps(LaunchPlan& lp, int h_kv, int gqa, int target_wgs) {
   int64_t unsplit_wgs = 0, total_steps = 0, longest = 1;
-  for (SeqDesc& sd : lp.descs) {
-    sd.n_row_tiles = (int)ceil_div((int64_t)sd.chunk_len * gqa, lp.shape.rows_per_wg);
+  set_row_tiles(lp, gqa);
+  for (const SeqDesc& sd : lp.descs) {
     const int64_t kv_tiles = ceil_div((int64_t)sd.kv_len, lp.shape.tile_keys);
     unsplit_wgs += (int64_t)h_kv * sd.n_row_tiles;
     total_steps += (int64_t)h_kv * sd.n_row_tiles * kv_tiles;
@@ -364,9 +371,30 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
     // 256 bytes each, which can cost the last rows)
     int64_t fit = (int64_t)(std::min<size_t>(budget, (size_t)1 << 60) / row_bytes);
     while (fit > 0 && partial_bytes(fit, h_q, head_dim) > budget) --fit;
-    rows_steps = choose_steps(plan.rows, h_kv, gqa, num_cus,
-                              walk_cost(head_dim, plan.rows.q_blocks), rows_steps, kMinTiles,
-                              row_bytes, fit - keys_rows);
+    if ((int)plan.rows.descs.size() <= kMaxPlannedSeqs) {
+      double us, small_us;
+      rows_steps = choose_steps(plan.rows, h_kv, gqa, num_cus,
+                                walk_cost(head_dim, plan.rows.q_blocks), rows_steps, kMinTiles,
+                                row_bytes, fit - keys_rows, us);
+      // At head dim 64 the small workgroups are the alternative: half the granule, short walks
+      // overlapped (777 tokens at 20K, 32/8 heads: 164 -> 155 us; 14 prompts, 24 tiles
+      // on average: 174 -> 163 us; 12 prompts, 14 tiles: 226 -> 215 us; but 1 % longer at 96 and
+      // 288 tiles where both fill the device).  At 128 two of their rings do not fit a unit.
+      if (head_dim == 64 && plan.rows.q_blocks == 2) {
+        LaunchPlan small = plan.rows;
+        small.q_blocks = 1;
+        small.shape.rows_per_wg = kWaves * 32;
+        set_row_tiles(small, gqa);
+        const int64_t steps = choose_steps(small, h_kv, gqa, num_cus, walk_cost(head_dim, 1),
+                                           INT32_MAX, kMinTiles, row_bytes, fit - keys_rows,
+                                           small_us);
+        if (small_us < 0.97 * us &&
+            workgroups(small, h_kv, steps, kMinTiles) > num_cus) {  // else nothing pairs up
+          plan.rows = small;
+          rows_steps = steps;
+        }
+      }
+    }
   }
   if (!plan.rows.descs.empty())
     plan_launch(plan.rows, h_kv, gqa, rows_steps, kMinTiles, plan.part_rows);

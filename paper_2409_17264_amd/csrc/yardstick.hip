@@ -6,7 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "common.h"
-#include "prefill_kernel.h"  // async_load16, lds_address
+#include "prefill_kernel.h"  // async_stream16, lds_address
 
 namespace medha {
 namespace {
@@ -56,7 +56,7 @@ stream_yardstick_kernel(const char* __restrict__ src, size_t n_pieces, uint32_t*
     const char* p = src + piece * kPieceBytes;
 #pragma unroll
     for (int j = 0; j < kLoadsPerPiece; ++j)
-      async_load16(p + j * 1024, (uint32_t)(lane * 16), ring + st * kPieceBytes + j * 1024);
+      async_stream16(p + j * 1024 + lane * 16, ring + st * kPieceBytes + j * 1024);
   };
   uint32_t acc = 0;
   if (w0 < n_pieces) issue(w0, 0);

@@ -540,6 +540,8 @@ def test_plan_keeps_to_the_workspace_it_is_given():
     (8, 2, 64, [300], [900]),                 # 15 row tiles: runs
     (32, 8, 128, [0, 40, 0], [700, 130, 1]),  # a group per die; only the last sequence turned
     (12, 3, 64, [64, 0], [1500, 600]),        # 3 groups of 24 and 10
+    (32, 8, 64, [0, 0, 9, 0, 0, 0], [400, 333, 290, 500, 512, 77]),  # small workgroups, in pairs
+    (16, 8, 64, [2500], [500]),               # the same in KV ranges
 ])
 def test_prompts_whose_walks_differ(h_q, h_kv, d, prefix, chunk):
     """No or little prefix: row tiles walk different numbers of keys, and the slots are dealt out
