@@ -81,36 +81,56 @@ constexpr int64_t kMaxPartialBytes = (int64_t)128 << 20;
 constexpr int kMaxPlannedSeqs = 16;  // launches of more sequences keep the simple rule
 constexpr int kMaxWaves = 8;         // rounds of workgroups per compute unit worth considering
 
-// Workgroups of one length on the fullest accelerator die.
+// Workgroups that walk the same number of tiles, on the fullest accelerator die.
 struct WalkGroup {
+  int64_t tiles, count;
+};
+
+// Slots that are free from the same time on.
+struct FreeSlots {
   double us;
   int64_t count;
 };
 
 // When the last workgroup ends if `machines` slots take the groups in descending length, each
-// workgroup going to the slot that is free first.  Slots free at the same time are kept as one
-// entry, so equal walks cost one step per round of the device.
-inline double makespan(std::vector<WalkGroup>& groups, int64_t machines) {
+// workgroup going to the slot that is free first.  Slots free at the same time are one entry, so
+// equal walks cost one step per round of the device, and the slots a group leaves behind come in
+// ascending order, so they are appended, and merged once with the slots it did not touch.
+inline double makespan(std::vector<WalkGroup>& groups, int64_t machines, const WalkCost& wc) {
   std::sort(groups.begin(), groups.end(),
-            [](const WalkGroup& a, const WalkGroup& b) { return a.us > b.us; });
-  std::vector<WalkGroup> free_at{{0.0, machines}};  // (time, slots), ascending
+            [](const WalkGroup& a, const WalkGroup& b) { return a.tiles > b.tiles; });
+  std::vector<FreeSlots> before, after, merged;  // ascending
+  for (auto* v : {&before, &after, &merged}) v->reserve(2 * machines);
+  before.push_back(FreeSlots{0.0, machines});
   double end = 0.0;
-  for (WalkGroup g : groups)
-    while (g.count > 0) {
-      WalkGroup& first = free_at.front();
-      const int64_t n = std::min(g.count, first.count);
-      const double t = first.us + g.us;
-      end = std::max(end, t);
-      g.count -= n;
+  for (size_t k = 0; k < groups.size();) {
+    const int64_t tiles = groups[k].tiles;
+    int64_t count = 0;
+    for (; k < groups.size() && groups[k].tiles == tiles; ++k) count += groups[k].count;
+    const double us = wc.fixed_us + (double)tiles * wc.tile_us;
+    after.clear();
+    size_t i = 0, j = 0;  // first entries of `before` and `after` not used up
+    while (count > 0) {
+      const bool old = i < before.size() && (j == after.size() || before[i].us <= after[j].us);
+      FreeSlots& first = old ? before[i] : after[j];
+      const int64_t n = std::min(count, first.count);
+      const double t = first.us + us;
+      count -= n;
       first.count -= n;
-      if (first.count == 0) free_at.erase(free_at.begin());
-      auto at = std::lower_bound(free_at.begin(), free_at.end(), t,
-                                 [](const WalkGroup& a, double v) { return a.us < v; });
-      if (at != free_at.end() && at->us == t)
-        at->count += n;
+      if (first.count == 0) ++(old ? i : j);
+      if (!after.empty() && after.back().us == t && j < after.size())
+        after.back().count += n;
       else
-        free_at.insert(at, WalkGroup{t, n});
+        after.push_back(FreeSlots{t, n});
+      end = std::max(end, t);
     }
+    merged.clear();
+    while (i < before.size() || j < after.size()) {
+      const bool old = i < before.size() && (j == after.size() || before[i].us <= after[j].us);
+      merged.push_back(old ? before[i++] : after[j++]);
+    }
+    before.swap(merged);
+  }
   return end;
 }
 
@@ -143,117 +163,203 @@ inline void split_by_steps(const SeqDesc& sd, int tile_keys, int64_t steps, int 
   n_split = ceil_div(kv_tiles, tps);
 }
 
-// Partial token rows of a launch split by `steps`.
-inline int64_t partial_rows(const LaunchPlan& lp, int64_t steps, int min_tiles) {
-  int64_t rows = 0, n_split, tps;
+// Row tiles of one sequence that stand for each other in an estimate: `count` of them walk
+// `tiles` tiles (before the KV axis is cut).
+struct WalkClass {
+  int64_t tiles, count;
+};
+
+// Classes of a launch's triangles, dealt out by their row tiles (a sequence alone has 8).  With 8
+// for every sequence, one plan in 500 is another one, and planning 16 prompts takes twice as long.
+constexpr int kWalkClasses = 32;
+
+// What the estimates of a launch have in common, whatever its KV ranges.
+struct LaunchWalks {
+  std::vector<WalkClass> classes;   // of all sequences, longest walk first within a sequence
+  std::vector<int> first_class;     // of each sequence, and the end
+  std::vector<char> dealt;          // sequences whose walks differ (see decode_slot_dealt)
+  int64_t total_tiles = 0;          // walked by all workgroups
+  int64_t busy = 0, unsplit = 0;    // workgroups without a cut: with keys to walk, and all
+  int64_t key_tiles = 0;            // tiles if every workgroup walked all keys
+  int64_t longest = 1;              // KV tiles of the longest sequence
+};
+
+inline LaunchWalks launch_walks(const LaunchPlan& lp, int h_kv, int gqa) {
+  LaunchWalks lw;
+  int64_t all_row_tiles = 0;
+  for (const SeqDesc& sd : lp.descs) all_row_tiles += sd.n_row_tiles;
+  lw.first_class.reserve(lp.descs.size() + 1);
+  lw.classes.reserve(lp.descs.size() + kWalkClasses);
   for (const SeqDesc& sd : lp.descs) {
-    split_by_steps(sd, lp.shape.tile_keys, steps, min_tiles, n_split, tps);
-    if (n_split > 1) rows += n_split * sd.chunk_len;
+    lw.first_class.push_back((int)lw.classes.size());
+    // up to 8 classes of row tiles stand for a causal triangle
+    const int64_t n_rt = sd.n_row_tiles;
+    const int64_t most = std::min<int64_t>(8, ceil_div(kWalkClasses * n_rt, all_row_tiles));
+    const bool uneven = uneven_walks(sd, lp.shape, gqa);
+    const int64_t classes = uneven ? std::min(n_rt, most) : 1;
+    lw.dealt.push_back(uneven);
+    for (int64_t c = classes; c-- > 0;) {
+      const int64_t lo = c * n_rt / classes, hi = (c + 1) * n_rt / classes;
+      const int64_t t = tiles_at(sd, lp.shape, gqa, uneven ? (lo + hi) / 2 : n_rt - 1);
+      lw.classes.push_back(WalkClass{t, hi - lo});
+      lw.total_tiles += t * (hi - lo) * h_kv;
+      if (t > 0) lw.busy += (hi - lo) * h_kv;
+    }
+    const int64_t kv_tiles = kv_tiles_of(sd, lp.shape.tile_keys);
+    lw.unsplit += n_rt * h_kv;
+    lw.key_tiles += n_rt * h_kv * kv_tiles;
+    lw.longest = std::max(lw.longest, kv_tiles);
   }
-  return rows;
+  lw.first_class.push_back((int)lw.classes.size());
+  return lw;
 }
 
-// Workgroup slots of a launch split by `steps`.
-inline int64_t workgroups(const LaunchPlan& lp, int h_kv, int64_t steps, int min_tiles) {
-  int64_t n = 0, n_split, tps;
+// Workgroups and partial token rows of a launch split by `steps`.
+struct SplitSize {
+  int64_t slots, part_rows;
+};
+
+inline SplitSize split_size(const LaunchPlan& lp, int h_kv, int64_t steps, int min_tiles) {
+  SplitSize s{0, 0};
+  int64_t n_split, tps;
   for (const SeqDesc& sd : lp.descs) {
     split_by_steps(sd, lp.shape.tile_keys, steps, min_tiles, n_split, tps);
-    n += kXcds * ceil_div((int64_t)h_kv * sd.n_row_tiles * n_split, kXcds);
+    s.slots += kXcds * ceil_div((int64_t)h_kv * sd.n_row_tiles * n_split, kXcds);
+    if (n_split > 1) s.part_rows += n_split * sd.chunk_len;
   }
-  return n;
+  return s;
+}
+
+inline double merge_us(int64_t part_rows, int64_t row_bytes) {
+  return part_rows > 0 ? kMergeLaunchUs + (double)(part_rows * row_bytes) / kMergeBytesPerUs : 0.0;
+}
+
+inline int64_t machines_of(int num_cus, const WalkCost& wc) {
+  return std::max<int64_t>(1, num_cus / kXcds) * wc.wgs_per_cu;
+}
+
+// The work of a launch with ranges of at most `steps` tiles, spread evenly: no estimate is less.
+inline double even_us(const LaunchWalks& lw, int64_t steps, int num_cus, const WalkCost& wc) {
+  const int64_t wgs = std::max(lw.busy, lw.total_tiles / steps);
+  return ((double)lw.total_tiles * wc.tile_us + (double)wgs * wc.fixed_us) /
+         (double)(kXcds * machines_of(num_cus, wc));
 }
 
 // Estimated time of a row-split launch whose KV ranges are at most `steps` tiles long.
-inline double launch_us(const LaunchPlan& lp, int h_kv, int gqa, int num_cus, const WalkCost& wc,
-                        int64_t steps, int min_tiles, int64_t row_bytes) {
-  const ModeShape sh = lp.shape;
+inline double launch_us(const LaunchPlan& lp, const LaunchWalks& lw, int h_kv, int num_cus,
+                        const WalkCost& wc, int64_t steps, int min_tiles, int64_t row_bytes) {
   std::vector<WalkGroup> groups;
+  groups.reserve(4 * lw.classes.size());
   int64_t part = 0;
-  for (const SeqDesc& sd : lp.descs) {
+  for (size_t s = 0; s < lp.descs.size(); ++s) {
+    const SeqDesc& sd = lp.descs[s];
     int64_t n_split, tps;
-    split_by_steps(sd, sh.tile_keys, steps, min_tiles, n_split, tps);
+    split_by_steps(sd, lp.shape.tile_keys, steps, min_tiles, n_split, tps);
     if (n_split > 1) part += n_split * sd.chunk_len;
-    // up to 8 classes of row tiles stand for a causal triangle
-    const int64_t n_rt = sd.n_row_tiles;
-    const int64_t t_last = tiles_at(sd, sh, gqa, n_rt - 1);
-    const int64_t classes = uneven_walks(sd, sh, gqa) ? std::min<int64_t>(n_rt, 8) : 1;
-    // Workgroups of the fullest die (see decode_slot_dealt): its whole groups, one of every 8, and an
-    // eighth, rounded up, of what the others hold.
-    const int64_t all = h_kv * n_split, dealt = all / kXcds;
+    // Workgroups of the fullest die: an even launch's equal runs (decode_slot) give it an
+    // eighth, rounded up; decode_slot_dealt gives it one of every 8 whole (head, range) groups,
+    // and an eighth, rounded up, of what the last groups hold.
+    const int c0 = lw.first_class[s], c1 = lw.first_class[s + 1];
+    const int64_t whole_groups = !lw.dealt[s] ? 0 : h_kv * n_split / kXcds;
+    const int64_t from = whole_groups * kXcds;  // the other groups: (range, heads of it)
     int64_t before = 0;
-    auto add = [&](int64_t tiles, int64_t count, bool whole) {
-      if (tiles <= 0) return;
-      int64_t n = count;
-      if (!whole) {
-        n = ceil_div(before + count, kXcds) - ceil_div(before, kXcds);
-        before += count;
-      }
-      if (n > 0) groups.push_back(WalkGroup{wc.fixed_us + (double)tiles * wc.tile_us, n});
+    auto add_whole = [&](int64_t tiles, int64_t n) {
+      if (tiles > 0 && n > 0) groups.push_back(WalkGroup{tiles, n});
     };
-    if (classes == 1) {
-      if (t_last >= tps) add(tps, n_rt * h_kv * (t_last / tps), false);
-      add(t_last % tps, n_rt * h_kv, false);
-      continue;
-    }
-    for (int64_t c = classes; c-- > 0;) {
-      const int64_t lo = c * n_rt / classes, hi = (c + 1) * n_rt / classes;
-      const int64_t t = tiles_at(sd, sh, gqa, (lo + hi) / 2);
-      for (int64_t g = 0; g < dealt && (g * kXcds / h_kv) * tps < t; ++g)
-        add(std::min(tps, t - (g * kXcds / h_kv) * tps), hi - lo, true);
-      const int64_t from = dealt * kXcds;  // the other groups: (split, heads of it)
-      for (int64_t sp = from / h_kv; sp < n_split && sp * tps < t; ++sp)
-        add(std::min(tps, t - sp * tps), (hi - lo) * (h_kv - std::max<int64_t>(0, from - sp * h_kv)),
-            false);
+    auto add_rest = [&](int64_t tiles, int64_t count) {
+      if (tiles <= 0 || count <= 0) return;
+      const int64_t n = ceil_div(before + count, kXcds) - ceil_div(before, kXcds);
+      before += count;
+      if (n > 0) groups.push_back(WalkGroup{tiles, n});
+    };
+    for (int c = c0; c < c1; ++c) {
+      const WalkClass& wcl = lw.classes[c];
+      // `full` ranges are walked to their end, the next one for `left` tiles
+      const int64_t full = wcl.tiles / tps, left = wcl.tiles % tps;
+      const int64_t upto_full = full * h_kv, upto_left = upto_full + (left > 0 ? h_kv : 0);
+      const int64_t w_full = std::min(whole_groups, ceil_div(upto_full, kXcds));
+      const int64_t w_left = std::min(whole_groups, ceil_div(upto_left, kXcds)) - w_full;
+      add_whole(tps, wcl.count * w_full);
+      add_whole(left, wcl.count * w_left);
+      const int64_t r_full = std::max<int64_t>(0, upto_full - from);
+      const int64_t r_left = std::max<int64_t>(0, upto_left - from) - r_full;
+      add_rest(tps, wcl.count * r_full);
+      add_rest(left, wcl.count * r_left);
     }
   }
-  const int64_t machines = std::max<int64_t>(1, num_cus / kXcds) * wc.wgs_per_cu;
-  double us = makespan(groups, machines);
-  if (part > 0) us += kMergeLaunchUs + (double)(part * row_bytes) / kMergeBytesPerUs;
-  return us;
+  return makespan(groups, machines_of(num_cus, wc), wc) + merge_us(part, row_bytes);
 }
 
-// Longest KV range (in tiles) of a row-split launch.  The simple rule (one round of workgroups
-// over the device, rounded up) can leave a second round nearly empty: 47 row tiles in 6 ranges
-// are 282 workgroups on 256 compute units and take twice the time of 256.  So the ranges that
-// fill 1, 2, ... whole rounds as well as possible are compared with it by estimated time: more
-// rounds waste less of the last one, but pay a workgroup's fixed cost each and write more
-// partials.  `base` is the simple rule's answer; it is always allowed, others only if their
-// partials fit `max_rows` token rows.
-inline int64_t choose_steps(const LaunchPlan& lp, int h_kv, int gqa, int num_cus,
+// Longest KV range (in tiles) of a row-split launch, and its estimated time (`best_us`).  The
+// simple rule (one round of workgroups over the device, rounded up) can leave a second round
+// nearly empty: 47 row tiles in 6 ranges are 282 workgroups on 256 compute units and take twice
+// the time of 256.  So the ranges that fill 1, 2, ... whole rounds as well as possible are
+// compared with it by estimated time: more rounds waste less of the last one, but pay a
+// workgroup's fixed cost each and write more partials.  `base` is the simple rule's answer; it
+// is always allowed, others only if their partials fit `max_rows` token rows.
+//
+// Planning is host time on every call, so what cannot win is not simulated: a plan is no faster
+// than its work spread evenly, and its work grows with its workgroups.  (Host time of one plan,
+// simulating every candidate -> now: 16 prompts of 1K median at 8/2 heads, d 64, 38 -> 13 us, and
+// their iteration, which plans twice, 85 -> 69 us; 8/1 heads, d 128, 15 -> 7 us.)
+inline int64_t choose_steps(const LaunchPlan& lp, const LaunchWalks& lw, int h_kv, int num_cus,
                             const WalkCost& wc, int64_t base, int min_tiles, int64_t row_bytes,
                             int64_t max_rows, double& best_us) {
-  best_us = launch_us(lp, h_kv, gqa, num_cus, wc, base, min_tiles, row_bytes);
-  int64_t longest = 1, unsplit = 0;
-  for (const SeqDesc& sd : lp.descs) {
-    longest = std::max(longest, kv_tiles_of(sd, lp.shape.tile_keys));
-    unsplit += (int64_t)h_kv * sd.n_row_tiles;
-  }
   const int64_t slots = (int64_t)num_cus * wc.wgs_per_cu;
-  if (unsplit >= kMaxWaves * slots || longest <= min_tiles) return base;
+  // (launches of very many rounds end within a walk or two of the even spread)
+  best_us = lw.unsplit >= 8 * kMaxWaves * slots
+                ? even_us(lw, lw.longest, num_cus, wc)
+                : launch_us(lp, lw, h_kv, num_cus, wc, base, min_tiles, row_bytes);
+  if (lw.unsplit >= kMaxWaves * slots || lw.longest <= min_tiles) return base;
   const int64_t allowed = std::min(max_rows, kMaxPartialBytes / row_bytes);
   int64_t best = base, prev = base;
-  auto consider = [&](int64_t steps) {
-    if (steps == prev || partial_rows(lp, steps, min_tiles) > allowed) return;
+  // A few idle compute units are not all loss: the part is power-limited, the others clock
+  // higher.  (47 row tiles, 4712 tiles: 16 ranges in 3 rounds, 2 % of them empty, are estimated
+  // at 0.97 of 5 ranges in one round with 8 % empty, and measure the same within 2 %.)
+  constexpr double kWorth = 0.97;
+  auto consider = [&](int64_t steps, int64_t part_rows) {
+    if (steps == prev || part_rows > allowed) return;
     prev = steps;
-    const double us = launch_us(lp, h_kv, gqa, num_cus, wc, steps, min_tiles, row_bytes);
-    // A few idle compute units are not all loss: the part is power-limited, the others clock
-    // higher.  (47 row tiles, 4712 tiles: 16 ranges in 3 rounds, 2 % of them empty, are estimated
-    // at 0.97 of 5 ranges in one round with 8 % empty, and measure the same within 2 %.)
-    if (us < 0.97 * best_us) {
+    if (even_us(lw, steps, num_cus, wc) + merge_us(part_rows, row_bytes) >= kWorth * best_us)
+      return;
+    const double us = launch_us(lp, lw, h_kv, num_cus, wc, steps, min_tiles, row_bytes);
+    if (us < kWorth * best_us) {
       best = steps;
       best_us = us;
     }
   };
-  consider(longest);  // no split at all
+  const SplitSize uncut = split_size(lp, h_kv, lw.longest, min_tiles);
+  consider(lw.longest, uncut.part_rows);
+  const SplitSize finest = split_size(lp, h_kv, min_tiles, min_tiles);
+  int64_t hi = lw.longest;  // the shortest ranges that fit the rounds so far, and their size
+  SplitSize at_hi = uncut;
   for (int waves = 1; waves <= kMaxWaves; ++waves) {
-    if (workgroups(lp, h_kv, longest, min_tiles) > waves * slots) continue;
-    int64_t lo = min_tiles, hi = longest;  // the shortest ranges that fit `waves` rounds
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) / 2;
-      if (workgroups(lp, h_kv, mid, min_tiles) <= waves * slots) hi = mid; else lo = mid + 1;
+    const int64_t room = waves * slots;
+    if (uncut.slots > room) continue;
+    if (even_us(lw, lw.longest, num_cus, wc) >= kWorth * best_us) break;
+    // The shortest ranges that fit: a search that gallops from a guess (all tiles spread evenly,
+    // or what fewer rounds needed, in proportion) and bisects once it has both sides.
+    int64_t lo = min_tiles, step = 1;
+    int64_t probe = hi == lw.longest ? lw.key_tiles / room : hi * (waves - 1) / waves;
+    if (finest.slots <= room) {
+      hi = min_tiles;
+      at_hi = finest;
     }
-    consider(lo);
-    if (lo <= min_tiles) break;
+    while (lo < hi) {
+      probe = std::min(std::max(probe, lo), hi - 1);
+      const SplitSize size = split_size(lp, h_kv, probe, min_tiles);
+      const bool fits = size.slots <= room;
+      if (fits) {
+        hi = probe;
+        at_hi = size;
+      } else {
+        lo = probe + 1;
+      }
+      probe = hi - lo <= step ? (lo + hi) / 2 : fits ? hi - step : lo + step - 1;
+      step *= 2;
+    }
+    consider(hi, at_hi.part_rows);
+    if (hi <= min_tiles) break;
   }
   return best;
 }
@@ -361,19 +467,19 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
   int64_t keys_steps = 1, rows_steps = 1, min_rows = 0;
   if (!plan.keys.descs.empty()) {
     keys_steps = simple_steps(plan.keys, h_kv, gqa, num_cus * 8);
-    min_rows += partial_rows(plan.keys, keys_steps, kMinTiles);
+    min_rows += split_size(plan.keys, h_kv, keys_steps, kMinTiles).part_rows;
   }
   if (!plan.rows.descs.empty()) {
     rows_steps = simple_steps(plan.rows, h_kv, gqa, num_cus);
     const int64_t keys_rows = min_rows;
-    min_rows += partial_rows(plan.rows, rows_steps, kMinTiles);
+    min_rows += split_size(plan.rows, h_kv, rows_steps, kMinTiles).part_rows;
     // token rows of partials that fit the budget (the workspace's two arrays are rounded up to
     // 256 bytes each, which can cost the last rows)
     int64_t fit = (int64_t)(std::min<size_t>(budget, (size_t)1 << 60) / row_bytes);
     while (fit > 0 && partial_bytes(fit, h_q, head_dim) > budget) --fit;
     if ((int)plan.rows.descs.size() <= kMaxPlannedSeqs) {
       double us, small_us;
-      rows_steps = choose_steps(plan.rows, h_kv, gqa, num_cus,
+      rows_steps = choose_steps(plan.rows, launch_walks(plan.rows, h_kv, gqa), h_kv, num_cus,
                                 walk_cost(head_dim, plan.rows.q_blocks), rows_steps, kMinTiles,
                                 row_bytes, fit - keys_rows, us);
       // At head dim 64 the small workgroups are the alternative: half the granule, short walks
@@ -385,13 +491,16 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
         small.q_blocks = 1;
         small.shape.rows_per_wg = kWaves * 32;
         set_row_tiles(small, gqa);
-        const int64_t steps = choose_steps(small, h_kv, gqa, num_cus, walk_cost(head_dim, 1),
-                                           INT32_MAX, kMinTiles, row_bytes, fit - keys_rows,
-                                           small_us);
-        if (small_us < 0.97 * us &&
-            workgroups(small, h_kv, steps, kMinTiles) > num_cus) {  // else nothing pairs up
-          plan.rows = small;
-          rows_steps = steps;
+        const LaunchWalks walks = launch_walks(small, h_kv, gqa);
+        const WalkCost cost = walk_cost(head_dim, 1);
+        if (even_us(walks, walks.longest, num_cus, cost) < 0.97 * us) {
+          const int64_t steps = choose_steps(small, walks, h_kv, num_cus, cost, INT32_MAX,
+                                             kMinTiles, row_bytes, fit - keys_rows, small_us);
+          if (small_us < 0.97 * us && split_size(small, h_kv, steps, kMinTiles).slots >
+                                          num_cus) {  // else nothing pairs up
+            plan.rows = std::move(small);
+            rows_steps = steps;
+          }
         }
       }
     }
