@@ -46,7 +46,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // Asynchronous loads of the 32-key block starting at sequence key `key0`
 // (a multiple of 32, so it spans exactly the two pages page0, page1).
-template <int D>
+template <int D, bool kOnce>
 __device__ __forceinline__ void issue_block(const AttnArgs& args, int page0, int page1, int key0,
                                             int kv_total, int kv_head, uint32_t k_lds,
                                             uint32_t v_lds, int lane) {
@@ -64,9 +64,36 @@ __device__ __forceinline__ void issue_block(const AttnArgs& args, int page0, int
     const int64_t off =
         (((int64_t)page * args.h_kv + kv_head) * kPageSize + (t & 15)) * (D * 2);
     const uint32_t lds_off = j * G::kRowsPerInstr * (D * 2);
-    async_stream16(kp + off + Swz<D>::k(row, pos) * 16, k_lds + lds_off);
-    async_stream16(vp + off + Swz<D>::v(row, pos) * 16, v_lds + lds_off);
+    async_stream16<kOnce>(kp + off + Swz<D>::k(row, pos) * 16, k_lds + lds_off);
+    async_stream16<kOnce>(vp + off + Swz<D>::v(row, pos) * 16, v_lds + lds_off);
   }
+}
+
+// Keys and values that other sequences of the launch read too are worth keeping in the caches,
+// those that one workgroup alone reads are not (async_stream16).  Which it is stands in the page
+// table only: sequences that share pages share a prefix (or, as several queries against one KV
+// shard, all keys), so the pages are at the same place of their tables, and one look at the
+// others' entry for the range's first page tells.  It takes one load per lane and 0.1 to 0.7 us
+// a launch (64 decodes of 2K median 117.4 -> 118.0 us a pass); the walk stands in the code twice
+// because a branch at every load costs short launches as much again.  Beyond the last-level
+// cache a sequence's K/V is gone before the next one reads it, shared or not.  (32/8 heads,
+// d 128: 64 decodes that share 8K keys, 161 us loaded non-temporally, 115 us through the caches;
+// 16 that share 32K, 253 and 165; 4 that share 128K, 537 MB each, 329 and 358.)
+constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;
+
+// `other_*`: of the sequence this lane looks at.
+template <int D>
+__device__ __forceinline__ bool read_by_others(const AttnArgs& args, const SeqDesc& sd, int seq,
+                                               int64_t other_pt_off, int other_kv_len, int key0,
+                                               int lane) {
+  if (args.n_seq == 1 || key0 >= sd.kv_len) return false;
+  if ((int64_t)sd.kv_len * args.h_kv * (4 * D) > kLastLevelCacheBytes) return false;
+  const bool has = lane < args.n_seq && lane != seq && key0 < other_kv_len;
+  const int page_index = key0 / kPageSize;
+  const int own = args.page_table[sd.pt_off + page_index];
+  // (a lane with nothing to compare reads the range's own entry: no branch around the load)
+  const int page = args.page_table[(has ? other_pt_off : sd.pt_off) + page_index];
+  return __any(has && page == own);
 }
 
 // STAGES = blocks in flight per wavefront.  2 (128 KiB of LDS, one workgroup per compute unit)
@@ -83,7 +110,16 @@ decode_kernel(const AttnArgs args) {
   __shared__ __attribute__((aligned(1024))) char lds[G::kLdsBytes];
 
   const SeqDesc* descs = args.inline_descs;
-  const SeqDesc sd = uniform(descs[find_seq_slot(descs, args.n_seq, blockIdx.x)]);
+  const int lane = threadIdx.x & 63;
+  int64_t other_pt_off = 0;
+  int other_kv_len = 0;
+  if (args.n_seq > 1) {  // (read before the search so that both share one trip to memory)
+    const SeqDesc& other = descs[min(lane, args.n_seq - 1)];
+    other_pt_off = other.pt_off;
+    other_kv_len = other.kv_len;
+  }
+  const int seq = find_seq_slot(descs, args.n_seq, blockIdx.x);
+  const SeqDesc sd = uniform(descs[seq]);
   // one row tile per sequence here, so a slot is just (KV head, split)
   const SlotItem it = decode_slot(blockIdx.x - sd.work_start, args.h_kv, sd.n_split, 1);
   if (!it.valid) return;
@@ -92,8 +128,11 @@ decode_kernel(const AttnArgs args) {
   const int gqa = args.h_q / args.h_kv;
   const int n_rows = sd.chunk_len * gqa;  // <= 32
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
   const int col = lane & 31, half = lane >> 5;
+
+  const int k_begin = split * sd.tiles_per_split * G::kSplitKeys;
+  const bool cached =
+      read_by_others<D>(args, sd, seq, other_pt_off, other_kv_len, k_begin, lane);
 
   RowBlock<D> rb;
   rb.init(fabsf(args.scale_log2), lane);
@@ -117,7 +156,6 @@ decode_kernel(const AttnArgs args) {
 
   // This workgroup's key range and its 32-key blocks.
   const int keys_needed = max(0, min(kv_total, sd.prefix_len + sd.chunk_len));  // last row's
-  const int k_begin = split * sd.tiles_per_split * G::kSplitKeys;
   const int k_end = min(keys_needed, k_begin + sd.tiles_per_split * G::kSplitKeys);
   const int n_blocks = k_end > k_begin ? (k_end - k_begin + G::kBlockKeys - 1) / G::kBlockKeys : 0;
   const int unmasked_keys = max(0, min(kv_total, sd.prefix_len + 1));  // visible to every row
@@ -128,21 +166,23 @@ decode_kernel(const AttnArgs args) {
   const char* ring = lds + wave * (G::kStagesPerWave * G::kBlockBytes);
 
   // issue block b into stage st (both wave-uniform)
-  auto issue = [&](int b, int st) {
+  auto issue = [&](int b, int st, auto once_tag) {
+    constexpr bool kOnce = decltype(once_tag)::value;
     const int key0 = k_begin + b * G::kBlockKeys;
     const int pi = __builtin_amdgcn_readfirstlane(key0 >> 4);
     const int page0 = pt[pi];
     const int page1 = pt[min(pi + 1, last_page)];
     const uint32_t base = ring_lds + st * G::kBlockBytes;
-    issue_block<D>(args, page0, page1, key0, kv_total, kv_head, base, base + G::kHalfBytes, lane);
+    issue_block<D, kOnce>(args, page0, page1, key0, kv_total, kv_head, base,
+                          base + G::kHalfBytes, lane);
   };
   // Walks this wavefront's blocks b0, b0+4, ... < b_end with two in flight.
   // Self-contained: starts and ends with no load in flight.  MASK applies the
   // per-row key limit (only the last blocks of a sequence need it).
-  auto run_blocks = [&](int b0, int b_end, auto mask_tag) {
+  auto run_blocks = [&](int b0, int b_end, auto mask_tag, auto once) {
     constexpr bool MASK = decltype(mask_tag)::value;
-    if (b0 < b_end) issue(b0, 0);
-    if (STAGES == 2 && b0 + kWaves < b_end) issue(b0 + kWaves, 1);
+    if (b0 < b_end) issue(b0, 0, once);
+    if (STAGES == 2 && b0 + kWaves < b_end) issue(b0 + kWaves, 1, once);
     int st = 0;
     for (int b = b0; b < b_end; b += kWaves, st ^= (STAGES - 1)) {
       if (STAGES == 2 && b + kWaves < b_end)
@@ -152,15 +192,20 @@ decode_kernel(const AttnArgs args) {
       const char* base = ring + st * G::kBlockBytes;
       rb.template step<1, MASK>(base, base + G::kHalfBytes, k_begin + b * G::kBlockKeys, half);
       // every LDS read of the stage has returned (its data fed the matrix cores)
-      if (b + STAGES * kWaves < b_end) issue(b + STAGES * kWaves, st);
+      if (b + STAGES * kWaves < b_end) issue(b + STAGES * kWaves, st, once);
     }
   };
   // blocks below n_unmasked are visible to every row; this wavefront's first block at or
   // above it is the smallest wave + 4i >= n_unmasked
   const int n_unmasked = min(n_blocks, max(0, unmasked_keys - k_begin) / G::kBlockKeys);
   const int first_masked = wave + ((max(0, n_unmasked - wave) + kWaves - 1) / kWaves) * kWaves;
-  run_blocks(wave, n_unmasked, std::false_type{});
-  run_blocks(first_masked, n_blocks, std::true_type{});
+  if (cached) {
+    run_blocks(wave, n_unmasked, std::false_type{}, std::false_type{});
+    run_blocks(first_masked, n_blocks, std::true_type{}, std::false_type{});
+  } else {
+    run_blocks(wave, n_unmasked, std::false_type{}, std::true_type{});
+    run_blocks(first_masked, n_blocks, std::true_type{}, std::true_type{});
+  }
 
   // Combine the 4 wavefronts' (m, l, O) over their disjoint keys through LDS.
   const bool direct = sd.n_split == 1;

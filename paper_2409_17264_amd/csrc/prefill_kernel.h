@@ -54,16 +54,24 @@ __device__ __forceinline__ void async_load16(const void* base_uniform, uint32_t 
                : "s"(lds_addr_uniform), "v"(lane_off), "s"(base_uniform)
                : "m0", "memory");
 }
-// The same with a per-lane address, for data that is read once: the non-temporal hint keeps
-// the stream from being allocated in the caches on its way, which is worth a tenth of the
-// rate.  For the key-split kernel, where one workgroup alone reads a key: 1M keys in 4 shards,
-// 8 KV heads, 706 -> 643 us with both merges (6.1 -> 6.7 TB/s); 64 decodes of 2K median 136 ->
-// 120 us, 128 of 8K 812 -> 726 us; wider scopes (sc0, sc1) with the hint change nothing.
+// The same with a per-lane address.  kOnce: with the non-temporal hint, for data that nobody
+// else reads soon: the stream is not allocated in the caches on its way, which is worth a tenth
+// of the rate.  (Key-split kernel: 1M keys in 4 shards, 8 KV heads, 706 -> 643 us with both
+// merges, 6.1 -> 6.7 TB/s; 64 decodes of 2K median 136 -> 120 us, 128 of 8K 812 -> 726 us; a
+// single decode of 2K from a cold cache 16.3 -> 15.1 us a pass; wider scopes, sc0 and sc1, with
+// the hint change nothing.)
+template <bool kOnce>
 __device__ __forceinline__ void async_stream16(const void* gptr, uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
-               :
-               : "s"(lds_addr_uniform), "v"(gptr)
-               : "m0", "memory");
+  if constexpr (kOnce)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                 :
+                 : "s"(lds_addr_uniform), "v"(gptr)
+                 : "m0", "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds_addr_uniform), "v"(gptr)
+                 : "m0", "memory");
 }
 
 // Byte address of a __shared__ object inside the workgroup's LDS allocation.

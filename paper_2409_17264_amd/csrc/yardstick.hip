@@ -56,7 +56,7 @@ stream_yardstick_kernel(const char* __restrict__ src, size_t n_pieces, uint32_t*
     const char* p = src + piece * kPieceBytes;
 #pragma unroll
     for (int j = 0; j < kLoadsPerPiece; ++j)
-      async_stream16(p + j * 1024 + lane * 16, ring + st * kPieceBytes + j * 1024);
+      async_stream16<true>(p + j * 1024 + lane * 16, ring + st * kPieceBytes + j * 1024);
   };
   uint32_t acc = 0;
   if (w0 < n_pieces) issue(w0, 0);

@@ -624,3 +624,52 @@ def test_random_batches(seed):
     out, lse = gpu_prefill(b)
     ro, rl = oracle_prefill(b)
     check(out, lse, ro, rl, f"random batch seed {seed}: hq{h_q} hkv{h_kv} d{d} n{n}")
+
+
+# ------------------------------------------------------------ pages that sequences share
+def _share_prefix(b, shared):
+    """Sequence i takes its first shared[i] pages from sequence 0's table."""
+    for i, n in enumerate(shared):
+        b.page_table[b.page_table_offs[i]:b.page_table_offs[i] + n] = b.page_table[:n]
+
+
+@pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk,shared", [
+    # all, some, none of the pages, and one that is shorter than the others' shared part
+    (32, 8, 128, [4000, 4100, 3000, 900, 5000], [1, 1, 1, 1, 1], [0, 250, 100, 56, 0]),
+    (8, 2, 64, [2500, 2500, 70, 2600], [1, 3, 1, 8], [0, 156, 1, 0]),
+    # two launches of 64 and 6 sequences; the second holds sharers of the first's pages only
+    (4, 1, 128, [300 + 7 * i for i in range(70)], [1] * 70, [0] + [i % 19 for i in range(1, 70)]),
+])
+def test_decodes_that_share_pages(h_q, h_kv, d, prefix, chunk, shared):
+    b = wl.make_prefill_batch("shared", h_q, h_kv, d, prefix, chunk, seed=len(prefix))
+    _share_prefix(b, shared)
+    ro, rl = oracle_prefill(b)
+    out, lse = gpu_prefill(to_dev(b))
+    check(out, lse, ro, rl, f"shared pages hq{h_q} d{d} {len(prefix)}")
+
+
+def test_shared_pages_are_served_from_the_caches():
+    """16 decodes of 32K keys that share all but their last pages, 134 MB, against 16 that share
+    none, 2.1 GB.  Loads that bypass the caches fetch the shared pages anew for most sequences:
+    0.77 of the time measured, against 0.5."""
+    n, keys = 16, 32768
+    times = []
+    b = wl.make_prefill_batch("cached", 32, 8, 128, [keys - 1] * n, [1] * n, seed=3, device="cuda")
+    out = torch.empty((n, 32, 128), dtype=torch.float32, device="cuda")
+    lse = torch.empty((n, 32), dtype=torch.float32, device="cuda")
+    ws = torch.empty(medha.chunked_prefill_workspace_bytes(b.prefix_len, b.chunk_len, 32, 8, 128),
+                     dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        pt = torch.from_numpy(b.page_table).cuda()
+        spans = []
+        for _ in range(30):
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            medha.chunked_prefill_attn(b.q, b.k_pool, b.v_pool, pt, b.page_table_offs,
+                                       b.prefix_len, b.chunk_len, b.scale, out, lse, ws)
+            t1.record()
+            torch.cuda.synchronize()
+            spans.append(t0.elapsed_time(t1))
+        times.append(float(np.median(spans)))
+        _share_prefix(b, [0] + [keys // 16 - 2] * (n - 1))
+    assert times[1] < 0.64 * times[0], times
