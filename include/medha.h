@@ -90,8 +90,10 @@ typedef struct medha_kv_cache {
  *                    medha_chunked_prefill_workspace_bytes(...) bytes; contents
  *                    are scratch (split-KV partials); may be NULL when that
  *                    size is <= 256 (nothing is split).  A smaller one is refused
- *                    only below what the plan with the fewest partials takes; in
- *                    between, the fastest plan that fits it is used.
+ *                    below the partials of the simple rule, which cuts the keys into
+ *                    about one workgroup per compute unit (refused even where the
+ *                    plan chosen would write fewer); in between, the fastest plan
+ *                    that fits it is used.
  *
  * Work is split over query tiles and, when those are too few to fill the GPU,
  * also over KV ranges whose partials are merged on the same stream.  Sequence
@@ -118,9 +120,9 @@ size_t medha_chunked_prefill_workspace_bytes(const int32_t* prefix_len, const in
  * part of the library's device image (every GPU the library runs on holds its own copy
  * until the process ends).  The call allocates nothing and calls no allocating routine;
  * its first call on a device looks the array's address up (make that call outside a
- * graph capture).  The plan is the fastest one whose partials fit the array; a batch that
- * could not do with MEDHA_NOALLOC_SCRATCH_BYTES of workspace is refused with
- * MEDHA_ERR_WORKSPACE and nothing is enqueued.  All calls on one GPU share
+ * graph capture).  The plan is the fastest one whose partials fit the array; a batch for
+ * which medha_chunked_prefill_attn would refuse a workspace of MEDHA_NOALLOC_SCRATCH_BYTES
+ * is refused with MEDHA_ERR_WORKSPACE and nothing is enqueued.  All calls on one GPU share
  * that GPU's array: calls that overlap on one GPU (different streams, or graphs
  * replayed concurrently) race on it and must be serialised by the caller.  Nothing in
  * the array has to start at zero: every partial is written before it is read.
@@ -244,7 +246,8 @@ int medha_kv_append(const void* k_new, const void* v_new, const medha_kv_cache* 
  * Introspection of the launch plan (host only; needs no GPU).  How the library
  * would lay a chunked-prefill batch out over workgroups on a device with
  * num_cus compute units (0 = the current device, or 256 if there is none):
- * per sequence the kernel it goes to, its query-row tiling and its KV split.
+ * per sequence the kernel it goes to, its query-row tiling and its KV split, and
+ * the workspace size that the query above reports.
  * A decode item of kv_len n is the sequence (prefix_len n - 1, chunk_len 1),
  * so prefix_len may be -1 here.  medha_describe_slot maps a workgroup slot of
  * a sequence (0 <= slot < n_slots) to its work item and returns 1, or 0 for an

@@ -439,7 +439,7 @@ int medha_describe_plan(const int32_t* prefix_len, const int32_t* chunk_len, int
   }
   if (grid_rows) *grid_rows = plan.rows.n_slots;
   if (grid_keys) *grid_keys = plan.keys.n_slots;
-  if (workspace_bytes) *workspace_bytes = plan.bytes;
+  if (workspace_bytes) *workspace_bytes = plan.workspace_bytes();
   return MEDHA_OK;
 }
 

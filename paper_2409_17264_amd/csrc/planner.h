@@ -32,10 +32,12 @@ struct Plan {
   int64_t part_rows = 0;  // token rows of split-KV partials (both launches)
   // workspace layout (byte offsets, 256-aligned)
   size_t off_part_o = 0, off_part_lse = 0, bytes = 0;
-  // partials of the plan with the least scratch: what a caller has to bring at least
+  // partials of the simple rule's ranges: what a caller has to bring at least, also where the
+  // plan chosen writes fewer (a cut that does not pay is dropped), so that what is refused
+  // depends on the sizes alone
   int64_t min_part_rows = 0;
   size_t min_bytes = 0;
-  // what callers are told to bring: enough for this plan and for any smaller choice
+  // what callers are told to bring
   size_t workspace_bytes() const { return std::max(bytes, min_bytes); }
 };
 

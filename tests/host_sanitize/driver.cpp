@@ -97,7 +97,7 @@ static void check_plan(const std::vector<int32_t>& prefix, const std::vector<int
   CHECK(grid_rows == total[0] && grid_keys == total[1]);
   CHECK(ws >= (size_t)part_rows * h_q * (d + 1) * 4);
   CHECK(ws == medha_chunked_prefill_workspace_bytes(prefix.data(), chunk.data(), n, h_q, h_kv, d) ||
-        cus != 0);
+        cus != 256);  // (the query plans for 256 where there is no device)
 }
 
 static void planner_fuzz(std::mt19937_64& rng) {

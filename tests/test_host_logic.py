@@ -44,6 +44,25 @@ def test_workspace_queries_reject_bad_arguments():
     assert medha.chunked_prefill_workspace_bytes([100], [16], 8, 2, 128) >= 256
 
 
+def _simple_rule_rows(prefix, chunk, h_q, h_kv, num_cus):
+    """Partial token rows if the keys are cut into about one workgroup per compute unit (key-split
+    launches: eight): the least workspace a call has to bring."""
+    gqa, total = h_q // h_kv, 0
+    rows_per_wg = 256 if max(c * gqa for c in chunk) >= 256 else 128
+    for mode, rows, tile, target in ((0, rows_per_wg, 64, num_cus), (1, 32, 128, 8 * num_cus)):
+        seqs = [(h_kv * -(-c * gqa // rows), -(-(p + c) // tile), c)
+                for p, c in zip(prefix, chunk) if (c * gqa <= 32) == (mode == 1)]
+        if sum(wgs for wgs, _, _ in seqs) >= target:
+            continue
+        steps = max(1, -(-sum(wgs * tiles for wgs, tiles, _ in seqs) // target))
+        for _, tiles, c in seqs:
+            tiles = max(1, tiles)
+            n = max(1, min(-(-tiles // steps), max(1, tiles // 4)))
+            n = -(-tiles // -(-tiles // n))
+            total += n * c if n > 1 else 0
+    return total
+
+
 def _check_plan(prefix, chunk, h_q, h_kv, d, num_cus):
     entries, grid_rows, grid_keys, ws = medha.describe_plan(prefix, chunk, h_q, h_kv, d, num_cus)
     gqa = h_q // h_kv
@@ -92,7 +111,8 @@ def _check_plan(prefix, chunk, h_q, h_kv, d, num_cus):
             assert prev_walk is None or walk <= prev_walk
             prev_walk = walk
         assert end == grid
-    need = part_rows * h_q * (d + 1) * 4
+    rows = max(part_rows, _simple_rule_rows(prefix, chunk, h_q, h_kv, num_cus))
+    need = rows * h_q * (d + 1) * 4
     assert need <= ws <= need + 1024 + 64 * len(prefix)
     return entries, grid_rows, grid_keys
 
@@ -127,6 +147,17 @@ def test_plans_of_ragged_batches():
     # a decode over zero keys is planned too
     e, _, _ = _check_plan([-1, 0], [1, 1], 8, 2, 128, 256)
     assert e[0].n_split == 1
+
+
+@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,d", [
+    ([10000], [7885], 8, 1, 128),             # planned without a cut, which the simple rule makes
+    ([36000], [1700], 8, 1, 128),             # more ranges than the simple rule's
+    ([1024], [256], 2, 1, 64),
+    ([0] * 5, [300, 1, 2000, 77, 1], 8, 2, 64),
+])
+def test_described_workspace_is_what_a_call_has_to_bring(prefix, chunk, h_q, h_kv, d):
+    described = medha.describe_plan(prefix, chunk, h_q, h_kv, d, 256)[3]
+    assert described == medha.chunked_prefill_workspace_bytes(prefix, chunk, h_q, h_kv, d)
 
 
 @pytest.mark.parametrize("prefix,chunk,h_q,h_kv,d", [
