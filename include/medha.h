@@ -249,10 +249,15 @@ int medha_kv_append(const void* k_new, const void* v_new, const medha_kv_cache* 
  * per sequence the kernel it goes to, its query-row tiling and its KV split, and
  * the workspace size that the query above reports.
  * A decode item of kv_len n is the sequence (prefix_len n - 1, chunk_len 1),
- * so prefix_len may be -1 here.  medha_describe_slot maps a workgroup slot of
- * a sequence (0 <= slot < n_slots) to its work item and returns 1, or 0 for an
- * idle padding slot.  These two calls exist for tests and tuning; they launch
- * nothing.
+ * so prefix_len may be -1 here.  medha_describe_plan_slot plans the same batch and
+ * says what the workgroup in slot `slot` (0 <= slot < grid) of the launches of one
+ * mode works on: the sequence (its place in the batch), KV head, KV range and row
+ * tile; it returns 1, or 0 for an idle padding slot (only the sequence is set).
+ * medha_describe_slot knows the sizes of one sequence only (0 <= slot < n_slots) and
+ * gives the order of sequences whose row tiles walk about the same number of keys:
+ * all key-split ones and row-split ones with a long prefix.  Prompts and first
+ * chunks are handed out in another order.  These calls exist for tests and tuning;
+ * they launch nothing.
  */
 typedef struct medha_plan_entry {
   int32_t mode;            /* 0: row-split prefill kernel, 1: key-split decode kernel */
@@ -269,6 +274,11 @@ int medha_describe_plan(const int32_t* prefix_len, const int32_t* chunk_len, int
                         int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
                         int32_t num_cus, medha_plan_entry* entries /* host [batch] */,
                         int32_t* grid_rows, int32_t* grid_keys, size_t* workspace_bytes);
+
+int medha_describe_plan_slot(const int32_t* prefix_len, const int32_t* chunk_len, int32_t batch,
+                             int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                             int32_t num_cus, int32_t mode, int32_t slot, int32_t* seq,
+                             int32_t* kv_head, int32_t* split, int32_t* row_tile);
 
 int medha_describe_slot(int32_t slot, int32_t num_kv_heads, int32_t n_split, int32_t n_row_tiles,
                         int32_t* kv_head, int32_t* split, int32_t* row_tile);

@@ -28,6 +28,7 @@ EXPORTS = (
     "medha_lse_merge",
     "medha_kv_append",
     "medha_describe_plan",
+    "medha_describe_plan_slot",
     "medha_describe_slot",
     "medha_strerror",
     "medha_abi_version",
@@ -94,6 +95,10 @@ def load_library():
     lib.medha_describe_plan.argtypes = [vp, vp, i32, i32, i32, i32, i32, ctypes.POINTER(PlanEntry),
                                         ctypes.POINTER(i32), ctypes.POINTER(i32),
                                         ctypes.POINTER(sz)]
+    lib.medha_describe_plan_slot.restype = ctypes.c_int
+    lib.medha_describe_plan_slot.argtypes = [vp, vp, i32, i32, i32, i32, i32, i32, i32,
+                                             ctypes.POINTER(i32), ctypes.POINTER(i32),
+                                             ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.medha_describe_slot.restype = ctypes.c_int
     lib.medha_describe_slot.argtypes = [i32, i32, i32, i32, ctypes.POINTER(i32),
                                         ctypes.POINTER(i32), ctypes.POINTER(i32)]
@@ -168,8 +173,23 @@ def describe_plan(prefix_len, chunk_len, num_q_heads: int, num_kv_heads: int, he
     return list(entries)[:len(pre)], g_rows.value, g_keys.value, ws.value
 
 
+def describe_plan_slot(prefix_len, chunk_len, num_q_heads: int, num_kv_heads: int, head_dim: int,
+                       num_cus: int, mode: int, slot: int):
+    """Host-only: (sequence, kv_head, split, row_tile) of a workgroup slot of the plan's launches
+    of one mode, or None if idle."""
+    lib = load_library()
+    pre, chk = _host(prefix_len, np.int32), _host(chunk_len, np.int32)
+    out = [ctypes.c_int32(0) for _ in range(4)]
+    rc = lib.medha_describe_plan_slot(_hp(pre), _hp(chk), len(pre), num_q_heads, num_kv_heads,
+                                      head_dim, num_cus, mode, slot, *map(ctypes.byref, out))
+    if rc < 0:
+        _check(rc)
+    return tuple(x.value for x in out) if rc == 1 else None
+
+
 def describe_slot(slot: int, num_kv_heads: int, n_split: int, n_row_tiles: int):
-    """Host-only: (kv_head, split, row_tile) of a workgroup slot, or None if idle."""
+    """Host-only: (kv_head, split, row_tile) of a workgroup slot, or None if idle; of sequences
+    whose row tiles walk about the same number of keys (describe_plan_slot: of any)."""
     lib = load_library()
     h, s, r = ctypes.c_int32(0), ctypes.c_int32(0), ctypes.c_int32(0)
     rc = lib.medha_describe_slot(slot, num_kv_heads, n_split, n_row_tiles, ctypes.byref(h),

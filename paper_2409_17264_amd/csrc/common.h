@@ -144,6 +144,18 @@ __host__ __device__ inline SlotItem decode_slot_dealt(int u, int h_kv, int n_spl
   return r;
 }
 
+// Work item of slot `u` (counted from the sequence's first) of a row-split launch.  The launch's
+// last sequence starts with its longest walks, so that the short ones end the launch (one prompt
+// of 5959 tokens at 32/8 heads: 327 -> 306 us).  Sequences before it have others behind them to
+// fill the device; eight prompts take 1.5 % longer if all do it.
+__host__ __device__ inline SlotItem row_split_item(const SeqDesc& sd, int u, int h_kv,
+                                                   bool last_of_launch) {
+  SlotItem r = sd.dealt ? decode_slot_dealt(u, h_kv, sd.n_split, sd.n_row_tiles)
+                        : decode_slot(u, h_kv, sd.n_split, sd.n_row_tiles);
+  if (sd.dealt && last_of_launch) r.row_tile = sd.n_row_tiles - 1 - r.row_tile;
+  return r;
+}
+
 // Index of the last of n <= 64 ascending keys that is <= value, key(i) being key i; n >= 1 and
 // key(0) <= value.  All 64 lanes have to be active.  A wavefront that asks for one value reads a
 // key per lane and counts: one trip to memory where a binary search takes six dependent ones

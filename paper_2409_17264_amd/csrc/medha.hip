@@ -218,6 +218,26 @@ size_t prefill_workspace(const int32_t* prefix_len, const int32_t* chunk_len, in
   return least ? plan.min_bytes : plan.workspace_bytes();
 }
 
+// The plan that the introspection calls describe.
+int described_plan(const int32_t* prefix_len, const int32_t* chunk_len, int32_t batch,
+                   int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t num_cus,
+                   Plan& plan) {
+  if (batch < 0 || (batch > 0 && (prefix_len == nullptr || chunk_len == nullptr)))
+    return MEDHA_ERR_INVALID_ARG;
+  const int rc = check_heads(num_q_heads, num_kv_heads, head_dim, kPageSize);
+  if (rc != MEDHA_OK) return rc;
+  std::vector<SeqInput> seqs(batch);
+  int64_t row = 0;
+  for (int b = 0; b < batch; ++b) {
+    if (prefix_len[b] < -1 || chunk_len[b] < 1) return MEDHA_ERR_INVALID_ARG;
+    seqs[b] = SeqInput{0, (int32_t)row, (int32_t)row, chunk_len[b], prefix_len[b]};
+    row += chunk_len[b];
+  }
+  plan = make_plan(seqs.data(), batch, num_q_heads, num_kv_heads, head_dim,
+                   num_cus > 0 ? num_cus : current_num_cus());
+  return MEDHA_OK;
+}
+
 }  // namespace
 }  // namespace medha
 
@@ -407,20 +427,11 @@ int medha_describe_plan(const int32_t* prefix_len, const int32_t* chunk_len, int
                         int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
                         int32_t num_cus, medha_plan_entry* entries, int32_t* grid_rows,
                         int32_t* grid_keys, size_t* workspace_bytes) {
-  if (batch < 0 || (batch > 0 && (prefix_len == nullptr || chunk_len == nullptr ||
-                                  entries == nullptr)))
-    return MEDHA_ERR_INVALID_ARG;
-  int rc = check_heads(num_q_heads, num_kv_heads, head_dim, kPageSize);
+  if (batch > 0 && entries == nullptr) return MEDHA_ERR_INVALID_ARG;
+  Plan plan;
+  const int rc = described_plan(prefix_len, chunk_len, batch, num_q_heads, num_kv_heads, head_dim,
+                                num_cus, plan);
   if (rc != MEDHA_OK) return rc;
-  std::vector<SeqInput> seqs(batch);
-  int64_t row = 0;
-  for (int b = 0; b < batch; ++b) {
-    if (prefix_len[b] < -1 || chunk_len[b] < 1) return MEDHA_ERR_INVALID_ARG;
-    seqs[b] = SeqInput{0, (int32_t)row, (int32_t)row, chunk_len[b], prefix_len[b]};
-    row += chunk_len[b];
-  }
-  const Plan plan = make_plan(seqs.data(), batch, num_q_heads, num_kv_heads, head_dim,
-                              num_cus > 0 ? num_cus : current_num_cus());
   for (int mode = 0; mode < 2; ++mode) {
     const LaunchPlan& lp = mode == 0 ? plan.rows : plan.keys;
     for (size_t i = 0; i < lp.descs.size(); ++i) {
@@ -441,6 +452,32 @@ int medha_describe_plan(const int32_t* prefix_len, const int32_t* chunk_len, int
   if (grid_keys) *grid_keys = plan.keys.n_slots;
   if (workspace_bytes) *workspace_bytes = plan.workspace_bytes();
   return MEDHA_OK;
+}
+
+int medha_describe_plan_slot(const int32_t* prefix_len, const int32_t* chunk_len, int32_t batch,
+                             int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                             int32_t num_cus, int32_t mode, int32_t slot, int32_t* seq,
+                             int32_t* kv_head, int32_t* split, int32_t* row_tile) {
+  Plan plan;
+  const int rc = described_plan(prefix_len, chunk_len, batch, num_q_heads, num_kv_heads, head_dim,
+                                num_cus, plan);
+  if (rc != MEDHA_OK) return rc;
+  const LaunchPlan& lp = mode == 0 ? plan.rows : plan.keys;
+  if (mode < 0 || mode > 1 || slot < 0 || slot >= lp.n_slots) return MEDHA_ERR_INVALID_ARG;
+  size_t i = 0;
+  while (i + 1 < lp.descs.size() && lp.descs[i + 1].work_start <= slot) ++i;
+  const SeqDesc& sd = lp.descs[i];
+  const bool last = i + 1 == lp.descs.size() || (i + 1) % kMaxInlineSeq == 0;  // of its launch
+  const int u = slot - sd.work_start;
+  const SlotItem it = mode == 0 ? row_split_item(sd, u, num_kv_heads, last)
+                                : decode_slot(u, num_kv_heads, sd.n_split, 1);
+  if (seq) *seq = lp.seq_index[i];
+  if (it.valid) {
+    if (kv_head) *kv_head = it.kv_head;
+    if (split) *split = it.split;
+    if (row_tile) *row_tile = it.row_tile;
+  }
+  return it.valid;
 }
 
 int medha_describe_slot(int32_t slot, int32_t num_kv_heads, int32_t n_split, int32_t n_row_tiles,

@@ -708,16 +708,10 @@ __global__ void __launch_bounds__(512) prefill_kernel(const AttnArgs args) {
   const int seq = find_seq_slot(descs, args.n_seq, blockIdx.x);
   const SeqDesc sd = uniform(descs[seq]);
 
-  const int slot = blockIdx.x - sd.work_start;
-  const SlotItem it = sd.dealt ? decode_slot_dealt(slot, args.h_kv, sd.n_split, sd.n_row_tiles)
-                               : decode_slot(slot, args.h_kv, sd.n_split, sd.n_row_tiles);
+  const SlotItem it =
+      row_split_item(sd, blockIdx.x - sd.work_start, args.h_kv, seq == args.n_seq - 1);
   if (!it.valid) return;
-  const int kv_head = it.kv_head, split = it.split;
-  // The launch's last sequence starts with its longest walks, so that the short ones end the
-  // launch (one prompt of 5959 tokens at 32/8 heads: 327 -> 306 us).  Sequences before it have
-  // others behind them to fill the device; eight prompts take 1.5 % longer if all do it.
-  const int row_tile = sd.dealt && seq == args.n_seq - 1 ? sd.n_row_tiles - 1 - it.row_tile
-                                                          : it.row_tile;
+  const int row_tile = it.row_tile, kv_head = it.kv_head, split = it.split;
 
   const int gqa = args.h_q / args.h_kv;
   const int n_rows = sd.chunk_len * gqa;

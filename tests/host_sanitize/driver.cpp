@@ -84,6 +84,21 @@ static void check_plan(const std::vector<int32_t>& prefix, const std::vector<int
       for (char c : seen) CHECK(c);
     }
   }
+  // a few slots asked of the plan itself (each question plans anew)
+  for (int q = 0; q < 4 && grid_rows + grid_keys > 0; ++q) {
+    const int mode = grid_rows == 0 ? 1 : grid_keys == 0 ? 0 : q & 1;
+    const int grid = mode == 0 ? grid_rows : grid_keys;
+    const int slot = q < 2 ? grid - 1 : (int)((int64_t)grid * 2654435761u % grid / (q + 1));
+    int32_t seq = -1, kh = -1, sp = -1, rt = -1;
+    const int valid = medha_describe_plan_slot(prefix.data(), chunk.data(), n, h_q, h_kv, d, cus,
+                                               mode, slot, &seq, &kh, &sp, &rt);
+    CHECK(valid == 0 || valid == 1);
+    CHECK(seq >= 0 && seq < n && e[seq].mode == mode && e[seq].work_start <= slot &&
+          slot < e[seq].work_start + e[seq].n_slots);
+    if (valid)
+      CHECK(kh >= 0 && kh < h_kv && sp >= 0 && sp < e[seq].n_split && rt >= 0 &&
+            rt < e[seq].n_row_tiles);
+  }
   // the sequences of a launch tile its grid (in the planner's own order)
   for (int mode = 0; mode < 2; ++mode) {
     std::sort(spans[mode].begin(), spans[mode].end());

@@ -63,12 +63,19 @@ def _simple_rule_rows(prefix, chunk, h_q, h_kv, num_cus):
     return total
 
 
+def _walks_differ(prefix, chunk, gqa, e):
+    """Whether the causal triangle makes the row tiles' walks differ by more than a sixteenth."""
+    first, last = (-(-min(prefix + chunk, prefix + -(-rows // gqa)) // 64)
+                   for rows in (min(e.rows_per_wg, chunk * gqa), chunk * gqa))
+    return e.mode == 0 and e.n_row_tiles > 1 and last - first > last // 16
+
+
 def _check_plan(prefix, chunk, h_q, h_kv, d, num_cus):
     entries, grid_rows, grid_keys, ws = medha.describe_plan(prefix, chunk, h_q, h_kv, d, num_cus)
     gqa = h_q // h_kv
     spans = {0: [], 1: []}
     part_rows = 0
-    for p, c, e in zip(prefix, chunk, entries):
+    for seq, (p, c, e) in enumerate(zip(prefix, chunk, entries)):
         n_rows = c * gqa
         assert e.mode == (1 if n_rows <= 32 else 0)
         assert e.rows_per_wg in ((32,) if e.mode else (128, 256))
@@ -82,22 +89,27 @@ def _check_plan(prefix, chunk, h_q, h_kv, d, num_cus):
         assert e.n_slots == 8 * -(-items // 8)
         spans[e.mode].append((e.work_start, e.n_slots, min(e.tiles_per_split, kv_tiles)))
         # every (kv head, split, row tile) is owned by exactly one slot
-        seen = set()
+        slots = {}
         for s in range(e.n_slots):
-            it = medha.describe_slot(s, h_kv, e.n_split, e.n_row_tiles)
+            it = medha.describe_plan_slot(prefix, chunk, h_q, h_kv, d, num_cus, e.mode,
+                                          e.work_start + s)
             if it is not None:
-                assert it not in seen
+                assert it[0] == seq
+                it = it[1:]
+                assert it not in slots
                 assert 0 <= it[0] < h_kv and 0 <= it[1] < e.n_split and 0 <= it[2] < e.n_row_tiles
-                seen.add(it)
-        assert len(seen) == items
-        # row tiles sharing (kv head, split) sit on one die (slot % 8) when they fit
-        per_die = -(-items // 8)
-        if per_die % e.n_row_tiles == 0:
-            dies = {}
-            for s in range(e.n_slots):
-                it = medha.describe_slot(s, h_kv, e.n_split, e.n_row_tiles)
-                if it is not None:
-                    dies.setdefault(it[:2], set()).add(s % 8)
+                slots[it] = s
+        assert len(slots) == items
+        # row tiles sharing (kv head, split) sit on one die (slot % 8): of a sequence with a long
+        # prefix when they fit; of one whose row tiles walk different numbers of keys the whole
+        # groups of each die
+        dies, per_die = {}, -(-items // 8)
+        for it, s in slots.items():
+            dies.setdefault(it[:2], set()).add(s % 8)
+        if _walks_differ(p, c, gqa, e):
+            alone = h_kv * e.n_split // 8 * 8
+            assert all(len(dies[g % h_kv, g // h_kv]) == 1 for g in range(alone))
+        elif per_die % e.n_row_tiles == 0:
             assert all(len(v) == 1 for v in dies.values())
         if e.n_split > 1:
             part_rows += e.n_split * c
@@ -192,3 +204,19 @@ def test_bench_refuses_more_than_one_gpu_and_finds_its_traffic_figures():
         lines = [l for l in open(os.path.join(ROOT, "profiles", name))
                  if l.startswith("hbm_bytes_per_launch")]
         assert lines and float(lines[0].split("=")[1].split()[0]) > 1e6, name
+
+
+def test_described_slots_of_a_prompt_are_the_kernels():
+    """One prompt of 5959 tokens at 32/8 heads, 94 row tiles for each KV head: a head per die, the
+    longest walks first.  A long prefix keeps equal runs of ascending row tiles."""
+    got = [medha.describe_plan_slot([0], [5959], 32, 8, 128, 256, 0, s) for s in range(24)]
+    assert got == [(0, s % 8, 0, 93 - s // 8) for s in range(24)]
+    got = [medha.describe_plan_slot([32768], [2048], 32, 8, 128, 256, 0, s) for s in range(24)]
+    assert got == [(0, s % 8, 0, s // 8) for s in range(24)]
+    # 64 sequences go out in one launch; each launch has a last sequence of its own
+    first = [medha.describe_plan_slot([0] * 66, [300] * 66, 8, 8, 128, 256, 0, 16 * i)
+             for i in (0, 62, 63, 64, 65)]
+    assert first == [(0, 0, 0, 0), (62, 0, 0, 0), (63, 0, 0, 1), (64, 0, 0, 0), (65, 0, 0, 1)]
+    for bad in (dict(mode=2, slot=0), dict(mode=0, slot=-1), dict(mode=0, slot=752), dict(mode=1, slot=0)):
+        with pytest.raises(medha.MedhaError):
+            medha.describe_plan_slot([0], [5959], 32, 8, 128, 256, bad["mode"], bad["slot"])
