@@ -35,7 +35,10 @@
  *     gets O = 0 and LSE = -inf.
  *   - Arithmetic: bf16 operands, fp32 accumulation (matrix cores), fp32 softmax
  *     statistics; probabilities are rounded to bf16 before the P*V product.
- *     For one input and one device the result is bitwise reproducible.
+ *     For one input and one device the result is bitwise reproducible, with
+ *     every workspace of at least the size that the query reports.  A call that
+ *     has less scratch and is accepted all the same may cut the keys at other
+ *     places, which moves roundings.
  *   - Return value: MEDHA_OK (0) or a negative error code.  On an error
  *     detected by argument validation nothing is enqueued and no output byte
  *     is written.
@@ -115,7 +118,9 @@ size_t medha_chunked_prefill_workspace_bytes(const int32_t* prefix_len, const in
 /*
  * medha_chunked_prefill_attn for callers that cannot allocate device memory or hand
  * over a workspace: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same arguments, results and error codes, without the workspace:
+ * forbid hipMalloc.  Same arguments and error codes, without the workspace, and the
+ * same results, bit for bit if the size that the query reports is no more than
+ * MEDHA_NOALLOC_SCRATCH_BYTES (otherwise see "bitwise reproducible" above):
  * the split-KV partials go to a scratch array of MEDHA_NOALLOC_SCRATCH_BYTES that is
  * part of the library's device image (every GPU the library runs on holds its own copy
  * until the process ends).  The call allocates nothing and calls no allocating routine;

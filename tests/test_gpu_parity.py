@@ -513,18 +513,21 @@ def test_small_chunk_long_prefix_many_way_split(h_q, h_kv, d, prefix, chunk):
 
 # ------------------------------------------------------------ plans and the workspace at hand
 def test_plan_keeps_to_the_workspace_it_is_given():
-    """47 row tiles: the query reports what the fastest plan takes, and a call with less (down to
-    6 KV ranges, the fewest-partials rule's need) takes other ranges with the same results."""
-    h_q, chunk = 8, 1500
-    b = wl.make_prefill_batch("budget", h_q, 1, 128, [21000], [chunk], seed=91)
-    need = medha.chunked_prefill_workspace_bytes(b.prefix_len, b.chunk_len, h_q, 1, 128)
+    """54 row tiles: the fastest plan has 9 KV ranges, the least a call has to bring is 5 ranges'
+    partials.  With less than the query reports the ranges are others and the results the same
+    within rounding; with more they are the same bits; below the least the call is refused."""
+    h_q, chunk = 8, 1700
+    b = wl.make_prefill_batch("budget", h_q, 1, 128, [36000], [chunk], seed=91)
+    e, _, _, need = medha.describe_plan(b.prefix_len, b.chunk_len, h_q, 1, 128, 256)
     row = chunk * h_q * 129 * 4
-    assert need >= 6 * row
+    least = -(-5 * row // 256) * 256
+    assert e[0].n_split == 9 and need == -(-9 * row // 256) * 256
     b = to_dev(b)
     rows = edge_rows(b, 5, 6, 6, 8, 8)
     ro, rl = oracle_prefill(b, rows)
     pt = torch.from_numpy(b.page_table).cuda()
-    for nbytes in sorted({6 * row + 512, 8 * row, need}):
+    outs = {}
+    for nbytes in (least, least + row, need, need + row):
         ws = torch.full((nbytes + 4096,), 0xff, dtype=torch.uint8, device="cuda")
         out, lse = medha.chunked_prefill_attn(b.q, b.k_pool, b.v_pool, pt, b.page_table_offs,
                                               b.prefix_len, b.chunk_len, b.scale,
@@ -532,6 +535,13 @@ def test_plan_keeps_to_the_workspace_it_is_given():
         torch.cuda.synchronize()
         assert bool((ws[nbytes:] == 0xff).all())
         check(out.cpu().numpy()[rows], lse.cpu().numpy()[rows], ro, rl, f"workspace of {nbytes}")
+        outs[nbytes] = out
+    assert torch.equal(outs[need], outs[need + row])
+    assert not torch.equal(outs[need], outs[least])   # other ranges round P elsewhere
+    with pytest.raises(medha.MedhaError) as err:
+        medha.chunked_prefill_attn(b.q, b.k_pool, b.v_pool, pt, b.page_table_offs, b.prefix_len,
+                                   b.chunk_len, b.scale, workspace=ws[:least - 256])
+    assert err.value.code == -3
 
 
 # ------------------------------------------------------------ prompts and first chunks

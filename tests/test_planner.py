@@ -121,6 +121,47 @@ int main() {
 }
 """
 
+BUDGET = PRELUDE + r"""
+static bool same(const Plan& a, const Plan& b) {
+  for (auto pair : {std::make_pair(&a.rows, &b.rows), std::make_pair(&a.keys, &b.keys)}) {
+    const LaunchPlan &x = *pair.first, &y = *pair.second;
+    if (x.n_slots != y.n_slots || x.q_blocks != y.q_blocks || x.seq_index != y.seq_index) return false;
+    for (size_t i = 0; i < x.descs.size(); ++i)
+      if (x.descs[i].n_split != y.descs[i].n_split || x.descs[i].part_row != y.descs[i].part_row ||
+          x.descs[i].tiles_per_split != y.descs[i].tiles_per_split) return false;
+  }
+  return a.bytes == b.bytes;
+}
+int main() {
+  const int heads[][2] = {{1, 1}, {8, 1}, {8, 2}, {32, 8}, {12, 3}};
+  int less = 0;
+  for (int it = 0; it < 4000; ++it) {
+    const auto& hh = heads[rng() % 5];
+    const int d = rng() & 1 ? 64 : 128;
+    const auto seqs = draw(1 + rng() % (it % 3 ? 3 : 24));
+    auto plan = [&](size_t budget) {
+      return make_plan(seqs.data(), (int)seqs.size(), hh[0], hh[1], d, 256, budget);
+    };
+    const Plan full = plan(SIZE_MAX);
+    const size_t need = full.workspace_bytes();
+    // any workspace of the reported size or more: one plan
+    for (size_t b : {need, need + 1, 2 * need, need + 4096})
+      if (!same(full, plan(b))) { std::printf("another plan with %zu of %zu\n", b, need); return 1; }
+    // less, down to what a call has to bring: a plan that fits
+    if (full.min_bytes < need)
+      for (size_t b : {full.min_bytes, (full.min_bytes + need) / 2, need - 1}) {
+        const Plan p = plan(b);
+        if (p.bytes > b || p.min_bytes != full.min_bytes) { std::printf("%zu of %zu\n", p.bytes, b); return 1; }
+        less += !same(full, p);
+      }
+    // less still: the simple rule's plan or one without more partials, for the call to refuse
+    if (plan(0).bytes > std::max(full.min_bytes, full.bytes)) { std::puts("grew"); return 1; }
+  }
+  std::printf("ok %d\n", less);
+  return less > 200 ? 0 : 1;
+}
+"""
+
 
 def _run(tmp_path, source):
     src, exe = str(tmp_path / "planner.hip"), str(tmp_path / "planner")
@@ -138,6 +179,13 @@ def _run(tmp_path, source):
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 def test_estimates_and_choices_are_those_of_the_plain_search(tmp_path):
     _run(tmp_path, ESTIMATE)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_one_plan_for_every_workspace_that_is_large_enough(tmp_path):
+    """The plan, and with it every bit of the result, is one and the same with all workspaces of
+    the reported size or more; with less it fits what is there."""
+    _run(tmp_path, BUDGET)
 
 
 def _plan_us(prefix, chunk, h_q, h_kv, d):

@@ -1,7 +1,8 @@
 """The entry point that allocates nothing (for callers that cannot call hipMalloc: graph
 capture, tight serving loops): its split-KV partials live in a scratch array inside the
-library's device image.  Checked against the ordinary entry point, bit for bit (the plan and the
-kernels are the same), on calls in a row that share the array, the later ones smaller."""
+library's device image.  Checked against the ordinary entry point, bit for bit where the fastest
+plan fits the array (plan and kernels are then the same), on calls in a row that share the array,
+the later ones smaller."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +10,7 @@ import torch
 import paper_2409_17264_amd as medha
 from paper_2409_17264_amd import binding
 from paper_2409_17264_amd import workloads as wl
-from tests.gpu_util import check, oracle_prefill, to_dev
+from tests.gpu_util import check, edge_rows, oracle_prefill, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -41,6 +42,22 @@ def test_noalloc_entry_point_matches_the_workspace_one_on_consecutive_calls():
         out, lse, ref_o, ref_l = _both(b)
         assert np.array_equal(out, ref_o) and np.array_equal(lse, ref_l), f"call {i}"
         check(out, lse, ro, rl, f"no-alloc entry point, call {i}")
+
+
+def test_noalloc_entry_point_takes_a_plan_that_fits_the_array():
+    """The fastest plan of this chunk takes 4 KV ranges, 95 MiB; the array holds 64 MiB and the
+    call is accepted, since the simple rule's 2 ranges take 47: other ranges, so equal to the
+    workspace entry point within rounding only."""
+    b = wl.make_prefill_batch("noalloc fit", 32, 8, 128, [20000], [1500], seed=64)
+    need = medha.chunked_prefill_workspace_bytes(b.prefix_len, b.chunk_len, 32, 8, 128)
+    assert need > binding.NOALLOC_SCRATCH_BYTES
+    b = to_dev(b)
+    rows = edge_rows(b, 5, 6, 6, 8, 8)
+    ro, rl = oracle_prefill(b, rows)
+    out, lse, ref_o, ref_l = _both(b)
+    check(out[rows], lse[rows], ro, rl, "no-alloc entry point, a smaller plan")
+    check(ref_o[rows], ref_l[rows], ro, rl, "workspace entry point")
+    assert not np.array_equal(out, ref_o)
 
 
 def test_noalloc_entry_point_refuses_what_does_not_fit():
