@@ -545,17 +545,28 @@ def test_plan_keeps_to_the_workspace_it_is_given():
 
 
 # ------------------------------------------------------------ prompts and first chunks
-@pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk", [
-    (8, 1, 128, [0], [1300]),                 # 41 row tiles dealt one by one, in KV ranges
-    (8, 2, 64, [300], [900]),                 # 15 row tiles: runs
-    (32, 8, 128, [0, 40, 0], [700, 130, 1]),  # a group per die; only the last sequence turned
-    (12, 3, 64, [64, 0], [1500, 600]),        # 3 groups of 24 and 10
-    (32, 8, 64, [0, 0, 9, 0, 0, 0], [400, 333, 290, 500, 512, 77]),  # small workgroups, in pairs
-    (16, 8, 64, [2500], [500]),               # the same in KV ranges
+@pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk,layout", [
+    # (rows per workgroup, row tiles, KV ranges) of every sequence.  A (head, range) group per die
+    # and left-over groups whose many row tiles are dealt one by one:
+    (8, 1, 128, [0], [1300], [(256, 41, 5)]),
+    # 8 groups, one for each die
+    (8, 2, 64, [300], [900], [(256, 15, 4)]),
+    # 6 groups of 8 row tiles, cut into equal runs; 3 groups a die and a 25th in runs
+    (12, 3, 128, [0], [500], [(256, 8, 2)]),
+    (10, 5, 128, [0], [1400], [(256, 11, 5)]),
+    # a group per die and range; only the last sequence turned
+    (32, 8, 128, [0, 40, 0], [700, 130, 1], [(256, 11, 2), (256, 3, 1), (32, 1, 1)]),
+    # the small workgroups of d 64: 9 groups of 47 and 3 of 19; a group per die; in KV ranges
+    (12, 3, 64, [64, 0], [1500, 600], [(128, 47, 3), (128, 19, 1)]),
+    (32, 8, 64, [0, 0, 9, 0, 0, 0], [400, 333, 290, 500, 512, 77],
+     [(128, 13, 1), (128, 11, 1), (128, 10, 1), (128, 16, 1), (128, 16, 1), (128, 3, 1)]),
+    (16, 8, 64, [2500], [500], [(128, 8, 8)]),
 ])
-def test_prompts_whose_walks_differ(h_q, h_kv, d, prefix, chunk):
+def test_prompts_whose_walks_differ(h_q, h_kv, d, prefix, chunk, layout):
     """No or little prefix: row tiles walk different numbers of keys, and the slots are dealt out
     so that every die gets the same mix."""
+    entries = medha.describe_plan(prefix, chunk, h_q, h_kv, d, 256)[0]
+    assert [(e.rows_per_wg, e.n_row_tiles, e.n_split) for e in entries] == layout
     b = wl.make_prefill_batch("uneven", h_q, h_kv, d, prefix, chunk, seed=sum(chunk),
                               poison_unused=True)
     ro, rl = oracle_prefill(b)

@@ -177,7 +177,8 @@ def test_described_workspace_is_what_a_call_has_to_bring(prefix, chunk, h_q, h_k
     ([65000] * 4, [600] * 4, 8, 1, 128),      # 4 x 19
     ([20011], [777], 32, 8, 64),              # 8 x 13
     ([50000], [4864], 8, 1, 128),             # 152: more than half the device, unsplit
-    ([9000], [33], 8, 1, 128),                # the small workgroups
+    ([9000], [33], 8, 1, 128),                # two row tiles, ranges of the shortest kind
+    ([9000], [31], 8, 1, 128),                # the same of small workgroups
 ])
 def test_row_split_launches_fill_whole_rounds_of_the_device(prefix, chunk, h_q, h_kv, d):
     """Time of the planned launch in tiles, workgroups of one length each: no more than 1.15 times
