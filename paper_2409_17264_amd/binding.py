@@ -134,9 +134,15 @@ def _dp(t: torch.Tensor) -> int:
     return t.data_ptr()
 
 
+# torch.cuda.current_stream() without the Stream object it wraps the handle in (0.3 us against
+# 2.8 us).  The function is private to torch: a version without it takes the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # torch.cuda.current_stream() without the Stream object it wraps the handle in
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _kv(k_pool: torch.Tensor, v_pool: torch.Tensor) -> _KvCache:

@@ -647,6 +647,15 @@ def test_random_batches(seed):
     check(out, lse, ro, rl, f"random batch seed {seed}: hq{h_q} hkv{h_kv} d{d} n{n}")
 
 
+# ------------------------------------------------------------ the stream a call goes to
+def test_calls_go_to_the_current_stream():
+    from paper_2409_17264_amd import binding
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.default_stream(), side):
+        with torch.cuda.stream(stream):
+            assert binding._stream() == stream.cuda_stream == torch.cuda.current_stream().cuda_stream
+
+
 # ------------------------------------------------------------ pages that sequences share
 def _share_prefix(b, shared):
     """Sequence i takes its first shared[i] pages from sequence 0's table."""

@@ -190,6 +190,19 @@ def test_row_split_launches_fill_whole_rounds_of_the_device(prefix, chunk, h_q, 
     assert rounds * max(x.tiles_per_split for x in e) <= 1.15 * tiles / slots + 12 * rounds
 
 
+def test_stream_handle_without_the_private_function(monkeypatch):
+    import importlib.util
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    spec = importlib.util.spec_from_file_location("binding_again", binding.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream() == 1234
+
+
 def test_bench_refuses_more_than_one_gpu_and_finds_its_traffic_figures():
     import subprocess
     import sys
