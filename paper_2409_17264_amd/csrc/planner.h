@@ -63,25 +63,34 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // What a workgroup of a row-split launch costs, in microseconds (MI355X): one KV tile of its
 // walk, and everything outside the walk (descriptor, Q, the ring's first fill, the epilogue).
 // Only the ratios matter: they weigh more, shorter KV ranges against fewer, longer ones.
+// Launches of one, two and four rounds of equal walks (512 to 8192 keys) take 1.70 us a tile and
+// 10.3 to 11.5 us outside the walk at head dim 128, 1.05 us and 5.0 to 6.5 us at 64, with 256-row
+// workgroups.  At 64 the constants ask 12 tiles for a workgroup's start and end, not 6: plans
+// lean towards fewer ranges there.
 struct WalkCost {
   double tile_us, fixed_us;
   int wgs_per_cu;  // workgroups a compute unit holds at a time
 };
 
-// (measured; the small workgroups of head dim 64 share a compute unit in pairs, where one's
-// start and end hide behind the other's walk, at the price of a second copy of the K/V loads)
+// (the small workgroups of head dim 64 share a compute unit in pairs, where one's start and end
+// hide behind the other's walk, at the price of a second copy of the K/V loads)
 inline WalkCost walk_cost(int head_dim, int q_blocks) {
   if (head_dim == 128) return q_blocks == 2 ? WalkCost{1.64, 10.0, 1} : WalkCost{1.2, 10.0, 1};
   return q_blocks == 2 ? WalkCost{0.9, 11.0, 1} : WalkCost{0.91, 9.0, 2};
 }
 
-// The merge of a launch's partials: a launch, then bytes at the rate the merge kernel reads
-// them (31 MB in 8 us).  Writing them hides behind the walks of other workgroups.
+// What partials cost: a launch, then their bytes.  The merge kernel takes 8 us for 31 MB and 17
+// to 18 us for 99 MB; the constants ask 10 and 25, since partials are written and held as well.
 constexpr double kMergeLaunchUs = 3.0, kMergeBytesPerUs = 4.5e6;
 // Partials beyond this are not worth their memory (a split that needs more is not considered).
 constexpr int64_t kMaxPartialBytes = (int64_t)128 << 20;
-constexpr int kMaxPlannedSeqs = 16;  // launches of more sequences keep the simple rule
-constexpr int kMaxWaves = 8;         // rounds of workgroups per compute unit worth considering
+// Launches of more sequences keep the simple rule: the estimate has been held against measured
+// launches up to here only.  Where the rule leaves a round nearly empty that costs 5 to 15 % (17
+// chunks of 200 at 20K, 8/1 heads, 338 us, 318 with the estimate's plan; 24 of them 492 and 444;
+// 17 chunks of 600 at 65K 2.99 and 2.53 ms); 64 chunks of 200 and 17 to 64 prompts at head dim
+// 128 take the same either way.
+constexpr int kMaxPlannedSeqs = 16;
+constexpr int kMaxWaves = 8;  // rounds of workgroups per compute unit worth considering
 
 // Workgroups that walk the same number of tiles, on the fullest accelerator die.
 struct WalkGroup {
@@ -485,9 +494,10 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
                                 walk_cost(head_dim, plan.rows.q_blocks), rows_steps, kMinTiles,
                                 row_bytes, fit - keys_rows, us);
       // At head dim 64 the small workgroups are the alternative: half the granule, short walks
-      // overlapped (777 tokens at 20K, 32/8 heads: 164 -> 155 us; 14 prompts, 24 tiles
-      // on average: 174 -> 163 us; 12 prompts, 14 tiles: 226 -> 215 us; but 1 % longer at 96 and
-      // 288 tiles where both fill the device).  At 128 two of their rings do not fit a unit.
+      // overlapped (14 prompts of 1K median at 8/2 heads 162 -> 150 us a pass, 12 of 700 at 32/8
+      // heads 126.0 -> 121.5; 777 tokens at 900, 32/8 heads, 31.5 -> 29.4; at 20K, 8/2 heads,
+      // 53.9 -> 51.6, 32/8 heads 160.8 -> 158.7; the same at 1500 tokens at 50K; 1 % longer at 96
+      // and 288 tiles where both fill the device).  At 128 two of their rings do not fit a unit.
       if (head_dim == 64 && plan.rows.q_blocks == 2) {
         LaunchPlan small = plan.rows;
         small.q_blocks = 1;
