@@ -58,8 +58,9 @@ __device__ __forceinline__ void async_load16(const void* base_uniform, uint32_t 
 // else reads soon: the stream is not allocated in the caches on its way, which is worth a tenth
 // of the rate.  (Key-split kernel: 1M keys in 4 shards, 8 KV heads, 706 -> 643 us with both
 // merges, 6.1 -> 6.7 TB/s; 64 decodes of 2K median 136 -> 120 us, 128 of 8K 812 -> 726 us; a
-// single decode of 2K from a cold cache 16.3 -> 15.1 us a pass; wider scopes, sc0 and sc1, with
-// the hint change nothing.)
+// single decode of 2K 16.3 -> 15.1 us a pass, 4 of them 18.0 -> 16.4, if the caches hold other
+// data by then, as behind a model's other layers; 13.5 -> 15.2 if the 33 MB of the 4 are still
+// there from the call before.  Wider scopes, sc0 and sc1, with the hint change nothing.)
 template <bool kOnce>
 __device__ __forceinline__ void async_stream16(const void* gptr, uint32_t lds_addr_uniform) {
   if constexpr (kOnce)
