@@ -201,7 +201,9 @@ struct RowBlock {
   // pointers it passes; with it the pointers' constant parts fit the LDS instructions'
   // 16-bit immediate offset and cost no address arithmetic).
   __device__ __forceinline__ void init(float scale, int lane, int v_bias = 0) {
-    scale_log2 = scale;
+    // 0 becomes the smallest positive number: a finite score still scales to 0 (within 2^-21), a
+    // masked one (-inf) to -inf, not to a NaN, and no probability needs a select for it
+    scale_log2 = fmaxf(scale, __FLT_DENORM_MIN__);
     m = -INFINITY;
     l = 0.f;
 #pragma unroll
@@ -288,7 +290,7 @@ struct RowBlock {
   // no key).
   template <bool MASK>
   __device__ __forceinline__ float update_reference(float mx_raw) {
-    const float mx = max_halves(mx_raw) * scale_log2;  // scale_log2 >= 0
+    const float mx = max_halves(mx_raw) * scale_log2;  // scale_log2 > 0
     if (__any(mx > m)) {
       const float m_new = fmaxf(m, mx);
       // a row that has seen no key yet keeps m = -inf: nothing to rescale
@@ -303,12 +305,9 @@ struct RowBlock {
     return (MASK && m == -INFINITY) ? 0.f : m;
   }
 
-  // One probability: exp2(s*scale_log2 - m_use), 0 for a masked score (the select is
-  // also right when scale_log2 == 0, where -inf * 0 is not a number).
-  template <bool MASK>
+  // One probability: exp2(s*scale_log2 - m_use), 0 for a masked score (-inf; scale_log2 > 0).
   __device__ __forceinline__ float prob(float sv, float m_use) const {
-    const float p = fast_exp2(__builtin_fmaf(sv, scale_log2, -m_use));
-    return (MASK && sv == -INFINITY) ? 0.f : p;
+    return fast_exp2(__builtin_fmaf(sv, scale_log2, -m_use));
   }
 
   // vop holds the V^T operands of slices 0 and 1, already requested by the caller.
@@ -338,7 +337,7 @@ struct RowBlock {
       f32x8 pe;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        pe[e] = prob<MASK>(s[g >> 1][8 * (g & 1) + e], m_use);
+        pe[e] = prob(s[g >> 1][8 * (g & 1) + e], m_use);
         ls += pe[e];
       }
       return __builtin_convertvector(pe, bf16x8);
@@ -401,6 +400,16 @@ struct RowBlock {
   // Diagonal tiles (MASK true) always take the exact route.
   static constexpr float kSpecShare = 1.f / 16.f;
 
+  // The vector arithmetic runs kLead slots ahead of the matrix instructions: behind the tile's
+  // barrier both wavefronts of a SIMD wait for their first K operands, and the first three slots'
+  // exponentials fill that wait instead of coming after it.  The loads of the tile three ahead are
+  // issued in slot kLoadSlot, their twenty scalar instructions between two MFMAs and not between
+  // the barrier and the first one.  (Both together, against none and slot 0: head dim 64, 777
+  // tokens at 20K, 32/8 heads, 163.3 -> 158.1 us; 5000 tokens, 8/1 heads, 99.8 -> 98.2; 32 tokens
+  // at 1M 160.9 -> 159.2; the long walks at head dim 128 -0.4 %, where fewer idle cycles cost
+  // clock.  A lead of 2 or 4 and the loads in slot 2, 3, 6 or 8 are 0.1 to 0.6 % longer.)
+  static constexpr int kLead = 3, kLoadSlot = 4;
+
   __device__ __forceinline__ void add_to_sum(float ls) { l = __builtin_fmaf(ls, kSpecShare, l); }
   // The row's sum of probabilities relative to the reference point (both lanes of the row).
   __device__ __forceinline__ float row_sum() const { return sum_halves(l) * (1.f / kSpecShare); }
@@ -418,7 +427,7 @@ struct RowBlock {
       f32x8 pe;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        pe[e] = prob<false>(sc[KB][8 * h + e], m_use);
+        pe[e] = prob(sc[KB][8 * h + e], m_use);
         ls += pe[e];
       }
       const uint4 w = __builtin_bit_cast(uint4, __builtin_convertvector(pe, bf16x8));
@@ -432,9 +441,10 @@ struct RowBlock {
   // their K reads and S^T MFMAs; k_next and sn are not touched.  SPEC false takes the
   // exact route (row maximum first) also on an unmasked tile: for the first tiles of a
   // walk, whose speculation would fail anyway, it is the cheaper of the two.
-  template <bool MASK, bool QK = true, bool SPEC = true>
+  template <bool MASK, bool QK = true, bool SPEC = true, class Loads>
   __device__ __forceinline__ void fused(const char* k_next, const char* v_cur, f32x16 (&sc)[2],
-                                        f32x16 (&sn)[2], int key0, int half) {
+                                        f32x16 (&sn)[2], int key0, int half,
+                                        Loads issue_loads) {
     constexpr bool kSpec = SPEC && !MASK;
     constexpr int kQk = 2 * kSlices;       // MFMAs of the next tile's S^T
     constexpr int kPv = 4 * kDBlocks;      // MFMAs of the current tile's O^T
@@ -443,8 +453,11 @@ struct RowBlock {
     constexpr int kSpan = 3 * kSlots / 16; // slots over which a slice's exponentials spread
     // slice g: exponentials in slots [kMaxSlots + g*kSpan, +kSpan), MFMAs from kQk + g*kDBlocks
     static_assert(kMaxSlots + 4 * kSpan <= kQk + 3 * kDBlocks, "P^T ready before its MFMAs");
-    // the speculation checks close slots 2*kSpan-1 and 4*kSpan-1
-    static_assert(2 * kSpan <= kQk && 4 * kSpan <= kQk + 2 * kDBlocks, "checked before consumed");
+    // The speculation checks close slots kCheck0 and kCheck1: behind the slices they cover, before
+    // any MFMA takes those -- and behind the MFMAs of the slices before, whose probabilities a
+    // failed check does not touch when it moves the reference point and rescales O.
+    static_assert(2 * kSpan <= kQk && 4 * kSpan == kQk + 2 * kDBlocks, "checked before consumed");
+    constexpr int kCheck0 = 2 * kSpan - 1 - kLead, kCheck1 = 4 * kSpan - 1;
     bf16x8 ka[4], va[4];
     uint32_t pw[4][4];  // P^T operands of the 4 slices as packed bf16 pairs
     float mx = -INFINITY, m_use = m, ls = 0.f;
@@ -475,6 +488,39 @@ struct RowBlock {
     }
     __builtin_amdgcn_sched_barrier(0);
 
+    // slot i's share of the softmax of the current tile (taken in slot i - kLead)
+    auto share = [&](auto slot_index) {
+      constexpr int i = decltype(slot_index)::value;
+      if constexpr (!kSpec && i < kMaxSlots) {
+        constexpr int per = 32 / (kSpec ? 1 : kMaxSlots);
+#pragma unroll
+        for (int f = i * per; f < (i + 1) * per; ++f) {
+          if (MASK) {
+            const int t = key0 + (f >> 4) * 32 + 8 * ((f & 15) >> 2) + 4 * half + (f & 3);
+            sc[f >> 4][f & 15] = (t <= limit) ? sc[f >> 4][f & 15] : -INFINITY;
+          }
+          mx = fmaxf(mx, sc[f >> 4][f & 15]);
+        }
+      }
+      if constexpr (!kSpec && i == kMaxSlots) m_use = update_reference<MASK>(mx);
+      if constexpr (i >= kMaxSlots && i < kMaxSlots + 4 * kSpan) {
+        constexpr int g = (i - kMaxSlots) / kSpan, r = (i - kMaxSlots) % kSpan;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if ((e * kSpan) / 8 == r) {
+            const float pe = prob(sc[g >> 1][8 * (g & 1) + e], m_use);
+            // (the first term after a check starts the sum: no addition to zero)
+            if (kSpec && (g & 1) == 0 && e == 0) ls = pe; else ls += pe;
+            if (e & 1) {
+              const f32x2 pair = {pe_prev, pe};
+              pw[g][e >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
+            } else {
+              pe_prev = pe;
+            }
+          }
+      }
+      asm volatile("" : "+v"(ls));  // keeps the additions in their slots
+    };
     auto slot = [&](auto slot_index) {
       constexpr int i = decltype(slot_index)::value;
       // The wavefront's issue priority falls as it advances through the tile (3, 2, 1, 0 by
@@ -494,40 +540,12 @@ struct RowBlock {
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i & 3], __builtin_bit_cast(bf16x8, w),
                                                         o[db], 0, 0, 0);
       }
-      // this slot's share of the softmax of the current tile
-      if constexpr (!kSpec && i < kMaxSlots) {
-        constexpr int per = 32 / (kSpec ? 1 : kMaxSlots);
-#pragma unroll
-        for (int f = i * per; f < (i + 1) * per; ++f) {
-          if (MASK) {
-            const int t = key0 + (f >> 4) * 32 + 8 * ((f & 15) >> 2) + 4 * half + (f & 3);
-            sc[f >> 4][f & 15] = (t <= limit) ? sc[f >> 4][f & 15] : -INFINITY;
-          }
-          mx = fmaxf(mx, sc[f >> 4][f & 15]);
-        }
-      }
-      if constexpr (!kSpec && i == kMaxSlots) m_use = update_reference<MASK>(mx);
-      if constexpr (i >= kMaxSlots && i < kMaxSlots + 4 * kSpan) {
-        constexpr int g = (i - kMaxSlots) / kSpan, r = (i - kMaxSlots) % kSpan;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if ((e * kSpan) / 8 == r) {
-            const float pe = prob<MASK>(sc[g >> 1][8 * (g & 1) + e], m_use);
-            // (the first term after a check starts the sum: no addition to zero)
-            if (kSpec && (g & 1) == 0 && e == 0) ls = pe; else ls += pe;
-            if (e & 1) {
-              const f32x2 pair = {pe_prev, pe};
-              pw[g][e >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
-            } else {
-              pe_prev = pe;
-            }
-          }
-      }
-      asm volatile("" : "+v"(ls));  // keeps the additions in their slots
-      if constexpr (kSpec && (i == 2 * kSpan - 1 || i == 4 * kSpan - 1)) {
+      if constexpr (i == kLoadSlot) issue_loads();
+      if constexpr (i + kLead < kSlots) share(std::integral_constant<int, i + kLead>{});
+      if constexpr (kSpec && (i == kCheck0 || i == kCheck1)) {
         // ls covers the two slices just finished
         if (__builtin_expect(__any(!(ls <= l)), 0)) {
-          respeculate<(i == 2 * kSpan - 1) ? 0 : 1>(sc, pw, ls);
+          respeculate<(i == kCheck0) ? 0 : 1>(sc, pw, ls);
           m_use = m;
           add_to_sum(ls);
           l = 0.5f * sum_halves(l);
@@ -540,6 +558,8 @@ struct RowBlock {
       }
       __builtin_amdgcn_sched_barrier(0);
     };
+    static_for<kLead>(share);
+    __builtin_amdgcn_sched_barrier(0);
     static_for<kSlots>(slot);
     if (!kSpec) add_to_sum(ls);  // (the speculative route adds at its checks)
   }
@@ -591,6 +611,14 @@ struct Ring {
   uint32_t lds_addr;  // the same place as an LDS byte address, for the tile loads
 };
 
+// Says that the registers' contents are of no use (and costs no instruction): without it the
+// compiler keeps old values through code that overwrites them on some of its paths only.
+template <class T, int N>
+__device__ __forceinline__ void forget(T (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "=v"(x[i]));
+}
+
 // Walks tiles [kt_a, kt_b) through the 4-stage ring; every row of the workgroup sees the
 // tiles below kt_mid in full.  Self-contained: starts with no load in flight and ends with
 // none.
@@ -630,6 +658,8 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
   // page id of the next tile to issue
   int page_next = tile_page<D, NW>(pt, min(kt_a + 3, last), kv_total, wave);
   f32x16 s0[2], s1[2];  // scores of the even / odd tiles (counted from kt_a)
+  forget(s0);
+  forget(s1);
   ring_barrier<2 * G::kLoadsPerWaveTile>();  // tile kt_a has landed, for everyone
   rb.template qk<2>(ring.base, s0);
   if (kt_u > kt_a) {
@@ -648,17 +678,19 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
         // this wavefront's loads of tile cur+1 have landed (tile cur+2 may fly); after the
         // barrier everyone's have, and everyone is done with the stage refilled next
         ring_barrier<G::kLoadsPerWaveTile>();
-        asm volatile("" : "+s"(page_next));  // the page id is first needed here, not before
-        const uint32_t nxt = ring.lds_addr + ((s + 3) % NS) * kTile;
-        ld.issue(args, page_next, min(cur + 3, last), kv_total, kv_head, nxt, nxt + NS * kTile);
+        auto issue_loads = [&] {
+          asm volatile("" : "+s"(page_next));  // the page id is first needed here, not before
+          const uint32_t nxt = ring.lds_addr + ((s + 3) % NS) * kTile;
+          ld.issue(args, page_next, min(cur + 3, last), kv_total, kv_head, nxt, nxt + NS * kTile);
+        };
         const char* k_next = ring.base + ((s + 1) % NS) * kTile;
         const char* v_cur = ring.base + s * kTile;  // + the bias in rb.v_off
         if (s & 1)
           rb.template fused<kMask, true, kSpeculate>(k_next, v_cur, s1, s0, cur * G::kTileKeys,
-                                                     half);
+                                                     half, issue_loads);
         else
           rb.template fused<kMask, true, kSpeculate>(k_next, v_cur, s0, s1, cur * G::kTileKeys,
-                                                     half);
+                                                     half, issue_loads);
         // The scalar load of the next page id goes HERE, after the tile's last LDS read has
         // been consumed and before the barrier: scalar loads and LDS reads share one
         // counter and scalar loads return out of order, so with one in flight every wait for
@@ -679,16 +711,19 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
   // walk takes it up front.
   for (; kt < end_u && kt < kt_a + kWarmTiles; kt += NS)
     group(kt, std::false_type{}, std::false_type{});
-  for (; kt < end_u; kt += NS) group(kt, std::false_type{}, std::true_type{});
+  // (the weight is for the register allocator: what has to be spilled is spilled elsewhere)
+  for (; __builtin_expect_with_probability(kt < end_u, 1, 0.995); kt += NS)
+    group(kt, std::false_type{}, std::true_type{});
   for (; kt < last; kt += NS) group(kt, std::true_type{}, std::false_type{});
-  // the last tile: its scores are in registers, its V tile landed with its K tile
+  // the last tile: its scores are in registers, its V tile landed with its K tile (the exact route:
+  // at a short walk's end speculation fails, and one tile of a long one costs nothing)
   auto final_tile = [&](auto mask) {
     constexpr bool kMask = decltype(mask)::value;
     const char* v_last = ring.base + ((last - kt_a) % NS) * kTile;  // + the bias in rb.v_off
     if ((last - kt_a) & 1)
-      rb.template fused<kMask, false>(nullptr, v_last, s1, s0, last * G::kTileKeys, half);
+      rb.template fused<kMask, false, false>(nullptr, v_last, s1, s0, last * G::kTileKeys, half, [] {});
     else
-      rb.template fused<kMask, false>(nullptr, v_last, s0, s1, last * G::kTileKeys, half);
+      rb.template fused<kMask, false, false>(nullptr, v_last, s0, s1, last * G::kTileKeys, half, [] {});
   };
   if (kt_u == kt_b)
     final_tile(std::false_type{});
