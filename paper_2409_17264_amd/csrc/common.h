@@ -21,7 +21,6 @@ constexpr int kPageSize = 16;     // tokens per KV page
 constexpr int kThreads = 256;     // threads per workgroup (4 wavefronts of 64)
 constexpr int kWaves = 4;
 constexpr int kXcds = 8;          // accelerator dies; workgroup i is dispatched to die i % 8
-constexpr int kPrefillStages = 4;  // K/V tiles in flight per workgroup (LDS ring)
 constexpr int kMaxInlineSeq = 64; // sequence descriptors per kernel launch (they travel as kernel arguments)
 constexpr int kShortWalkTiles = 24;   // key-split launches walking at most this many 128-key tiles per workgroup use the small ring
 constexpr int kWideMergeSplits = 16;  // more KV ranges per row than this: the wide merge kernel

@@ -75,10 +75,9 @@ hipError_t launch_decode(const AttnArgs& a, int grid, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int D, int NW>
+template <int D, int NW, int NV = 4>
 hipError_t launch_prefill(const AttnArgs& a, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL((prefill_kernel<D, NW, kPrefillStages>), dim3(grid), dim3(NW * 64), 0,
-                     stream, a);
+  hipLaunchKernelGGL((prefill_kernel<D, NW, NV>), dim3(grid), dim3(NW * 64), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -120,6 +119,8 @@ hipError_t launch_plan(const LaunchPlan& lp, bool split_keys, int d, AttnArgs& a
     } else if (lp.q_blocks == 2) {
       e = d == 128 ? launch_prefill<128, 8>(a, grid, stream)
                    : launch_prefill<64, 8>(a, grid, stream);
+    } else if (lp.paired) {
+      e = launch_prefill<128, 4, 2>(a, grid, stream);
     } else {
       e = d == 128 ? launch_prefill<128, 4>(a, grid, stream)
                    : launch_prefill<64, 4>(a, grid, stream);

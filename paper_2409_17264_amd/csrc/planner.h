@@ -21,6 +21,7 @@ struct LaunchPlan {
   std::vector<int32_t> seq_index;  // position of each descriptor in the caller's batch
   ModeShape shape{0, 0};
   int q_blocks = 1;   // 32-row blocks per wavefront (row-split mode)
+  bool paired = false;  // two workgroups to a compute unit, with the short ring (head dim 128)
   int n_slots = 0;    // grid size
   int total_rows = 0; // token rows of the launch
   bool any_split = false;
@@ -78,6 +79,10 @@ inline WalkCost walk_cost(int head_dim, int q_blocks) {
   if (head_dim == 128) return q_blocks == 2 ? WalkCost{1.64, 10.0, 1} : WalkCost{1.2, 10.0, 1};
   return q_blocks == 2 ? WalkCost{0.9, 11.0, 1} : WalkCost{0.91, 9.0, 2};
 }
+
+// Small workgroups (128 rows) where that is not their only form: alone on a compute unit (head dims 64
+// and 128), and in pairs with the short ring (head dim 128).
+constexpr WalkCost kAloneCost[2] = {{0.65, 9.0, 1}, {1.25, 8.0, 1}}, kPairedCost{1.85, 8.0, 2};
 
 // What partials cost: a launch, then their bytes.  The merge kernel takes 8 us for 31 MB and 17
 // to 18 us for 99 MB; the constants ask 10 and 25, since partials are written and held as well.
@@ -493,28 +498,55 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
       rows_steps = choose_steps(plan.rows, launch_walks(plan.rows, h_kv, gqa), h_kv, num_cus,
                                 walk_cost(head_dim, plan.rows.q_blocks), rows_steps, kMinTiles,
                                 row_bytes, fit - keys_rows, us);
-      // At head dim 64 the small workgroups are the alternative: half the granule, short walks
-      // overlapped (14 prompts of 1K median at 8/2 heads 162 -> 150 us a pass, 12 of 700 at 32/8
-      // heads 126.0 -> 121.5; 777 tokens at 900, 32/8 heads, 31.5 -> 29.4; at 20K, 8/2 heads,
-      // 53.9 -> 51.6, 32/8 heads 160.8 -> 158.7; the same at 1500 tokens at 50K; 1 % longer at 96
-      // and 288 tiles where both fill the device).  At 128 two of their rings do not fit a unit.
-      if (head_dim == 64 && plan.rows.q_blocks == 2) {
+      // The small workgroups as an alternative, `least` to `most` of them, where the estimate falls
+      // below `worth` of the plan so far.
+      auto try_small = [&](const WalkCost& cost, bool paired, double worth, int64_t least,
+                           int64_t most) {
         LaunchPlan small = plan.rows;
         small.q_blocks = 1;
+        small.paired = paired;
         small.shape.rows_per_wg = kWaves * 32;
         set_row_tiles(small, gqa);
         const LaunchWalks walks = launch_walks(small, h_kv, gqa);
-        const WalkCost cost = walk_cost(head_dim, 1);
-        if (even_us(walks, walks.longest, num_cus, cost) < 0.97 * us) {
-          const int64_t steps = choose_steps(small, walks, h_kv, num_cus, cost, INT32_MAX,
-                                             kMinTiles, row_bytes, fit - keys_rows, small_us);
-          if (small_us < 0.97 * us && split_size(small, h_kv, steps, kMinTiles).slots >
-                                          num_cus) {  // else nothing pairs up
-            plan.rows = std::move(small);
-            rows_steps = steps;
-          }
+        if (even_us(walks, walks.longest, num_cus, cost) >= worth * us) return;
+        const int64_t steps = choose_steps(small, walks, h_kv, num_cus, cost, INT32_MAX, kMinTiles,
+                                           row_bytes, fit - keys_rows, small_us);
+        const int64_t slots = split_size(small, h_kv, steps, kMinTiles).slots;
+        if (small_us < worth * us && slots >= least && slots <= most) {
+          plan.rows = std::move(small);
+          rows_steps = steps;
+          us = small_us;
         }
+      };
+      const bool big = plan.rows.q_blocks == 2;
+      bool behind = true;  // every chunk has a prefix as long as itself
+      bool shared = true;  // every K/V stream has two small row tiles to read it
+      for (const SeqDesc& sd : plan.rows.descs) {
+        behind &= sd.prefix_len >= sd.chunk_len;
+        shared &= (int64_t)sd.chunk_len * gqa > kWaves * 32;
       }
+      // At head dim 64 they share a compute unit in pairs (else nothing is gained): half the granule,
+      // short walks overlapped (14 prompts of 1K median at 8/2 heads 162 -> 150 us a pass, 12 of
+      // 700 at 32/8 heads 126.0 -> 121.5; 777 tokens at 900, 32/8 heads, 31.5 -> 29.4; at 20K, 8/2
+      // heads, 53.9 -> 51.6, 32/8 heads 160.8 -> 158.7; the same at 1500 tokens at 50K; 1 % longer
+      // at 96 and 288 tiles where both fill the device).
+      if (head_dim == 64 && big) try_small(walk_cost(64, 1), false, 0.97, num_cus + 1, INT64_MAX);
+      // A launch that leaves compute units idle spreads over twice as many of them: a small
+      // workgroup has its SIMDs to itself, one wavefront each, and takes three quarters of the
+      // time a tile (64 tokens at 2000, 8/1 heads, d 128, 18.3 -> 15.2 us; 300 at 1000, 32/8, 29.4
+      // -> 25.9; 200 at 8000, 8/1, 29.6 -> 26.5; d 64: 100 at 2000, 32/8, 15.8 -> 14.4; 64 at 3000,
+      // 8/2, 14.5 -> 12.9; with one KV head, where a handful of workgroups is all there is either
+      // way, 256 at 1024, 2/1, 13.4 -> 13.1: left as it is).  Prompts and chunks longer than their prefix keep the large
+      // ones: alone they gain as well (1300 tokens at 8/1 27.4 -> 25.4), eight together lose 3 %.
+      if (behind && big && (head_dim == 128 || h_kv > 1))
+        try_small(kAloneCost[head_dim == 128], false, head_dim == 128 ? 0.97 : 0.90, 1, num_cus);
+      // In pairs at head dim 128 (see run_tiles): 900 tokens at 2000, 8/2 heads, 35.6 -> 31.0 us.
+      // Where 129 to 255 rows have no large form, two row tiles that share a K/V stream beat one
+      // after the other by 3 to 14 % at estimates of 0.78 to 0.87 (31 tokens at 1M, 8/1 heads, 179
+      // -> 162 us; 60 at 500K, 32/8, 644 -> 556) and lose 3 % at 0.91 (20 at 100K, 8/1 heads); a
+      // stream of one row tile alone wants the long ring (16 tokens at 1M 114 us, 127 in pairs).
+      if (head_dim == 128 && behind && shared)
+        try_small(kPairedCost, true, big ? 0.98 : 0.90, num_cus + 1, INT64_MAX);
     }
   }
   if (!plan.rows.descs.empty())

@@ -13,9 +13,9 @@
 // pipe and the vector ALU share an issue port and neither should wait for the other.
 //
 // K/V tiles go HBM -> LDS directly (no registers) with asynchronous 16-byte
-// global loads into a ring of NS stages (K tiles in its low half, V tiles in its
-// high half), gathered page by page through the page table.  Each page row is 16*D*2 contiguous bytes, so every 1 KiB load
-// instruction reads whole rows.  Rows are stored unpadded; bank conflicts are
+// global loads into a ring of stages (K tiles in its low part, V tiles in its
+// high part), gathered page by page through the page table.  Each page row is
+// 16*D*2 contiguous bytes, so every 1 KiB load instruction reads whole rows.  Rows are stored unpadded; bank conflicts are
 // avoided by XOR-swizzling the 16-byte column index with the row index (one
 // pattern for the 16-byte K reads, another for the 8-byte transposing V reads).
 #pragma once
@@ -143,7 +143,9 @@ struct TileLoader {
     }
   }
 
-  // page = id of the page holding rows row0.. of tile `tile` (see tile_page()).
+  // Loads K and / or V rows row0.. of tile `tile`; page = id of the page holding them (see
+  // tile_page()), k_stage / v_stage = LDS addresses of the tile's places in the ring.
+  template <bool K, bool V>
   __device__ __forceinline__ void issue(const AttnArgs& args, int page, int tile, int kv_total,
                                         int kv_head, uint32_t k_stage, uint32_t v_stage) const {
     const int64_t page_off = ((int64_t)page * args.h_kv + kv_head) * (kPageSize * D * 2);
@@ -153,8 +155,8 @@ struct TileLoader {
 #pragma unroll
       for (int j = 0; j < G::kInstrPerWave; ++j) {
         const uint32_t lds_off = (row0 + j * G::kRowsPerInstr) * (D * 2);  // wave-uniform
-        async_load16(kp, k_off[j], k_stage + lds_off);
-        async_load16(vp, v_off[j], v_stage + lds_off);
+        if (K) async_load16(kp, k_off[j], k_stage + lds_off);
+        if (V) async_load16(vp, v_off[j], v_stage + lds_off);
       }
     } else {
       // last, ragged tile: keys past the end are clamped to the last one (masked, but finite)
@@ -163,10 +165,12 @@ struct TileLoader {
         const int row = row0 + j * G::kRowsPerInstr + r_in;
         const int t = min(tile * G::kTileKeys + row, kv_total - 1);
         const uint32_t lds_off = (row0 + j * G::kRowsPerInstr) * (D * 2);
-        async_load16(kp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::k(row, pos) * 16),
-                     k_stage + lds_off);
-        async_load16(vp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::v(row, pos) * 16),
-                     v_stage + lds_off);
+        if (K)
+          async_load16(kp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::k(row, pos) * 16),
+                       k_stage + lds_off);
+        if (V)
+          async_load16(vp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::v(row, pos) * 16),
+                       v_stage + lds_off);
       }
     }
   }
@@ -592,11 +596,21 @@ __device__ __forceinline__ int find_seq_slot(const SeqDesc* descs, int n_seq, in
   return find_last(n_seq, slot, [&](int i) { return descs[i].work_start; });
 }
 
-template <int D, int NW, int NS>
+// A ring with room for 4 K and 4 V tiles, or for 3 and 2.
+template <int NV>
+struct RingShape {
+  static_assert(NV == 4 || NV == 2, "ring");
+  static constexpr int kV = NV;
+  static constexpr int kK = NV == 4 ? 4 : 3;
+  static constexpr int kLag = 4 - NV;             // tiles the V loads stay behind the K loads
+  static constexpr int kRound = NV == 4 ? 4 : 6;  // tiles after which stages and score sets repeat
+};
+
+template <int D, int NW, int NV>
 struct PrefillShape {
   static constexpr int kRowsPerWg = NW * 32;
-  static constexpr int kStageBytes = 2 * TileGeom<D, NW>::kTileBytes;  // K tile then V tile
-  static constexpr int kLdsBytes = NS * kStageBytes;
+  static constexpr int kVBias = RingShape<NV>::kK * TileGeom<D, NW>::kTileBytes;  // V tiles' offset
+  static constexpr int kLdsBytes = kVBias + NV * TileGeom<D, NW>::kTileBytes;
 };
 
 // Tiles at the head of an unmasked walk that take the exact route without speculating
@@ -605,7 +619,7 @@ struct PrefillShape {
 // walks take 4 % longer.
 constexpr int kWarmTiles = 24;
 
-// The ring: NS stages of (K tile, V tile), contiguous from `base`.
+// The ring: K tiles, then V tiles, contiguous from `base`.
 struct Ring {
   char* base;         // for operand reads
   uint32_t lds_addr;  // the same place as an LDS byte address, for the tile loads
@@ -619,48 +633,81 @@ __device__ __forceinline__ void forget(T (&x)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "=v"(x[i]));
 }
 
-// Walks tiles [kt_a, kt_b) through the 4-stage ring; every row of the workgroup sees the
+// Walks tiles [kt_a, kt_b) through the ring; every row of the workgroup sees the
 // tiles below kt_mid in full.  Self-contained: starts with no load in flight and ends with
 // none.
 //
 // Iteration `cur` runs RowBlock::fused(): the softmax and P*V of tile cur together
 // with the Q*K^T of tile cur+1, whose scores it hands to the next iteration in
 // registers (two score sets, used alternately).  So at the barrier that opens
-// iteration cur, tile cur+1 must have landed, tile cur+2 is in flight, and tile cur+3
-// is issued into the stage of tile cur-1, which everybody left at that barrier.
+// iteration cur, K tile cur+1 and V tile cur must have landed, K tile cur+2 is in flight, and
+// K tile cur+3 is issued in the iteration.  With it
+//   4 V stages: V tile cur+3, both into the stages of tile cur-1, which everybody left at that
+//     barrier: two tiles in flight between iterations, for long streams;
+//   2 V stages: V tile cur+1, into the stage of V tile cur-1, and K tile cur+3 into that of K tile
+//     cur, read for the last time in the iteration before.  5/8 of the LDS, so that at head dim
+//     128 two workgroups of 4 wavefronts fit a compute unit (80 KiB each) and one's start and end
+//     hide behind the other's walk; the V tile has one iteration to land.  (900 tokens at 2000,
+//     8/2 heads, 35.7 -> 31.2 us; 60 tokens at 500K, 32/8 heads, 644 -> 556.  Long walks of many
+//     row tiles take 4 % longer so: each pair fetches K and V twice, which costs clock.)
 //
 // The masked tiles follow the unmasked ones in the same pipeline.  Ring stages are
-// compile-time, so the change-over happens between groups of NS tiles: up to NS-1 fully
+// compile-time, so the change-over happens between rounds of 4 (6) tiles: up to 3 (5) fully
 // visible tiles take the masked form, which costs each about a fifth more; draining the ring
 // and filling it again at the exact tile (as two walks) costs 3 to 4 tiles' time.
-template <int D, int NW, int NS>
+template <int D, int NW, int NV>
 __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args, ConstI32Ptr pt,
                                           int kt_a, int kt_mid, int kt_b, int kv_total,
                                           int kv_head, const Ring& ring,
                                           const TileLoader<D, NW>& ld, int wave, int lane) {
   using G = TileGeom<D, NW>;
-  static_assert(NS == 4, "stages: tile cur, cur+1, cur+2 (in flight), cur+3 (being issued)");
-  static_assert(kWarmTiles % NS == 0, "the walk's head is a whole number of ring rounds");
-  constexpr int kTile = G::kTileBytes;  // K tiles fill the low half of the ring, V tiles the high
+  using R = RingShape<NV>;
+  static_assert(kWarmTiles % R::kRound == 0, "the walk's head is a whole number of ring rounds");
+  constexpr int kTile = G::kTileBytes;  // K tiles fill the low part of the ring, V tiles the high
   if (kt_a >= kt_b) return;
   const int half = lane >> 5;
   const int last = kt_b - 1;
   // tiles [kt_a, kt_u) take the unmasked form
-  const int kt_u = kt_mid >= kt_b ? kt_b : kt_a + (kt_mid - kt_a) / NS * NS;
-  // prologue: tiles kt_a .. kt_a+2 (clamped: a repeated tile is loaded again, harmlessly)
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const int tile = min(kt_a + s, last);
-    const int page = tile_page<D, NW>(pt, tile, kv_total, wave);
-    ld.issue(args, page, tile, kv_total, kv_head, ring.lds_addr + s * kTile,
-             ring.lds_addr + (NS + s) * kTile);
-  }
-  // page id of the next tile to issue
-  int page_next = tile_page<D, NW>(pt, min(kt_a + 3, last), kv_total, wave);
+  const int kt_u = kt_mid >= kt_b ? kt_b : kt_a + (kt_mid - kt_a) / R::kRound * R::kRound;
+  // Page ids of the next K tile to issue and of the two tiles before it.
+  int page_next = 0, page_1 = 0, page_2 = 0;
+  auto next_page = [&](int tile) {
+    if (R::kLag > 0) {
+      page_2 = page_1;
+      page_1 = page_next;
+    }
+    page_next = tile_page<D, NW>(pt, min(tile, last), kv_total, wave);
+  };
+  // Issues K tile `tile` into K stage k_stage and V tile `tile` - kLag into V stage v_stage, if that
+  // is one (tiles past the walk's end: the last one again, harmlessly).  With the short ring V goes
+  // first, so that the wait for it leaves the K tile in flight.
+  auto issue = [&](int tile, auto k_stage, auto v_stage) {
+    const uint32_t k_lds = ring.lds_addr + decltype(k_stage)::value * kTile;
+    const uint32_t v_lds = ring.lds_addr + (R::kK + decltype(v_stage)::value) * kTile;
+    if constexpr (R::kLag == 0) {
+      ld.template issue<true, true>(args, page_next, min(tile, last), kv_total, kv_head, k_lds, v_lds);
+    } else {
+      if constexpr (decltype(v_stage)::value >= 0)
+        ld.template issue<false, true>(args, page_2, min(tile - R::kLag, last), kv_total, kv_head, 0,
+                                       v_lds);
+      ld.template issue<true, false>(args, page_next, min(tile, last), kv_total, kv_head, k_lds, 0);
+    }
+  };
+  // loads of the iteration before that its successor's barrier leaves in flight
+  constexpr int kYoungest = R::kLag == 0 ? G::kLoadsPerWaveTile : G::kInstrPerWave;
+  // prologue: K tiles kt_a .. kt_a+2 and V tiles up to kt_a+2-kLag
+  auto first = [&](auto i_const) {
+    constexpr int i = decltype(i_const)::value;
+    next_page(kt_a + i);
+    issue(kt_a + i, i_const, std::integral_constant<int, i - R::kLag>{});
+  };
+  static_for<3>(first);
+  next_page(kt_a + 3);
   f32x16 s0[2], s1[2];  // scores of the even / odd tiles (counted from kt_a)
   forget(s0);
   forget(s1);
-  ring_barrier<2 * G::kLoadsPerWaveTile>();  // tile kt_a has landed, for everyone
+  // K tile kt_a has landed, for everyone
+  ring_barrier<R::kLag == 0 ? 2 * G::kLoadsPerWaveTile : 3 * G::kInstrPerWave>();
   rb.template qk<2>(ring.base, s0);
   if (kt_u > kt_a) {
     float mx = -INFINITY;
@@ -668,24 +715,24 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
     for (int f = 0; f < 32; ++f) mx = fmaxf(mx, s0[f >> 4][f & 15]);
     rb.template update_reference<false>(mx);
   }
-  // One group of NS iterations starting at tile kt (stage numbers are compile-time).
-  auto group = [&](int kt, auto mask, auto spec) {
+  // One round of iterations starting at tile kt (stage numbers are compile-time).
+  auto round = [&](int kt, auto mask, auto spec) {
     constexpr bool kMask = decltype(mask)::value, kSpeculate = decltype(spec)::value;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
+    auto iteration = [&](auto s_const) {
+      constexpr int s = decltype(s_const)::value;
       const int cur = kt + s;
       if (cur < last) {
-        // this wavefront's loads of tile cur+1 have landed (tile cur+2 may fly); after the
-        // barrier everyone's have, and everyone is done with the stage refilled next
-        ring_barrier<G::kLoadsPerWaveTile>();
+        // this wavefront's loads for the iteration have landed (the youngest may fly); after the
+        // barrier everyone's have, and everyone is done with the stages refilled next
+        ring_barrier<kYoungest>();
         auto issue_loads = [&] {
           asm volatile("" : "+s"(page_next));  // the page id is first needed here, not before
-          const uint32_t nxt = ring.lds_addr + ((s + 3) % NS) * kTile;
-          ld.issue(args, page_next, min(cur + 3, last), kv_total, kv_head, nxt, nxt + NS * kTile);
+          issue(cur + 3, std::integral_constant<int, (s + 3) % R::kK>{},
+                std::integral_constant<int, (s + 3 - R::kLag) % R::kV>{});
         };
-        const char* k_next = ring.base + ((s + 1) % NS) * kTile;
-        const char* v_cur = ring.base + s * kTile;  // + the bias in rb.v_off
-        if (s & 1)
+        const char* k_next = ring.base + ((s + 1) % R::kK) * kTile;
+        const char* v_cur = ring.base + (s % R::kV) * kTile;  // + the bias in rb.v_off
+        if constexpr (s & 1)
           rb.template fused<kMask, true, kSpeculate>(k_next, v_cur, s1, s0, cur * G::kTileKeys,
                                                      half, issue_loads);
         else
@@ -697,10 +744,11 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
         // an LDS operand becomes a wait for everything -- a stall of a scalar-load latency in
         // front of the tile's first MFMA.  Here its latency hides behind the barrier.
         __builtin_amdgcn_sched_barrier(0);
-        page_next = tile_page<D, NW>(pt, min(cur + 4, last), kv_total, wave);
+        next_page(cur + 4);
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    };
+    static_for<R::kRound>(iteration);
   };
   int kt = kt_a;
   const int end_u = min(kt_u, last);
@@ -709,17 +757,19 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
   // voting and the odd large score, rarely in the first twenty.  A failed check costs a
   // multiple of what the row maximum costs when it is taken up front, so the head of the
   // walk takes it up front.
-  for (; kt < end_u && kt < kt_a + kWarmTiles; kt += NS)
-    group(kt, std::false_type{}, std::false_type{});
+  for (; kt < end_u && kt < kt_a + kWarmTiles; kt += R::kRound)
+    round(kt, std::false_type{}, std::false_type{});
   // (the weight is for the register allocator: what has to be spilled is spilled elsewhere)
-  for (; __builtin_expect_with_probability(kt < end_u, 1, 0.995); kt += NS)
-    group(kt, std::false_type{}, std::true_type{});
-  for (; kt < last; kt += NS) group(kt, std::true_type{}, std::false_type{});
-  // the last tile: its scores are in registers, its V tile landed with its K tile (the exact route:
+  for (; __builtin_expect_with_probability(kt < end_u, 1, 0.995); kt += R::kRound)
+    round(kt, std::false_type{}, std::true_type{});
+  for (; kt < last; kt += R::kRound) round(kt, std::true_type{}, std::false_type{});
+  // the last tile: its scores are in registers, its V tile landed with its K tile, or at this
+  // barrier (the exact route:
   // at a short walk's end speculation fails, and one tile of a long one costs nothing)
+  if constexpr (R::kLag > 0) ring_barrier<kYoungest>();
   auto final_tile = [&](auto mask) {
     constexpr bool kMask = decltype(mask)::value;
-    const char* v_last = ring.base + ((last - kt_a) % NS) * kTile;  // + the bias in rb.v_off
+    const char* v_last = ring.base + ((last - kt_a) % R::kV) * kTile;  // + the bias in rb.v_off
     if ((last - kt_a) & 1)
       rb.template fused<kMask, false, false>(nullptr, v_last, s1, s0, last * G::kTileKeys, half, [] {});
     else
@@ -734,9 +784,9 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
 
 // (the launch bound is 512 also for the 4-wavefront variant: it makes the compiler budget
 // for two wavefronts per SIMD, at most 256 vector registers, all architectural)
-template <int D, int NW, int NS>
+template <int D, int NW, int NV>
 __global__ void __launch_bounds__(512) prefill_kernel(const AttnArgs args) {
-  using Shape = PrefillShape<D, NW, NS>;
+  using Shape = PrefillShape<D, NW, NV>;
   __shared__ __attribute__((aligned(1024))) char lds[Shape::kLdsBytes];
   const Ring stages{lds, lds_address(lds)};
 
@@ -756,8 +806,7 @@ __global__ void __launch_bounds__(512) prefill_kernel(const AttnArgs args) {
   const int col = lane & 31, half = lane >> 5;
 
   RowBlock<D> rb;
-  // V tiles sit NS K-tiles above the ring's base
-  rb.init(fabsf(args.scale_log2), lane, NS * TileGeom<D, NW>::kTileBytes);
+  rb.init(fabsf(args.scale_log2), lane, Shape::kVBias);
 
   const int wg_row0 = row_tile * Shape::kRowsPerWg;
   const int r = wg_row0 + wave * 32 + col;
@@ -794,7 +843,7 @@ __global__ void __launch_bounds__(512) prefill_kernel(const AttnArgs args) {
   ConstI32Ptr pt = (ConstI32Ptr)(args.page_table + sd.pt_off);
   TileLoader<D, NW> loader;
   loader.init(wave, lane);
-  run_tiles<D, NW, NS>(rb, args, pt, kt_begin, kt_mid, kt_end, kv_total, kv_head, stages, loader,
+  run_tiles<D, NW, NV>(rb, args, pt, kt_begin, kt_mid, kt_end, kv_total, kv_head, stages, loader,
                        wave, lane);
 
   const bool direct = sd.n_split == 1;

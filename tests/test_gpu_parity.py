@@ -574,6 +574,32 @@ def test_prompts_whose_walks_differ(h_q, h_kv, d, prefix, chunk, layout):
     check(out, lse, ro, rl, f"prompts hq{h_q} hkv{h_kv} d{d} {prefix} {chunk}")
 
 
+# ------------------------------------------------------------ small workgroups behind a prefix
+@pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk,n_split,paired", [
+    # pairs on a compute unit, short ring: ranges of 6 and 5 tiles whose last one is shorter, rows
+    # that see none, some or all of the last range; the masked tiles at several ring positions
+    (8, 2, 128, 2000, 900, 8, True), (8, 2, 128, 2049, 870, 8, True), (8, 2, 128, 1950, 901, 9, True),
+    # two row tiles, the second with 32 of 128 rows and with 4: 30-tile ranges, which leave the exact
+    # route, and a ragged last page
+    (32, 8, 128, 60000, 40, 32, True), (32, 8, 128, 61237, 33, 32, True), (16, 16, 128, 9000, 140, 16, True),
+    # alone on a compute unit: the smallest prefix, one range and several
+    (32, 8, 128, 49, 49, 1, False), (16, 16, 128, 300, 260, 2, False), (8, 1, 128, 2000, 64, 7, False),
+    (32, 8, 128, 1000, 300, 3, False), (32, 8, 64, 2000, 100, 7, False), (8, 2, 64, 3000, 64, 12, False),
+])
+def test_small_workgroups_behind_a_prefix(h_q, h_kv, d, prefix, chunk, n_split, paired):
+    """Chunks behind a prefix that leave the device idle or walk few tiles: 128-row workgroups."""
+    b = wl.make_prefill_batch("small_wg", h_q, h_kv, d, [prefix], [chunk], seed=prefix + chunk,
+                              poison_unused=True)
+    e, grid_rows, _, _ = medha.describe_plan(b.prefix_len, b.chunk_len, h_q, h_kv, d, 256)
+    assert (e[0].rows_per_wg, e[0].n_split) == (128, n_split) and (grid_rows > 256) == paired
+    rows = edge_rows(b, prefix, 6, 8, 8, 12) if prefix * chunk > 500_000 else None
+    ro, rl = oracle_prefill(b, rows)
+    out, lse = gpu_prefill(to_dev(b))
+    if rows is not None:
+        out, lse = out[rows], lse[rows]
+    check(out, lse, ro, rl, f"small workgroups hq{h_q} hkv{h_kv} d{d} P{prefix} c{chunk}")
+
+
 # ------------------------------------------------------------ softmax scale values
 @pytest.mark.parametrize("d,prefix", [(128, 64 * 20 + 7), (128, 64 * 23), (64, 64 * 22 - 1)])
 def test_walks_that_end_around_the_exact_route_warm_up(d, prefix):
