@@ -1,4 +1,5 @@
-"""ctypes binding over libmedha.so: argument marshalling only.
+"""Binding over libmedha.so: argument marshalling only, through ctypes and, for ordinary tensor
+calls, through the extension module _marshal.
 
 Device tensors are torch tensors (PyTorch is used for device memory and streams
 only); host-side length arrays are numpy / lists.  Every function enqueues on
@@ -16,6 +17,9 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libmedha.so")
 _LIB = None
+# The extension module that makes ordinary tensor calls (csrc/marshal.cpp), once the library is
+# loaded.  It answers None, with nothing enqueued, for a call that it leaves to the code here.
+_NATIVE = None
 
 EXPORTS = (
     "medha_chunked_prefill_attn",
@@ -60,12 +64,14 @@ def library_path() -> str:
 def load_library():
     """Load libmedha.so (built in-tree by ``paper_2409_17264_amd.build``).
     There is no fallback: a missing library is an error."""
-    global _LIB
+    global _LIB, _NATIVE
     if _LIB is not None:
         return _LIB
     if not os.path.exists(_LIB_PATH):
         raise FileNotFoundError(
             f"{_LIB_PATH} is missing: build it with `python -m paper_2409_17264_amd.build`")
+    from . import _marshal  # built with the library
+
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f32, sz = (ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float,
                              ctypes.c_size_t)
@@ -106,7 +112,11 @@ def load_library():
     lib.medha_strerror.argtypes = [ctypes.c_int]
     lib.medha_abi_version.restype = ctypes.c_int
     lib.medha_abi_version.argtypes = []
-    _LIB = lib
+    calls = ("medha_chunked_prefill_attn", "medha_chunked_prefill_attn_alloc",
+             "medha_decode_partial_attn", "medha_chunk_partial_attn", "medha_lse_merge",
+             "medha_kv_append")
+    _marshal.bind(_stream, *(ctypes.cast(getattr(lib, name), vp).value for name in calls))
+    _LIB, _NATIVE = lib, _marshal
     return lib
 
 
@@ -218,6 +228,10 @@ def chunked_prefill_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Te
     length arrays live on the host.  Returns (out fp32 [tokens][h_q][d],
     lse fp32 [tokens][h_q])."""
     lib = load_library()
+    done = _NATIVE.chunked_prefill_attn(q, k_pool, v_pool, page_table, page_table_offs, prefix_len,
+                                        chunk_len, softmax_scale, out, lse, workspace)
+    if done is not None:
+        return done
     assert q.is_cuda and q.dtype == torch.bfloat16 and q.is_contiguous() and q.dim() == 3
     assert page_table.is_cuda and page_table.dtype == torch.int32 and page_table.is_contiguous()
     tokens, h_q, d = q.shape
@@ -276,6 +290,10 @@ def decode_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Ten
     """q bf16 [num_queries][h_q][d]; returns (out_partial fp32 [items][h_q][d],
     lse_partial fp32 [items][h_q])."""
     lib = load_library()
+    done = _NATIVE.decode_partial_attn(q, k_pool, v_pool, page_table, page_table_offs, q_index, kv_len,
+                                       softmax_scale, out_partial, lse_partial, workspace)
+    if done is not None:
+        return done
     assert q.is_cuda and q.dtype == torch.bfloat16 and q.is_contiguous() and q.dim() == 3
     assert page_table.is_cuda and page_table.dtype == torch.int32 and page_table.is_contiguous()
     num_queries, h_q, d = q.shape
@@ -319,6 +337,11 @@ def chunk_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Tens
     keys of its page-table slice, row j seeing the first min(kv_len, max(0, visible0 + j)).
     Returns (out_partial fp32 [sum chunk_len][h_q][d], lse_partial fp32 [sum chunk_len][h_q])."""
     lib = load_library()
+    done = _NATIVE.chunk_partial_attn(q, k_pool, v_pool, page_table, page_table_offs, q_row, chunk_len,
+                                      kv_len, visible0, softmax_scale, out_partial, lse_partial,
+                                      workspace)
+    if done is not None:
+        return done
     assert q.is_cuda and q.dtype == torch.bfloat16 and q.is_contiguous() and q.dim() == 3
     assert page_table.is_cuda and page_table.dtype == torch.int32 and page_table.is_contiguous()
     tokens, h_q, d = q.shape
@@ -351,6 +374,9 @@ def lse_merge(out_partial: torch.Tensor, lse_partial: torch.Tensor,
               out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None):
     """out_partial fp32 [S][rows][h_q][d], lse_partial fp32 [S][rows][h_q]."""
     lib = load_library()
+    done = _NATIVE.lse_merge(out_partial, lse_partial, out, lse)
+    if done is not None:
+        return done
     assert out_partial.is_cuda and out_partial.dtype == torch.float32
     assert lse_partial.dtype == torch.float32
     assert out_partial.is_contiguous() and lse_partial.is_contiguous() and out_partial.dim() == 4
@@ -372,6 +398,10 @@ def kv_append(k_new: torch.Tensor, v_new: torch.Tensor, k_pool: torch.Tensor,
               chunk_len) -> None:
     """k_new, v_new bf16 [tokens][h_kv][d] (device) are written into the pools in place."""
     lib = load_library()
+    done = _NATIVE.kv_append(k_new, v_new, k_pool, v_pool, page_table, page_table_offs, prefix_len,
+                             chunk_len)
+    if done is not None:
+        return None
     for t in (k_new, v_new):
         assert t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.dim() == 3
     assert k_new.shape == v_new.shape

@@ -1,5 +1,6 @@
 """Compile the HIP libraries for gfx950: csrc/medha.hip into libmedha.so (the product)
-and csrc/yardstick.hip into libmedha_yardstick.so (the benchmark's yardsticks).
+and csrc/yardstick.hip into libmedha_yardstick.so (the benchmark's yardsticks), and the
+binding's host code, csrc/marshal.cpp, into the extension module _marshal.so.
 
 Run as ``python -m paper_2409_17264_amd.build``; also called by
 ``__graft_entry__.build()``.  hipcc cross-compiles without a GPU.
@@ -8,6 +9,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -16,6 +18,8 @@ LIB = os.path.join(HERE, "libmedha.so")
 # source file -> shared library
 TARGETS = {"medha.hip": LIB, "yardstick.hip": os.path.join(HERE, "libmedha_yardstick.so")}
 
+MARSHAL = os.path.join(HERE, "_marshal.so")
+
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -23,22 +27,39 @@ HIPCC_FLAGS = [
 ]
 
 
+def _run(cmd, what: str, verbose: bool) -> None:
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError(f"the compiler failed on {what}")
+    if verbose and res.stderr:
+        lines = [l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l]
+        sys.stderr.write("\n".join(lines) + "\n")
+
+
+def _marshal_command():
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    include, lib = os.path.join(root, "include"), os.path.join(root, "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I", INCLUDE, "-I", CSRC, "-isystem", include,
+            "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"),
+            "-o", MARSHAL, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     found = sorted(os.path.basename(p) for p in glob.glob(os.path.join(CSRC, "*.hip")))
     assert found == sorted(TARGETS), f"every .hip source needs a target: {found}"
     for src, lib in TARGETS.items():
-        cmd = [hipcc] + HIPCC_FLAGS + ["-I", INCLUDE, "-I", CSRC, os.path.join(CSRC, src),
-                                       "-o", lib]
-        if verbose:
-            print(" ".join(cmd))
-        res = subprocess.run(cmd, capture_output=True, text=True)
-        if res.returncode != 0:
-            sys.stderr.write(res.stdout + res.stderr)
-            raise RuntimeError(f"hipcc failed on {src}")
-        if verbose and res.stderr:
-            lines = [l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l]
-            sys.stderr.write("\n".join(lines) + "\n")
+        _run([hipcc] + HIPCC_FLAGS + ["-I", INCLUDE, "-I", CSRC, os.path.join(CSRC, src), "-o", lib],
+             src, verbose)
+    _run(_marshal_command(), "marshal.cpp", verbose)
     return LIB
 
 

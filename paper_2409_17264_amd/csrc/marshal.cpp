@@ -1,0 +1,376 @@
+// Argument marshalling of the Python binding's tensor calls: what binding.py does with a call's
+// arguments, in native code.  An ordinary call (plain tensors, arrays of the right types, everything
+// in order) is made from here; every other one is answered with None, with nothing enqueued, and
+// binding.py then goes through it step by step, converts what can be converted and raises what has
+// to be raised.  (Host time of one decode at 2048 tokens, its append and its attention: 23.9 us in
+// Python, of which 7 us were the three launches and 5 us the three allocations; no more than the
+// 16 us of its kernels from here.)
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <c10/util/SmallVector.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstring>
+#include <limits>
+
+#include "medha.h"
+#include "medha_internal.h"
+
+namespace {
+
+// Entry points of libmedha.so (bind()), and the binding's function for torch's current stream.
+struct Library {
+  decltype(&medha_chunked_prefill_attn) prefill = nullptr;
+  decltype(&medha_chunked_prefill_attn_alloc) prefill_alloc = nullptr;
+  decltype(&medha_decode_partial_attn) decode = nullptr;
+  decltype(&medha_chunk_partial_attn) chunk = nullptr;
+  decltype(&medha_lse_merge) merge = nullptr;
+  decltype(&medha_kv_append) append = nullptr;
+  PyObject* stream = nullptr;
+} lib;
+
+// A host array of the caller's, copied: the call runs without the interpreter's lock.
+template <class T>
+class HostArray {
+ public:
+  // False unless `o` is a C-contiguous buffer of T.
+  bool take(PyObject* o) {
+    Py_buffer view;
+    if (PyObject_GetBuffer(o, &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) != 0) {
+      PyErr_Clear();
+      return false;
+    }
+    const char* f = view.format;
+    const bool type = f != nullptr && f[0] != 0 && f[1] == 0 &&
+                      (sizeof(T) == 4 ? f[0] == 'i' : f[0] == 'l' || f[0] == 'q') &&
+                      view.itemsize == (Py_ssize_t)sizeof(T);
+    if (type) {
+      values_.resize(view.len / sizeof(T));
+      if (view.len > 0) std::memcpy(values_.data(), view.buf, view.len);
+    }
+    PyBuffer_Release(&view);
+    return type;
+  }
+  const T* data() const { return values_.data(); }
+  int64_t size() const { return (int64_t)values_.size(); }
+
+ private:
+  c10::SmallVector<T, 72> values_;
+};
+
+// The interpreter's lock is given back in this scope, as ctypes does around a call.
+class Unlocked {
+ public:
+  Unlocked() : state_(PyEval_SaveThread()) {}
+  ~Unlocked() { PyEval_RestoreThread(state_); }
+  Unlocked(const Unlocked&) = delete;
+
+ private:
+  PyThreadState* state_;
+};
+
+int64_t total(const HostArray<int32_t>& a) {
+  int64_t sum = 0;
+  for (int64_t i = 0; i < a.size(); ++i) sum += a.data()[i];
+  return sum;
+}
+
+// A plain tensor (no subclass), or null.
+const at::Tensor* tensor(PyObject* o) {
+  return THPVariable_CheckExact(o) ? &THPVariable_Unpack(o) : nullptr;
+}
+
+bool device_array(const at::Tensor* t, at::ScalarType type, int64_t dim) {
+  return t != nullptr && t->is_cuda() && t->scalar_type() == type && t->is_contiguous() &&
+         (dim < 0 || t->dim() == dim);
+}
+
+bool cache(PyObject* k, PyObject* v, medha_kv_cache& kv) {
+  const at::Tensor *kt = tensor(k), *vt = tensor(v);
+  if (!device_array(kt, at::kBFloat16, 4) || !device_array(vt, at::kBFloat16, 4) ||
+      kt->sizes() != vt->sizes())
+    return false;
+  for (int i = 0; i < 4; ++i)
+    if (kt->size(i) > std::numeric_limits<int32_t>::max()) return false;
+  kv = medha_kv_cache{kt->data_ptr(), vt->data_ptr(), (int32_t)kt->size(0), (int32_t)kt->size(2),
+                      (int32_t)kt->size(1), (int32_t)kt->size(3)};
+  return true;
+}
+
+// Page table and offsets of n sequences.
+bool pages(const at::Tensor* table, const HostArray<int64_t>& offs, int64_t n) {
+  return device_array(table, at::kInt, -1) && n >= 1 && n < std::numeric_limits<int32_t>::max() &&
+         offs.size() == n + 1 && offs.data()[n] <= table->numel();
+}
+
+// An output: the caller's tensor, checked, or a new one.
+bool output(PyObject* o, at::IntArrayRef sizes, const at::Tensor& like, at::Tensor& t) {
+  if (o == Py_None) {
+    t = at::empty(sizes, like.options().dtype(at::kFloat));
+    return true;
+  }
+  const at::Tensor* given = tensor(o);
+  if (!device_array(given, at::kFloat, -1) || given->sizes() != sizes) return false;
+  t = *given;
+  return true;
+}
+
+PyObject* pair(PyObject* a, const at::Tensor& ta, PyObject* b, const at::Tensor& tb) {
+  PyObject* x = a == Py_None ? THPVariable_Wrap(ta) : Py_NewRef(a);
+  PyObject* y = b == Py_None ? THPVariable_Wrap(tb) : Py_NewRef(b);
+  PyObject* r = x && y ? PyTuple_Pack(2, x, y) : nullptr;
+  Py_XDECREF(x);
+  Py_XDECREF(y);
+  return r;
+}
+
+bool number(PyObject* o, float& x) {
+  const double d = PyFloat_AsDouble(o);
+  if (d == -1.0 && PyErr_Occurred()) {
+    PyErr_Clear();
+    return false;
+  }
+  x = (float)d;
+  return true;
+}
+
+bool current_stream(void*& stream) {
+  PyObject* s = PyObject_CallNoArgs(lib.stream);
+  if (s == nullptr) return false;
+  stream = PyLong_AsVoidPtr(s);
+  Py_DECREF(s);
+  return !PyErr_Occurred();
+}
+
+// Runs `call` as the binding's steps are run: a C++ error (a tensor without storage, memory that is
+// not there) leaves the call to binding.py.  `call` returns a result, null with a Python error set,
+// or null without one for "not from here".
+template <class F>
+PyObject* ordinary(F&& call) {
+  if (lib.stream == nullptr) Py_RETURN_NONE;
+  PyObject* r = nullptr;
+  try {
+    r = call();
+  } catch (const std::exception&) {
+    r = nullptr;
+  }
+  if (r == nullptr) {
+    PyErr_Clear();  // (whatever it is comes again on the long way)
+    Py_RETURN_NONE;
+  }
+  return r;
+}
+
+struct Workspace {
+  at::Tensor bytes;
+  at::TensorOptions options;
+};
+
+void* allocate(size_t n, void* context) {
+  Workspace* w = static_cast<Workspace*>(context);
+  try {
+    w->bytes = at::empty({(int64_t)std::max<size_t>(n, 256)}, w->options);
+    return w->bytes.data_ptr();
+  } catch (const std::exception&) {
+    return nullptr;
+  }
+}
+
+// (q, k_pool, v_pool, page_table, offs, prefix_len, chunk_len, scale, out, lse, workspace)
+PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return ordinary([&]() -> PyObject* {
+    const at::Tensor *q, *table;
+    medha_kv_cache kv;
+    HostArray<int64_t> offs;
+    HostArray<int32_t> pre, chk;
+    float scale;
+    void* stream;
+    if (n != 11 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
+        !offs.take(a[4]) || !pre.take(a[5]) || !chk.take(a[6]) || chk.size() != pre.size() ||
+        !pages(table = tensor(a[3]), offs, pre.size()) || total(chk) != q->size(0) ||
+        q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[7], scale))
+      return nullptr;
+    at::Tensor out, lse;
+    if (!output(a[8], q->sizes(), *q, out) || !output(a[9], q->sizes().slice(0, 2), *q, lse))
+      return nullptr;
+    const at::Tensor* given = a[10] == Py_None ? nullptr : tensor(a[10]);
+    if ((a[10] != Py_None && given == nullptr) || !current_stream(stream)) return nullptr;
+    Workspace ws{{}, q->options().dtype(at::kByte)};
+    const void* qp = q->data_ptr();
+    const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
+    float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
+    void* wp = given ? given->data_ptr() : nullptr;
+    const int32_t batch = (int32_t)pre.size(), h_q = (int32_t)q->size(1);
+    int rc;
+    {
+      Unlocked unlocked;
+      rc = given ? lib.prefill(qp, &kv, tp, offs.data(), pre.data(), chk.data(), batch, h_q, scale, op,
+                             lp, wp, (size_t)given->numel(), stream)
+               : lib.prefill_alloc(qp, &kv, tp, offs.data(), pre.data(), chk.data(), batch, h_q,
+                                   scale, op, lp, allocate, &ws, stream);
+    }
+    return rc == MEDHA_OK ? pair(a[8], out, a[9], lse) : nullptr;
+  });
+}
+
+// (q, k_pool, v_pool, page_table, offs, q_index, kv_len, scale, out, lse, workspace)
+PyObject* decode_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return ordinary([&]() -> PyObject* {
+    const at::Tensor *q, *table, *ws;
+    medha_kv_cache kv;
+    HostArray<int64_t> offs;
+    HostArray<int32_t> qi, kl;
+    float scale;
+    void* stream;
+    if (n != 11 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
+        !offs.take(a[4]) || !qi.take(a[5]) || !kl.take(a[6]) || kl.size() != qi.size() ||
+        !pages(table = tensor(a[3]), offs, qi.size()) ||
+        q->size(0) > std::numeric_limits<int32_t>::max() ||
+        q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[7], scale) ||
+        (ws = tensor(a[10])) == nullptr)
+      return nullptr;
+    at::Tensor out, lse;
+    const int64_t sizes[3] = {qi.size(), q->size(1), q->size(2)};
+    if (!output(a[8], at::IntArrayRef(sizes, 3), *q, out) ||
+        !output(a[9], at::IntArrayRef(sizes, 2), *q, lse) || !current_stream(stream))
+      return nullptr;
+    const void* qp = q->data_ptr();
+    const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
+    float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
+    void* wp = ws->data_ptr();
+    int rc;
+    {
+      Unlocked unlocked;
+      rc = lib.decode(qp, (int32_t)q->size(0), &kv, tp, offs.data(), qi.data(), kl.data(),
+                    (int32_t)qi.size(), (int32_t)q->size(1), scale, op, lp, wp, (size_t)ws->numel(),
+                    stream);
+    }
+    return rc == MEDHA_OK ? pair(a[8], out, a[9], lse) : nullptr;
+  });
+}
+
+// (q, k_pool, v_pool, page_table, offs, q_row, chunk_len, kv_len, visible0, scale, out, lse,
+// workspace)
+PyObject* chunk_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return ordinary([&]() -> PyObject* {
+    const at::Tensor *q, *table, *ws;
+    medha_kv_cache kv;
+    HostArray<int64_t> offs;
+    HostArray<int32_t> qr, chk, kl, v0;
+    float scale;
+    void* stream;
+    if (n != 13 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
+        !offs.take(a[4]) || !qr.take(a[5]) || !chk.take(a[6]) || !kl.take(a[7]) ||
+        !v0.take(a[8]) || chk.size() != qr.size() || kl.size() != qr.size() ||
+        v0.size() != qr.size() || !pages(table = tensor(a[3]), offs, qr.size()) ||
+        q->size(0) > std::numeric_limits<int32_t>::max() ||
+        q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[9], scale) ||
+        (ws = tensor(a[12])) == nullptr)
+      return nullptr;
+    at::Tensor out, lse;
+    const int64_t sizes[3] = {total(chk), q->size(1), q->size(2)};
+    if (sizes[0] < 0 || !output(a[10], at::IntArrayRef(sizes, 3), *q, out) ||
+        !output(a[11], at::IntArrayRef(sizes, 2), *q, lse) || !current_stream(stream))
+      return nullptr;
+    const void* qp = q->data_ptr();
+    const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
+    float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
+    void* wp = ws->data_ptr();
+    int rc;
+    {
+      Unlocked unlocked;
+      rc = lib.chunk(qp, (int32_t)q->size(0), &kv, tp, offs.data(), qr.data(), chk.data(), kl.data(),
+                   v0.data(), (int32_t)qr.size(), (int32_t)q->size(1), scale, op, lp, wp,
+                   (size_t)ws->numel(), stream);
+    }
+    return rc == MEDHA_OK ? pair(a[10], out, a[11], lse) : nullptr;
+  });
+}
+
+// (out_partial, lse_partial, out, lse)
+PyObject* lse_merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return ordinary([&]() -> PyObject* {
+    const at::Tensor *po, *pl;
+    void* stream;
+    if (n != 4 || !device_array(po = tensor(a[0]), at::kFloat, 4) ||
+        !device_array(pl = tensor(a[1]), at::kFloat, 3) || pl->sizes() != po->sizes().slice(0, 3) ||
+        po->size(0) > std::numeric_limits<int32_t>::max() ||
+        po->size(2) > std::numeric_limits<int32_t>::max() ||
+        po->size(3) > std::numeric_limits<int32_t>::max())
+      return nullptr;
+    at::Tensor out, lse;
+    if (!output(a[2], po->sizes().slice(1), *po, out) ||
+        !output(a[3], po->sizes().slice(1, 2), *po, lse) || !current_stream(stream))
+      return nullptr;
+    const float *pop = static_cast<const float*>(po->data_ptr()),
+                *plp = static_cast<const float*>(pl->data_ptr());
+    float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
+    int rc;
+    {
+      Unlocked unlocked;
+      rc = lib.merge(pop, plp, (int32_t)po->size(0), po->size(1), (int32_t)po->size(2),
+                   (int32_t)po->size(3), op, lp, stream);
+    }
+    return rc == MEDHA_OK ? pair(a[2], out, a[3], lse) : nullptr;
+  });
+}
+
+// (k_new, v_new, k_pool, v_pool, page_table, offs, prefix_len, chunk_len); True when done
+PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return ordinary([&]() -> PyObject* {
+    const at::Tensor *k, *v, *table;
+    medha_kv_cache kv;
+    HostArray<int64_t> offs;
+    HostArray<int32_t> pre, chk;
+    void* stream;
+    if (n != 8 || !device_array(k = tensor(a[0]), at::kBFloat16, 3) ||
+        !device_array(v = tensor(a[1]), at::kBFloat16, 3) || k->sizes() != v->sizes() ||
+        !cache(a[2], a[3], kv) || k->size(1) != kv.num_kv_heads || k->size(2) != kv.head_dim ||
+        !offs.take(a[5]) || !pre.take(a[6]) || !chk.take(a[7]) || chk.size() != pre.size() ||
+        !pages(table = tensor(a[4]), offs, pre.size()) || total(chk) != k->size(0) ||
+        !current_stream(stream))
+      return nullptr;
+    const void *kp = k->data_ptr(), *vp = v->data_ptr();
+    const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
+    int rc;
+    {
+      Unlocked unlocked;
+      rc = lib.append(kp, vp, &kv, tp, offs.data(), pre.data(), chk.data(), (int32_t)pre.size(),
+                    stream);
+    }
+    return rc == MEDHA_OK ? Py_NewRef(Py_True) : nullptr;
+  });
+}
+
+// bind(stream, prefill, prefill_alloc, decode, chunk, merge, append): the entry points' addresses
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 7) {
+    PyErr_SetString(PyExc_TypeError, "bind() takes 7 arguments");
+    return nullptr;
+  }
+  void* p[6];
+  for (int i = 0; i < 6; ++i) p[i] = PyLong_AsVoidPtr(a[i + 1]);
+  if (PyErr_Occurred()) return nullptr;
+  lib.prefill = reinterpret_cast<decltype(lib.prefill)>(p[0]);
+  lib.prefill_alloc = reinterpret_cast<decltype(lib.prefill_alloc)>(p[1]);
+  lib.decode = reinterpret_cast<decltype(lib.decode)>(p[2]);
+  lib.chunk = reinterpret_cast<decltype(lib.chunk)>(p[3]);
+  lib.merge = reinterpret_cast<decltype(lib.merge)>(p[4]);
+  lib.append = reinterpret_cast<decltype(lib.append)>(p[5]);
+  Py_XSETREF(lib.stream, Py_NewRef(a[0]));
+  Py_RETURN_NONE;
+}
+
+#define CALL(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {CALL(bind), CALL(chunked_prefill_attn), CALL(decode_partial_attn),
+                         CALL(chunk_partial_attn), CALL(lse_merge), CALL(kv_append),
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }

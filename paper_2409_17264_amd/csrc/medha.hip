@@ -1,6 +1,7 @@
 // C ABI of the gfx950 paged-attention library: argument validation, launch
 // planning and kernel launches.  See include/medha.h for the contract.
 #include "medha.h"
+#include "medha_internal.h"
 
 #include <hip/hip_runtime.h>
 
@@ -239,6 +240,45 @@ int described_plan(const int32_t* prefix_len, const int32_t* chunk_len, int32_t 
   return MEDHA_OK;
 }
 
+// A chunked-prefill call; `alloc`: asked for a workspace of the reported size instead of the
+// caller's (an empty batch needs none).
+int chunked_prefill(const void* q, const medha_kv_cache* kv, const int32_t* page_table,
+                    const int64_t* page_table_offs, const int32_t* prefix_len,
+                    const int32_t* chunk_len, int32_t batch, int32_t num_q_heads,
+                    float softmax_scale, float* out, float* lse, void* workspace,
+                    size_t workspace_bytes, medha_alloc alloc, void* context, void* hip_stream) {
+  if (batch < 0) return MEDHA_ERR_INVALID_ARG;
+  int rc = check_kv(kv, num_q_heads);
+  if (rc != MEDHA_OK) return rc;
+  if (batch == 0) return MEDHA_OK;
+  if (q == nullptr || page_table == nullptr || page_table_offs == nullptr ||
+      prefix_len == nullptr || chunk_len == nullptr || out == nullptr || lse == nullptr)
+    return MEDHA_ERR_INVALID_ARG;
+  if (!aligned(q, 16) || !aligned(out, 16) || !aligned(lse, 4) || !std::isfinite(softmax_scale))
+    return MEDHA_ERR_INVALID_ARG;
+  std::vector<SeqInput> seqs(batch);
+  int64_t row = 0;
+  for (int b = 0; b < batch; ++b) {
+    if (prefix_len[b] < 0 || chunk_len[b] < 1) return MEDHA_ERR_INVALID_ARG;
+    const int64_t n = (int64_t)prefix_len[b] + chunk_len[b];
+    if (n > INT32_MAX) return MEDHA_ERR_INVALID_ARG;
+    const int64_t have = page_table_offs[b + 1] - page_table_offs[b];
+    if (page_table_offs[b] < 0 || have < ceil_div(n, kPageSize)) return MEDHA_ERR_INVALID_ARG;
+    seqs[b] = SeqInput{page_table_offs[b], (int32_t)row, (int32_t)row, chunk_len[b], prefix_len[b]};
+    row += chunk_len[b];
+    if (row > INT32_MAX) return MEDHA_ERR_INVALID_ARG;
+  }
+  const Plan plan = make_plan(seqs.data(), batch, num_q_heads, kv->num_kv_heads, kv->head_dim,
+                              current_num_cus(),
+                              alloc ? SIZE_MAX : usable_bytes(workspace, workspace_bytes));
+  if (alloc) {
+    workspace_bytes = plan.workspace_bytes();
+    workspace = alloc(workspace_bytes, context);
+  }
+  return run_plan(plan, q, kv, page_table, num_q_heads, softmax_scale, out, lse, workspace,
+                  workspace_bytes, hip_stream);
+}
+
 }  // namespace
 }  // namespace medha
 
@@ -271,31 +311,21 @@ int medha_chunked_prefill_attn(const void* q, const medha_kv_cache* kv, const in
                                const int32_t* chunk_len, int32_t batch, int32_t num_q_heads,
                                float softmax_scale, float* out, float* lse, void* workspace,
                                size_t workspace_bytes, void* hip_stream) {
-  if (batch < 0) return MEDHA_ERR_INVALID_ARG;
-  int rc = check_kv(kv, num_q_heads);
-  if (rc != MEDHA_OK) return rc;
-  if (batch == 0) return MEDHA_OK;
-  if (q == nullptr || page_table == nullptr || page_table_offs == nullptr ||
-      prefix_len == nullptr || chunk_len == nullptr || out == nullptr || lse == nullptr)
-    return MEDHA_ERR_INVALID_ARG;
-  if (!aligned(q, 16) || !aligned(out, 16) || !aligned(lse, 4) || !std::isfinite(softmax_scale))
-    return MEDHA_ERR_INVALID_ARG;
-  std::vector<SeqInput> seqs(batch);
-  int64_t row = 0;
-  for (int b = 0; b < batch; ++b) {
-    if (prefix_len[b] < 0 || chunk_len[b] < 1) return MEDHA_ERR_INVALID_ARG;
-    const int64_t n = (int64_t)prefix_len[b] + chunk_len[b];
-    if (n > INT32_MAX) return MEDHA_ERR_INVALID_ARG;
-    const int64_t have = page_table_offs[b + 1] - page_table_offs[b];
-    if (page_table_offs[b] < 0 || have < ceil_div(n, kPageSize)) return MEDHA_ERR_INVALID_ARG;
-    seqs[b] = SeqInput{page_table_offs[b], (int32_t)row, (int32_t)row, chunk_len[b], prefix_len[b]};
-    row += chunk_len[b];
-    if (row > INT32_MAX) return MEDHA_ERR_INVALID_ARG;
-  }
-  const Plan plan = make_plan(seqs.data(), batch, num_q_heads, kv->num_kv_heads, kv->head_dim,
-                              current_num_cus(), usable_bytes(workspace, workspace_bytes));
-  return run_plan(plan, q, kv, page_table, num_q_heads, softmax_scale, out, lse, workspace,
-                  workspace_bytes, hip_stream);
+  return chunked_prefill(q, kv, page_table, page_table_offs, prefix_len, chunk_len, batch,
+                         num_q_heads, softmax_scale, out, lse, workspace, workspace_bytes, nullptr,
+                         nullptr, hip_stream);
+}
+
+int medha_chunked_prefill_attn_alloc(const void* q, const medha_kv_cache* kv,
+                                     const int32_t* page_table, const int64_t* page_table_offs,
+                                     const int32_t* prefix_len, const int32_t* chunk_len,
+                                     int32_t batch, int32_t num_q_heads, float softmax_scale,
+                                     float* out, float* lse, medha_alloc alloc, void* context,
+                                     void* hip_stream) {
+  if (alloc == nullptr) return MEDHA_ERR_INVALID_ARG;
+  return chunked_prefill(q, kv, page_table, page_table_offs, prefix_len, chunk_len, batch,
+                         num_q_heads, softmax_scale, out, lse, nullptr, 0, alloc, context,
+                         hip_stream);
 }
 
 int medha_chunked_prefill_attn_noalloc(const void* q, const medha_kv_cache* kv,

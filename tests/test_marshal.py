@@ -1,0 +1,145 @@
+"""The extension module that makes ordinary tensor calls does what the binding's own steps do:
+the same results, outputs and errors for every form of the arguments."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_17264_amd as medha
+from paper_2409_17264_amd import binding
+from paper_2409_17264_amd import workloads as wl
+
+
+class _Nothing:
+    """Leaves every call to the binding."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def _outcome(call):
+    try:
+        r = call()
+    except Exception as e:  # noqa: BLE001
+        return type(e), getattr(e, "code", None)
+    torch.cuda.synchronize()
+    return r
+
+
+def _same(a, b):
+    if isinstance(a, tuple) and a and isinstance(a[0], torch.Tensor):
+        assert isinstance(b, tuple) and len(a) == len(b)
+        for x, y in zip(a, b):
+            assert (x.dtype, x.shape, x.device, x.is_contiguous()) == (y.dtype, y.shape, y.device,
+                                                                       y.is_contiguous())
+            assert torch.equal(x, y)
+    else:
+        assert a == b
+
+
+def _forms(x):
+    """The same numbers as a scheduler may hold them."""
+    x = np.asarray(x)
+    wide = np.zeros(2 * len(x), x.dtype)
+    wide[::2] = x
+    raw = np.zeros(x.nbytes + 1, np.uint8)
+    odd = raw[1:].view(x.dtype)
+    odd[:] = x
+    return [x, x.tolist(), tuple(x.tolist()), x.astype(np.int64), x.astype(np.int32),
+            x.astype(np.float64), wide[::2], x.reshape(1, -1), odd, torch.from_numpy(x.copy()),
+            x.astype(x.dtype.newbyteorder(">"))]
+
+
+def test_calls_without_a_device_are_refused_as_before():
+    b = wl.make_prefill_batch("cpu", 2, 1, 64, [20], [4], seed=1)
+    pt = torch.from_numpy(b.page_table)
+    with pytest.raises(AssertionError):
+        medha.chunked_prefill_attn(b.q, b.k_pool, b.v_pool, pt, b.page_table_offs, b.prefix_len,
+                                   b.chunk_len, b.scale)
+    with pytest.raises(AssertionError):
+        medha.lse_merge(torch.zeros(1, 1, 1, 4), torch.zeros(1, 1, 1))
+    with pytest.raises(AssertionError):
+        medha.kv_append(b.q[:, :1].contiguous(), b.q[:, :1].contiguous(), b.k_pool, b.v_pool, pt,
+                        b.page_table_offs, b.prefix_len, b.chunk_len)
+
+
+@pytest.mark.gpu
+def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
+    b = wl.make_prefill_batch("marshal", 8, 2, 128, [1500, 70, 0], [40, 1, 130], seed=11)
+    q, k, v = b.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda()
+    pt = torch.from_numpy(b.page_table).cuda()
+    offs, pre, chk = b.page_table_offs, b.prefix_len, b.chunk_len
+    tokens = b.tokens
+    new = wl.randn_bf16((tokens, 2, 128), 12, "cuda")
+    kl = (pre + chk).astype(np.int32)
+    qi = np.array([0, 3, 9], np.int32)
+    rows = np.array([0, 40, 41], np.int32)
+    f32 = dict(dtype=torch.float32, device="cuda")
+    po, pl = torch.randn(3, 5, 8, 128, **f32), torch.randn(3, 5, 8, **f32)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    small = torch.empty(256, dtype=torch.uint8, device="cuda")
+
+    def prefill(offs=offs, pre=pre, chk=chk, q=q, k=k, v=v, pt=pt, scale=b.scale, **o):
+        return lambda: medha.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, scale, **o)
+
+    def decode(qi=qi, kl=kl, **o):
+        return lambda: medha.decode_partial_attn(q, k, v, pt, offs, qi, kl, b.scale, **o)
+
+    def chunk(rows=rows, chk=chk, kl=kl, v0=pre + 1, **o):
+        return lambda: medha.chunk_partial_attn(q, k, v, pt, offs, rows, chk, kl, v0, b.scale, **o)
+
+    def append(offs=offs, pre=pre, chk=chk, new=new):
+        def run():
+            kk, vv = k.clone(), v.clone()
+            medha.kv_append(new, new, kk, vv, pt, offs, pre, chk)
+            return kk, vv
+        return run
+
+    def given(shape, **bad):
+        return dict(out=torch.empty(shape + (8, 128), **dict(f32, **bad)),
+                    lse=torch.empty(shape + (8,), **f32))
+
+    calls = [prefill(), decode(), chunk(), append(), lambda: medha.lse_merge(po, pl)]
+    for form in _forms(offs):
+        calls += [prefill(offs=form), append(offs=form)]
+    for form in _forms(pre):
+        calls += [prefill(pre=form), append(pre=form)]
+    for form in _forms(chk):
+        calls += [prefill(chk=form), chunk(chk=form), append(chk=form)]
+    for form in _forms(kl):
+        calls += [decode(kl=form), chunk(kl=form)]
+    for s in (1, 0, np.float32(0.1), np.float64(-0.3), torch.tensor(0.2)):
+        calls.append(prefill(scale=s))
+    for w in (ws, small, None):
+        calls += [prefill(workspace=w), decode(workspace=w), chunk(workspace=w),
+                  prefill(workspace=w, **given((tokens,))), decode(workspace=w, **given((3,))),
+                  chunk(workspace=w, **given((tokens,)))]
+    calls.append(lambda: medha.lse_merge(po, pl, **given((5,))))
+    # refused, by the binding or by the library
+    calls += [prefill(q=q.float()), prefill(q=q[:, ::2]), prefill(q=q[:-1]), prefill(k=k[:-1]),
+              prefill(k=k.float()), prefill(k=k.reshape(-1)), prefill(pt=pt.long()),
+              prefill(pt=pt[:-1]), prefill(pt=pt.cpu()), prefill(offs=offs[:-1]),
+              prefill(pre=pre[:-1]), prefill(pre=-pre - 1), prefill(pre="x"), prefill(pre=None),
+              prefill(scale=float("nan")), prefill(scale="x"), prefill(scale=None),
+              prefill(**given((tokens + 1,))), prefill(**given((tokens,), dtype=torch.float64)),
+              decode(qi=qi + 1000), decode(kl=-kl), decode(**given((2,))), chunk(rows=rows + 1000),
+              chunk(v0=pre[:-1]), append(new=new[:-1]), append(new=new.float()),
+              lambda: medha.lse_merge(po, pl[:-1]), lambda: medha.lse_merge(po.half(), pl),
+              lambda: medha.lse_merge(po[..., :6].contiguous(), pl)]
+    refused = 0
+    for i, call in enumerate(calls):
+        native = _outcome(call)
+        with monkeypatch.context() as m:
+            m.setattr(binding, "_NATIVE", _Nothing())
+            plain = _outcome(call)
+        print(f"call {i}", flush=True)
+        _same(native, plain)
+        refused += isinstance(native, tuple) and isinstance(native[0], type)
+    assert refused >= 28
+    # the module makes the ordinary calls itself, and hands back the caller's outputs
+    n = binding._NATIVE
+    out, lse = given((tokens,)).values()
+    r = n.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, b.scale, out, lse, None)
+    assert r[0] is out and r[1] is lse
+    assert n.kv_append(new, new, k, v, pt, offs, pre, chk) is True
+    assert n.lse_merge(po, pl, None, None) is not None
+    assert n.chunked_prefill_attn(q, k, v, pt, offs, pre.tolist(), chk, b.scale, None, None, None) is None
