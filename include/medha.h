@@ -259,9 +259,10 @@ int medha_kv_append(const void* k_new, const void* v_new, const medha_kv_cache* 
  * mode works on: the sequence (its place in the batch), KV head, KV range and row
  * tile; it returns 1, or 0 for an idle padding slot (only the sequence is set).
  * medha_describe_slot knows the sizes of one sequence only (0 <= slot < n_slots) and
- * gives the order of sequences whose row tiles walk about the same number of keys:
- * all key-split ones and row-split ones with a long prefix.  Prompts and first
- * chunks are handed out in another order.  These calls exist for tests and tuning;
+ * gives the order of a launch's first sequence if its row tiles walk about the same
+ * number of keys: key-split ones and row-split ones with a long prefix.  Later sequences
+ * count the dies from another one; prompts and first chunks are handed out in another
+ * order.  These calls exist for tests and tuning;
  * they launch nothing.
  */
 typedef struct medha_plan_entry {

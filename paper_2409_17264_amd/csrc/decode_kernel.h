@@ -120,8 +120,7 @@ decode_kernel(const AttnArgs args) {
   }
   const int seq = find_seq_slot(descs, args.n_seq, blockIdx.x);
   const SeqDesc sd = uniform(descs[seq]);
-  // one row tile per sequence here, so a slot is just (KV head, split)
-  const SlotItem it = decode_slot(blockIdx.x - sd.work_start, args.h_kv, sd.n_split, 1);
+  const SlotItem it = key_split_item(sd, blockIdx.x - sd.work_start, args.h_kv);
   if (!it.valid) return;
   const int kv_head = it.kv_head, split = it.split;
 

@@ -107,13 +107,16 @@ hipError_t launch_plan(const LaunchPlan& lp, bool split_keys, int d, AttnArgs& a
     if (grid <= 0) continue;
     hipError_t e;
     if (split_keys) {
-      // short walks: the small ring, two workgroups per compute unit (see decode_kernel)
-      int64_t steps = 0;
-      for (int i = 0; i < n; ++i)
+      // short walks: the small ring, two workgroups per compute unit (see decode_kernel), unless
+      // there is no second one (8 decodes of 2000 at 8/1 heads 20.4 -> 18.2 us a pass)
+      int64_t steps = 0, workgroups = 0;
+      for (int i = 0; i < n; ++i) {
+        workgroups += (int64_t)a.h_kv * a.inline_descs[i].n_split;
         steps = std::max<int64_t>(steps, std::min<int64_t>(
             a.inline_descs[i].tiles_per_split,
             ceil_div(a.inline_descs[i].kv_len, lp.shape.tile_keys)));
-      if (steps <= kShortWalkTiles)
+      }
+      if (steps <= kShortWalkTiles && workgroups > lp.num_cus)
         e = d == 128 ? launch_decode<128, 1>(a, grid, stream) : launch_decode<64, 1>(a, grid, stream);
       else
         e = d == 128 ? launch_decode<128, 2>(a, grid, stream) : launch_decode<64, 2>(a, grid, stream);
@@ -501,7 +504,7 @@ int medha_describe_plan_slot(const int32_t* prefix_len, const int32_t* chunk_len
   const bool last = i + 1 == lp.descs.size() || (i + 1) % kMaxInlineSeq == 0;  // of its launch
   const int u = slot - sd.work_start;
   const SlotItem it = mode == 0 ? row_split_item(sd, u, num_kv_heads, last)
-                                : decode_slot(u, num_kv_heads, sd.n_split, 1);
+                                : key_split_item(sd, u, num_kv_heads);
   if (seq) *seq = lp.seq_index[i];
   if (it.valid) {
     if (kv_head) *kv_head = it.kv_head;

@@ -24,6 +24,7 @@ struct LaunchPlan {
   bool paired = false;  // two workgroups to a compute unit, with the short ring (head dim 128)
   int n_slots = 0;    // grid size
   int total_rows = 0; // token rows of the launch
+  int num_cus = 0;    // compute units planned for
   bool any_split = false;
 };
 
@@ -38,8 +39,9 @@ struct Plan {
   // depends on the sizes alone
   int64_t min_part_rows = 0;
   size_t min_bytes = 0;
+  size_t reserve_bytes = 0;  // what the choice of fine ranges for the key-split launch asks for
   // what callers are told to bring
-  size_t workspace_bytes() const { return std::max(bytes, min_bytes); }
+  size_t workspace_bytes() const { return std::max({bytes, min_bytes, reserve_bytes}); }
 };
 
 struct SeqInput {
@@ -233,14 +235,17 @@ inline LaunchWalks launch_walks(const LaunchPlan& lp, int h_kv, int gqa) {
 // Workgroups and partial token rows of a launch split by `steps`.
 struct SplitSize {
   int64_t slots, part_rows;
+  int64_t items;  // slots that are not idle
 };
 
 inline SplitSize split_size(const LaunchPlan& lp, int h_kv, int64_t steps, int min_tiles) {
-  SplitSize s{0, 0};
+  SplitSize s{0, 0, 0};
   int64_t n_split, tps;
   for (const SeqDesc& sd : lp.descs) {
     split_by_steps(sd, lp.shape.tile_keys, steps, min_tiles, n_split, tps);
-    s.slots += kXcds * ceil_div((int64_t)h_kv * sd.n_row_tiles * n_split, kXcds);
+    const int64_t items = (int64_t)h_kv * sd.n_row_tiles * n_split;
+    s.items += items;
+    s.slots += kXcds * ceil_div(items, kXcds);
     if (n_split > 1) s.part_rows += n_split * sd.chunk_len;
   }
   return s;
@@ -412,8 +417,9 @@ inline void plan_launch(LaunchPlan& lp, int h_kv, int gqa, int64_t steps, int mi
     lp.descs.swap(descs);
     lp.seq_index.swap(index);
   }
-  int slot = 0, rank = 0;
+  int slot = 0, rank = 0, die = 0;
   for (SeqDesc& sd : lp.descs) {
+    sd.first_die = (int16_t)die;
     sd.work_start = slot;
     sd.row_rank = rank;
     sd.part_row = 0;
@@ -424,6 +430,7 @@ inline void plan_launch(LaunchPlan& lp, int h_kv, int gqa, int64_t steps, int mi
     }
     const int64_t items = (int64_t)h_kv * sd.n_split * sd.n_row_tiles;
     slot += (int)(kXcds * ceil_div(items, kXcds));
+    die = (int)((die + items) % kXcds);
     rank += sd.chunk_len;
   }
   lp.n_slots = slot;
@@ -472,6 +479,7 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
     lp.seq_index.push_back(b);
     if (n_rows > 32) max_rows = std::max(max_rows, (int)std::min<int64_t>(n_rows, 1 << 30));
   }
+  plan.rows.num_cus = plan.keys.num_cus = num_cus;
   // Row-split mode: 4 wavefronts x (32 * q_blocks) rows, 64-key tiles.
   plan.rows.q_blocks = max_rows >= 256 ? 2 : 1;
   plan.rows.shape = ModeShape{kWaves * 32 * plan.rows.q_blocks, 64};
@@ -480,19 +488,42 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
   plan.keys.shape = ModeShape{32, 32 * kWaves};
   constexpr int kMinTiles = 4;
   const int64_t row_bytes = (int64_t)h_q * (head_dim + 1) * sizeof(float);
-  int64_t keys_steps = 1, rows_steps = 1, min_rows = 0;
-  if (!plan.keys.descs.empty()) {
-    keys_steps = simple_steps(plan.keys, h_kv, gqa, num_cus * 8);
-    min_rows += split_size(plan.keys, h_kv, keys_steps, kMinTiles).part_rows;
-  }
+  int64_t keys_steps = 1, rows_steps = 1, keys_rows = 0, min_rows = 0, reserve_rows = 0;
+  int keys_min_tiles = kMinTiles;
   if (!plan.rows.descs.empty()) {
     rows_steps = simple_steps(plan.rows, h_kv, gqa, num_cus);
-    const int64_t keys_rows = min_rows;
-    min_rows += split_size(plan.rows, h_kv, rows_steps, kMinTiles).part_rows;
-    // token rows of partials that fit the budget (the workspace's two arrays are rounded up to
-    // 256 bytes each, which can cost the last rows)
-    int64_t fit = (int64_t)(std::min<size_t>(budget, (size_t)1 << 60) / row_bytes);
-    while (fit > 0 && partial_bytes(fit, h_q, head_dim) > budget) --fit;
+    min_rows = split_size(plan.rows, h_kv, rows_steps, kMinTiles).part_rows;
+  }
+  // token rows of partials that fit the budget (the workspace's two arrays are rounded up to
+  // 256 bytes each, which can cost the last rows)
+  int64_t fit = (int64_t)(std::min<size_t>(budget, (size_t)1 << 60) / row_bytes);
+  while (fit > 0 && partial_bytes(fit, h_q, head_dim) > budget) --fit;
+  if (!plan.keys.descs.empty()) {
+    keys_steps = simple_steps(plan.keys, h_kv, gqa, num_cus * 8);
+    const SplitSize simple = split_size(plan.keys, h_kv, keys_steps, kMinTiles);
+    const int64_t rows_min = min_rows;
+    min_rows += simple.part_rows;
+    keys_rows = simple.part_rows;
+    // A launch that leaves compute units idle at ranges of 4 tiles, and is merged anyway, takes the
+    // shortest ranges that find a unit each: a walk is a chain of trips to HBM, 1.2 us a tile.  (One
+    // decode of 2048 at 32/8 heads 14.4 -> 13.6 us a pass, of 8000 19.8 -> 14.8, 8 of 2000 at 8/1
+    // heads 20.4 -> 15.5, 100 of 1000 (two launches) 47.4 -> 42.3.  With more ranges than units
+    // 8 of 2000 at 32/8 heads take 30.9 -> 34.6, one of 300, which needs no merge, 10.6 -> 13.7.)
+    const int64_t launches = ceil_div((int64_t)plan.keys.descs.size(), kMaxInlineSeq);
+    if (simple.part_rows > 0 && simple.items < num_cus * launches)
+      for (int steps = 1; steps < kMinTiles; ++steps) {
+        const SplitSize fine = split_size(plan.keys, h_kv, steps, steps);
+        if (fine.items > num_cus * launches) continue;
+        if (fine.part_rows + rows_min <= fit) {
+          keys_steps = steps;
+          keys_min_tiles = steps;
+          keys_rows = fine.part_rows;
+          reserve_rows = fine.part_rows + rows_min;
+        }
+        break;
+      }
+  }
+  if (!plan.rows.descs.empty()) {
     if ((int)plan.rows.descs.size() <= kMaxPlannedSeqs) {
       double us, small_us;
       rows_steps = choose_steps(plan.rows, launch_walks(plan.rows, h_kv, gqa), h_kv, num_cus,
@@ -552,12 +583,13 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
   if (!plan.rows.descs.empty())
     plan_launch(plan.rows, h_kv, gqa, rows_steps, kMinTiles, plan.part_rows);
   if (!plan.keys.descs.empty())
-    plan_launch(plan.keys, h_kv, gqa, keys_steps, kMinTiles, plan.part_rows);
+    plan_launch(plan.keys, h_kv, gqa, keys_steps, keys_min_tiles, plan.part_rows);
 
   plan.off_part_o = 0;
   plan.off_part_lse = partial_o_bytes(plan.part_rows, h_q, head_dim);
   plan.bytes = partial_bytes(plan.part_rows, h_q, head_dim);
   plan.min_bytes = partial_bytes(min_rows, h_q, head_dim);
+  plan.reserve_bytes = partial_bytes(reserve_rows, h_q, head_dim);
   plan.min_part_rows = min_rows;
   return plan;
 }

@@ -587,7 +587,8 @@ __device__ __forceinline__ SeqDesc uniform(const SeqDesc& d) {
   u.part_row = __builtin_amdgcn_readfirstlane(d.part_row);
   u.row_rank = __builtin_amdgcn_readfirstlane(d.row_rank);
   u.kv_len = __builtin_amdgcn_readfirstlane(d.kv_len);
-  u.dealt = __builtin_amdgcn_readfirstlane(d.dealt);
+  u.dealt = (int16_t)__builtin_amdgcn_readfirstlane(d.dealt);
+  u.first_die = (int16_t)__builtin_amdgcn_readfirstlane(d.first_die);
   return u;
 }
 

@@ -600,6 +600,28 @@ def test_small_workgroups_behind_a_prefix(h_q, h_kv, d, prefix, chunk, n_split, 
     check(out, lse, ro, rl, f"small workgroups hq{h_q} hkv{h_kv} d{d} P{prefix} c{chunk}")
 
 
+# ------------------------------------------------------------ decodes that leave the device idle
+@pytest.mark.parametrize("h_q,h_kv,d,lens", [
+    (32, 8, 128, [2048]),                                    # ranges of one tile, the last one full
+    (32, 8, 128, [8000]),                                    # of two
+    (8, 1, 128, [130, 1023, 700, 4100, 1, 2049, 512, 513]),  # many dies' first items, uncut ones too
+    (8, 2, 64, [413, 60, 1500, 128, 129, 990, 31]),
+    (2, 1, 64, [500 + 7 * i for i in range(70)]),            # two launches
+])
+def test_decodes_in_short_ranges(h_q, h_kv, d, lens):
+    """Batches of decodes too small to fill the device at ranges of 4 tiles are cut finer, and their
+    sequences' workgroups start at another die each."""
+    prefix, chunk = [n - 1 for n in lens], [1] * len(lens)
+    entries = medha.describe_plan(prefix, chunk, h_q, h_kv, d, 256)[0]
+    longest = max(entries, key=lambda e: e.n_split)
+    assert longest.n_split > 1 and min(e.tiles_per_split for e in entries) < 4
+    b = wl.make_prefill_batch("short ranges", h_q, h_kv, d, prefix, chunk, seed=sum(lens),
+                              poison_unused=True)
+    ro, rl = oracle_prefill(b)
+    out, lse = gpu_prefill(to_dev(b))
+    check(out, lse, ro, rl, f"decodes hq{h_q} hkv{h_kv} d{d} {lens[:4]}")
+
+
 # ------------------------------------------------------------ softmax scale values
 @pytest.mark.parametrize("d,prefix", [(128, 64 * 20 + 7), (128, 64 * 23), (64, 64 * 22 - 1)])
 def test_walks_that_end_around_the_exact_route_warm_up(d, prefix):

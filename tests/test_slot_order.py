@@ -5,6 +5,8 @@ import subprocess
 
 import pytest
 
+import paper_2409_17264_amd as medha
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIPCC = "/opt/rocm/bin/hipcc"
 
@@ -56,3 +58,21 @@ def test_dealt_slots_cover_every_item_once_and_evenly(tmp_path):
     assert res.returncode == 0, res.stderr[-3000:]
     run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0 and "ok" in run.stdout, run.stdout + run.stderr
+
+
+@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,mode", [
+    ([900 + 31 * i for i in range(40)], [1] * 40, 8, 1, 1),      # one to four ranges of one head
+    ([300 * (1 + i % 5) for i in range(33)], [1] * 33, 8, 2, 1),
+    ([0] * 12, [90 + 16 * i for i in range(12)], 8, 1, 0),       # prompts of 3 to 9 row tiles
+])
+def test_sequences_of_few_items_are_spread_over_the_dies(prefix, chunk, h_q, h_kv, mode):
+    entries, grid_rows, grid_keys, _ = medha.describe_plan(prefix, chunk, h_q, h_kv, 128, 256)
+    items, dies = 0, [0] * 8
+    for s in range(grid_keys if mode else grid_rows):
+        it = medha.describe_plan_slot(prefix, chunk, h_q, h_kv, 128, 256, mode, s)
+        if it is not None:
+            items += 1
+            dies[s % 8] += 1
+    assert items == sum(h_kv * e.n_split * e.n_row_tiles for e in entries)
+    # equal runs of a sequence differ by one item, and those of more than 8 items by their last run
+    assert max(dies) <= items / 8 + len(entries) / 2 + 1, dies
