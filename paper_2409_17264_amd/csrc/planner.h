@@ -503,7 +503,14 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
     const SplitSize simple = split_size(plan.keys, h_kv, keys_steps, kMinTiles);
     const int64_t rows_min = min_rows;
     min_rows += simple.part_rows;
-    keys_rows = simple.part_rows;
+    // About 8 workgroups a compute unit are what a call has to bring scratch for.  Walks of 6 to 24
+    // tiles are cut into about 6: a workgroup's start and end weigh more than a finer last round (64
+    // decodes of 2K median, 32/8 heads, 116.7 -> 114.2 us a pass, at d 64 72.5 -> 70.8; 1M in 8 shards,
+    // 8/1 heads, 99.9 -> 98.9).  Ranges of 5 instead of 4 tiles are 1 to 2
+    // % longer (24 decodes of 4K, 32/8 heads, 87.2 -> 88.9); long walks fill their rounds with 8.
+    const int64_t six = simple_steps(plan.keys, h_kv, gqa, num_cus * 6);
+    if (six >= 6 && six <= kShortWalkTiles) keys_steps = six;
+    keys_rows = split_size(plan.keys, h_kv, keys_steps, kMinTiles).part_rows;
     // A launch that leaves compute units idle at ranges of 4 tiles, and is merged anyway, takes the
     // shortest ranges that find a unit each: a walk is a chain of trips to HBM, 1.2 us a tile.  (One
     // decode of 2048 at 32/8 heads 14.4 -> 13.6 us a pass, of 8000 19.8 -> 14.8, 8 of 2000 at 8/1
