@@ -79,7 +79,6 @@ __device__ __forceinline__ void issue_block(const AttnArgs& args, int page0, int
 // cache a sequence's K/V is gone before the next one reads it, shared or not.  (32/8 heads,
 // d 128: 64 decodes that share 8K keys, 161 us loaded non-temporally, 115 us through the caches;
 // 16 that share 32K, 253 and 165; 4 that share 128K, 537 MB each, 329 and 358.)
-constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;
 
 // `other_*`: of the sequence this lane looks at.
 template <int D>

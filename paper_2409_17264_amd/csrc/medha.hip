@@ -76,9 +76,23 @@ hipError_t launch_decode(const AttnArgs& a, int grid, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// A stream that one workgroup alone reads and that no cache can keep for the next call is loaded
+// with the non-temporal hint: one sequence, one row tile, K/V of one and a half times the last-level
+// cache or more (8/1 heads, d 128: 32 tokens at 1M, 537 MB, 155.1 -> 152.4 us, 16 113.7 -> 108.8; 32
+// at 500K, 8/2 heads, 109.3 -> 103.4; 60 at 700K, 8/2 heads, d 64, 358 MB, the same; 154 MB, called
+// again and again, 55.8 -> 63.0: those are still in the cache).
+bool read_once(const AttnArgs& a, int d) {
+  const SeqDesc& sd = a.inline_descs[0];
+  return a.n_seq == 1 && sd.n_row_tiles == 1 &&
+         2 * (int64_t)sd.kv_len * a.h_kv * (4 * d) > 3 * kLastLevelCacheBytes;
+}
+
 template <int D, int NW, int NV = 4>
 hipError_t launch_prefill(const AttnArgs& a, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL((prefill_kernel<D, NW, NV>), dim3(grid), dim3(NW * 64), 0, stream, a);
+  if (NV == 4 && read_once(a, D))
+    hipLaunchKernelGGL((prefill_kernel<D, NW, 4, true>), dim3(grid), dim3(NW * 64), 0, stream, a);
+  else
+    hipLaunchKernelGGL((prefill_kernel<D, NW, NV, false>), dim3(grid), dim3(NW * 64), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -47,12 +47,20 @@ struct Swz {
 // by vmcnt only.  Written by hand, like ring_barrier() below: the ring's ordering
 // is enforced by explicit counter waits, whereas the compiler, when it sees such
 // loads, drains the whole load queue before the next LDS read that might alias them.
+// kOnce: see async_stream16.
+template <bool kOnce>
 __device__ __forceinline__ void async_load16(const void* base_uniform, uint32_t lane_off,
                                              uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_addr_uniform), "v"(lane_off), "s"(base_uniform)
-               : "m0", "memory");
+  if constexpr (kOnce)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :
+                 : "s"(lds_addr_uniform), "v"(lane_off), "s"(base_uniform)
+                 : "m0", "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds_addr_uniform), "v"(lane_off), "s"(base_uniform)
+                 : "m0", "memory");
 }
 // The same with a per-lane address.  kOnce: with the non-temporal hint, for data that nobody
 // else reads soon: the stream is not allocated in the caches on its way, which is worth a tenth
@@ -145,7 +153,7 @@ struct TileLoader {
 
   // Loads K and / or V rows row0.. of tile `tile`; page = id of the page holding them (see
   // tile_page()), k_stage / v_stage = LDS addresses of the tile's places in the ring.
-  template <bool K, bool V>
+  template <bool K, bool V, bool kOnce>
   __device__ __forceinline__ void issue(const AttnArgs& args, int page, int tile, int kv_total,
                                         int kv_head, uint32_t k_stage, uint32_t v_stage) const {
     const int64_t page_off = ((int64_t)page * args.h_kv + kv_head) * (kPageSize * D * 2);
@@ -155,8 +163,8 @@ struct TileLoader {
 #pragma unroll
       for (int j = 0; j < G::kInstrPerWave; ++j) {
         const uint32_t lds_off = (row0 + j * G::kRowsPerInstr) * (D * 2);  // wave-uniform
-        if (K) async_load16(kp, k_off[j], k_stage + lds_off);
-        if (V) async_load16(vp, v_off[j], v_stage + lds_off);
+        if (K) async_load16<kOnce>(kp, k_off[j], k_stage + lds_off);
+        if (V) async_load16<kOnce>(vp, v_off[j], v_stage + lds_off);
       }
     } else {
       // last, ragged tile: keys past the end are clamped to the last one (masked, but finite)
@@ -166,11 +174,11 @@ struct TileLoader {
         const int t = min(tile * G::kTileKeys + row, kv_total - 1);
         const uint32_t lds_off = (row0 + j * G::kRowsPerInstr) * (D * 2);
         if (K)
-          async_load16(kp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::k(row, pos) * 16),
-                       k_stage + lds_off);
+          async_load16<kOnce>(kp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::k(row, pos) * 16),
+                              k_stage + lds_off);
         if (V)
-          async_load16(vp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::v(row, pos) * 16),
-                       v_stage + lds_off);
+          async_load16<kOnce>(vp, (uint32_t)((t & 15) * (D * 2) + Swz<D>::v(row, pos) * 16),
+                              v_stage + lds_off);
       }
     }
   }
@@ -656,7 +664,7 @@ __device__ __forceinline__ void forget(T (&x)[N]) {
 // compile-time, so the change-over happens between rounds of 4 (6) tiles: up to 3 (5) fully
 // visible tiles take the masked form, which costs each about a fifth more; draining the ring
 // and filling it again at the exact tile (as two walks) costs 3 to 4 tiles' time.
-template <int D, int NW, int NV>
+template <int D, int NW, int NV, bool kOnce>
 __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args, ConstI32Ptr pt,
                                           int kt_a, int kt_mid, int kt_b, int kv_total,
                                           int kv_head, const Ring& ring,
@@ -686,12 +694,12 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
     const uint32_t k_lds = ring.lds_addr + decltype(k_stage)::value * kTile;
     const uint32_t v_lds = ring.lds_addr + (R::kK + decltype(v_stage)::value) * kTile;
     if constexpr (R::kLag == 0) {
-      ld.template issue<true, true>(args, page_next, min(tile, last), kv_total, kv_head, k_lds, v_lds);
+      ld.template issue<true, true, kOnce>(args, page_next, min(tile, last), kv_total, kv_head, k_lds, v_lds);
     } else {
       if constexpr (decltype(v_stage)::value >= 0)
-        ld.template issue<false, true>(args, page_2, min(tile - R::kLag, last), kv_total, kv_head, 0,
+        ld.template issue<false, true, kOnce>(args, page_2, min(tile - R::kLag, last), kv_total, kv_head, 0,
                                        v_lds);
-      ld.template issue<true, false>(args, page_next, min(tile, last), kv_total, kv_head, k_lds, 0);
+      ld.template issue<true, false, kOnce>(args, page_next, min(tile, last), kv_total, kv_head, k_lds, 0);
     }
   };
   // loads of the iteration before that its successor's barrier leaves in flight
@@ -785,7 +793,7 @@ __device__ __forceinline__ void run_tiles(RowBlock<D>& rb, const AttnArgs& args,
 
 // (the launch bound is 512 also for the 4-wavefront variant: it makes the compiler budget
 // for two wavefronts per SIMD, at most 256 vector registers, all architectural)
-template <int D, int NW, int NV>
+template <int D, int NW, int NV, bool kOnce>
 __global__ void __launch_bounds__(512) prefill_kernel(const AttnArgs args) {
   using Shape = PrefillShape<D, NW, NV>;
   __shared__ __attribute__((aligned(1024))) char lds[Shape::kLdsBytes];
@@ -844,7 +852,7 @@ __global__ void __launch_bounds__(512) prefill_kernel(const AttnArgs args) {
   ConstI32Ptr pt = (ConstI32Ptr)(args.page_table + sd.pt_off);
   TileLoader<D, NW> loader;
   loader.init(wave, lane);
-  run_tiles<D, NW, NV>(rb, args, pt, kt_begin, kt_mid, kt_end, kv_total, kv_head, stages, loader,
+  run_tiles<D, NW, NV, kOnce>(rb, args, pt, kt_begin, kt_mid, kt_end, kv_total, kv_head, stages, loader,
                        wave, lane);
 
   const bool direct = sd.n_split == 1;

@@ -511,6 +511,20 @@ def test_small_chunk_long_prefix_many_way_split(h_q, h_kv, d, prefix, chunk):
     check(out, lse, ro, rl, f"small chunk hq{h_q} d{d} P{prefix} c{chunk} split{e[0].n_split}")
 
 
+@pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk", [(8, 2, 128, 400_001, 32), (32, 8, 64, 200_003, 64),
+                                                     (32, 8, 64, 200_003, 31)])
+def test_streams_too_long_for_the_caches(h_q, h_kv, d, prefix, chunk):
+    """One row tile against 410 MB of K/V: the tile loads with the non-temporal hint (at head dim
+    128 and 256 rows, one GPU's share of the 70B-sized layer at 32 tokens takes them too)."""
+    b = wl.make_prefill_batch("once", h_q, h_kv, d, [prefix], [chunk], 3 * chunk + d, "cuda")
+    e, _, _, _ = medha.describe_plan(b.prefix_len, b.chunk_len, h_q, h_kv, d, 256)
+    assert e[0].n_row_tiles == 1 and prefix * h_kv * 4 * d > 3 * (128 << 20)
+    rows = np.array([0, chunk // 2, chunk - 1], np.int64)
+    ro, rl = oracle_prefill(b, rows)
+    out, lse = gpu_prefill(b)
+    check(out[rows], lse[rows], ro, rl, f"long stream hq{h_q} hkv{h_kv} d{d} P{prefix} c{chunk}")
+
+
 # ------------------------------------------------------------ plans and the workspace at hand
 def test_plan_keeps_to_the_workspace_it_is_given():
     """54 row tiles: the fastest plan has 9 KV ranges, the least a call has to bring is 5 ranges'
