@@ -9,7 +9,7 @@
 // online-softmax state, and the four states are combined through LDS at the end.
 //
 // Each wavefront streams its blocks HBM -> LDS with asynchronous 16-byte loads
-// into a private two-stage ring (no workgroup barrier in the loop, so the four
+// into a private ring of one or two stages (no workgroup barrier in the loop, so the four
 // streams run decoupled and up to 128 KiB of loads are in flight per compute
 // unit).  The arithmetic per block is the prefill kernel's: S^T = K Q^T and
 // O^T += V^T P^T on the matrix cores with only `rows` of the 32 columns live,
@@ -98,7 +98,8 @@ __device__ __forceinline__ bool read_by_others(const AttnArgs& args, const SeqDe
 // STAGES = blocks in flight per wavefront.  2 (128 KiB of LDS, one workgroup per compute unit)
 // suits long walks; 1 (64 KiB, two workgroups per compute unit, so that one's start-up --
 // descriptor, page ids, the first blocks' trip to HBM -- and its final combine hide behind
-// the other's stream) suits launches whose workgroups walk only a few blocks each.
+// the other's stream) suits launches whose workgroups walk only a few blocks each and are more
+// than the compute units.
 // (launched with 256 threads; the bound of 512 makes the compiler budget for two wavefronts
 // per SIMD, i.e. at most 256 vector registers, all architectural: with more it parks the
 // accumulators in AGPRs and copies them back and forth around every vector-ALU use)
