@@ -155,7 +155,14 @@ def _stream() -> int:
     return _raw_stream(torch.cuda.current_device())
 
 
+def _reachable(t: torch.Tensor) -> bool:
+    """Whether the kernels can reach a tensor's memory, if it has any: the device's, or pinned
+    host memory."""
+    return t.is_cuda or t.numel() == 0 or t.is_pinned()
+
+
 def _kv(k_pool: torch.Tensor, v_pool: torch.Tensor) -> _KvCache:
+    assert _reachable(k_pool) and _reachable(v_pool)
     assert k_pool.dtype == torch.bfloat16 and v_pool.dtype == torch.bfloat16
     assert k_pool.is_contiguous() and v_pool.is_contiguous() and k_pool.shape == v_pool.shape
     num_pages, h_kv, page_size, d = k_pool.shape
@@ -219,6 +226,17 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
+def _check_output(t: torch.Tensor, shape) -> None:
+    assert _reachable(t) and t.dtype == torch.float32 and t.is_contiguous() and t.shape == shape
+
+
+def _check_workspace(t: torch.Tensor) -> None:
+    # dense, in whatever order: the library writes numel() bytes from the first element on
+    assert _reachable(t)
+    assert t.is_contiguous() or t.permute(
+        sorted(range(t.dim()), key=t.stride, reverse=True)).is_contiguous()
+
+
 def chunked_prefill_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Tensor,
                          page_table: torch.Tensor, page_table_offs, prefix_len, chunk_len,
                          softmax_scale: float, out: Optional[torch.Tensor] = None,
@@ -236,6 +254,7 @@ def chunked_prefill_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Te
     assert page_table.is_cuda and page_table.dtype == torch.int32 and page_table.is_contiguous()
     tokens, h_q, d = q.shape
     kv = _kv(k_pool, v_pool)
+    assert d == kv.head_dim
     offs = _host(page_table_offs, np.int64)
     pre, chk = _host(prefix_len, np.int32), _host(chunk_len, np.int32)
     batch = len(pre)
@@ -245,11 +264,12 @@ def chunked_prefill_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Te
         out = torch.empty((tokens, h_q, d), dtype=torch.float32, device=q.device)
     if lse is None:
         lse = torch.empty((tokens, h_q), dtype=torch.float32, device=q.device)
-    assert out.dtype == torch.float32 and out.is_contiguous() and out.shape == (tokens, h_q, d)
-    assert lse.dtype == torch.float32 and lse.is_contiguous() and lse.shape == (tokens, h_q)
+    _check_output(out, (tokens, h_q, d))
+    _check_output(lse, (tokens, h_q))
     if workspace is None:
         workspace = _workspace(lib.medha_chunked_prefill_workspace_bytes(
             _hp(pre), _hp(chk), batch, h_q, kv.num_kv_heads, d), q.device)
+    _check_workspace(workspace)
     _check(lib.medha_chunked_prefill_attn(
         _dp(q), ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(pre), _hp(chk), batch, h_q,
         float(softmax_scale), _dp(out), _dp(lse), _dp(workspace), workspace.numel(), _stream()))
@@ -269,13 +289,14 @@ def chunked_prefill_attn_noalloc(q: torch.Tensor, k_pool: torch.Tensor, v_pool: 
     assert page_table.is_cuda and page_table.dtype == torch.int32 and page_table.is_contiguous()
     tokens, h_q, d = q.shape
     kv = _kv(k_pool, v_pool)
+    assert d == kv.head_dim
     offs = _host(page_table_offs, np.int64)
     pre, chk = _host(prefix_len, np.int32), _host(chunk_len, np.int32)
     batch = len(pre)
     assert len(chk) == batch and len(offs) == batch + 1 and _total(chk) == tokens
     assert int(offs[-1]) <= page_table.numel()
-    assert out.dtype == torch.float32 and out.is_contiguous() and out.shape == (tokens, h_q, d)
-    assert lse.dtype == torch.float32 and lse.is_contiguous() and lse.shape == (tokens, h_q)
+    _check_output(out, (tokens, h_q, d))
+    _check_output(lse, (tokens, h_q))
     _check(lib.medha_chunked_prefill_attn_noalloc(
         _dp(q), ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(pre), _hp(chk), batch, h_q,
         float(softmax_scale), _dp(out), _dp(lse), _stream()))
@@ -298,6 +319,7 @@ def decode_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Ten
     assert page_table.is_cuda and page_table.dtype == torch.int32 and page_table.is_contiguous()
     num_queries, h_q, d = q.shape
     kv = _kv(k_pool, v_pool)
+    assert d == kv.head_dim
     offs = _host(page_table_offs, np.int64)
     qi, kl = _host(q_index, np.int32), _host(kv_len, np.int32)
     items = len(qi)
@@ -307,12 +329,12 @@ def decode_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Ten
         out_partial = torch.empty((items, h_q, d), dtype=torch.float32, device=q.device)
     if lse_partial is None:
         lse_partial = torch.empty((items, h_q), dtype=torch.float32, device=q.device)
-    assert out_partial.dtype == torch.float32 and out_partial.is_contiguous()
-    assert lse_partial.dtype == torch.float32 and lse_partial.is_contiguous()
-    assert out_partial.shape == (items, h_q, d) and lse_partial.shape == (items, h_q)
+    _check_output(out_partial, (items, h_q, d))
+    _check_output(lse_partial, (items, h_q))
     if workspace is None:
         workspace = _workspace(lib.medha_decode_partial_workspace_bytes(
             _hp(kl), items, h_q, kv.num_kv_heads, d), q.device)
+    _check_workspace(workspace)
     _check(lib.medha_decode_partial_attn(
         _dp(q), num_queries, ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(qi), _hp(kl), items,
         h_q, float(softmax_scale), _dp(out_partial), _dp(lse_partial), _dp(workspace),
@@ -346,6 +368,7 @@ def chunk_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Tens
     assert page_table.is_cuda and page_table.dtype == torch.int32 and page_table.is_contiguous()
     tokens, h_q, d = q.shape
     kv = _kv(k_pool, v_pool)
+    assert d == kv.head_dim
     offs = _host(page_table_offs, np.int64)
     qr, chk = _host(q_row, np.int32), _host(chunk_len, np.int32)
     kl, v0 = _host(kv_len, np.int32), _host(visible0, np.int32)
@@ -357,12 +380,12 @@ def chunk_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Tens
         out_partial = torch.empty((rows, h_q, d), dtype=torch.float32, device=q.device)
     if lse_partial is None:
         lse_partial = torch.empty((rows, h_q), dtype=torch.float32, device=q.device)
-    assert out_partial.dtype == torch.float32 and out_partial.is_contiguous()
-    assert lse_partial.dtype == torch.float32 and lse_partial.is_contiguous()
-    assert out_partial.shape == (rows, h_q, d) and lse_partial.shape == (rows, h_q)
+    _check_output(out_partial, (rows, h_q, d))
+    _check_output(lse_partial, (rows, h_q))
     if workspace is None:
         workspace = _workspace(lib.medha_chunk_partial_workspace_bytes(
             _hp(chk), _hp(kl), items, h_q, kv.num_kv_heads, d), q.device)
+    _check_workspace(workspace)
     _check(lib.medha_chunk_partial_attn(
         _dp(q), tokens, ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(qr), _hp(chk), _hp(kl),
         _hp(v0), items, h_q, float(softmax_scale), _dp(out_partial), _dp(lse_partial),
@@ -378,7 +401,7 @@ def lse_merge(out_partial: torch.Tensor, lse_partial: torch.Tensor,
     if done is not None:
         return done
     assert out_partial.is_cuda and out_partial.dtype == torch.float32
-    assert lse_partial.dtype == torch.float32
+    assert _reachable(lse_partial) and lse_partial.dtype == torch.float32
     assert out_partial.is_contiguous() and lse_partial.is_contiguous() and out_partial.dim() == 4
     s, rows, h_q, d = out_partial.shape
     assert lse_partial.shape == (s, rows, h_q)
@@ -386,8 +409,8 @@ def lse_merge(out_partial: torch.Tensor, lse_partial: torch.Tensor,
         out = torch.empty((rows, h_q, d), dtype=torch.float32, device=out_partial.device)
     if lse is None:
         lse = torch.empty((rows, h_q), dtype=torch.float32, device=out_partial.device)
-    assert out.is_contiguous() and lse.is_contiguous()
-    assert out.shape == (rows, h_q, d) and lse.shape == (rows, h_q)
+    _check_output(out, (rows, h_q, d))
+    _check_output(lse, (rows, h_q))
     _check(lib.medha_lse_merge(_dp(out_partial), _dp(lse_partial), s, rows, h_q, d, _dp(out),
                                _dp(lse), _stream()))
     return out, lse

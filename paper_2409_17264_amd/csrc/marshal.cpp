@@ -107,6 +107,9 @@ bool pages(const at::Tensor* table, const HostArray<int64_t>& offs, int64_t n) {
          offs.size() == n + 1 && offs.data()[n] <= table->numel();
 }
 
+// A caller's workspace (of any type: its elements are counted as bytes).
+bool room(const at::Tensor* t) { return t != nullptr && t->is_cuda() && t->is_contiguous(); }
+
 // An output: the caller's tensor, checked, or a new one.
 bool output(PyObject* o, at::IntArrayRef sizes, const at::Tensor& like, at::Tensor& t) {
   if (o == Py_None) {
@@ -190,7 +193,8 @@ PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     float scale;
     void* stream;
     if (n != 11 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
-        !offs.take(a[4]) || !pre.take(a[5]) || !chk.take(a[6]) || chk.size() != pre.size() ||
+        q->size(2) != kv.head_dim || !offs.take(a[4]) || !pre.take(a[5]) || !chk.take(a[6]) ||
+        chk.size() != pre.size() ||
         !pages(table = tensor(a[3]), offs, pre.size()) || total(chk) != q->size(0) ||
         q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[7], scale))
       return nullptr;
@@ -198,7 +202,7 @@ PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!output(a[8], q->sizes(), *q, out) || !output(a[9], q->sizes().slice(0, 2), *q, lse))
       return nullptr;
     const at::Tensor* given = a[10] == Py_None ? nullptr : tensor(a[10]);
-    if ((a[10] != Py_None && given == nullptr) || !current_stream(stream)) return nullptr;
+    if ((a[10] != Py_None && !room(given)) || !current_stream(stream)) return nullptr;
     Workspace ws{{}, q->options().dtype(at::kByte)};
     const void* qp = q->data_ptr();
     const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
@@ -227,11 +231,12 @@ PyObject* decode_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     float scale;
     void* stream;
     if (n != 11 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
-        !offs.take(a[4]) || !qi.take(a[5]) || !kl.take(a[6]) || kl.size() != qi.size() ||
+        q->size(2) != kv.head_dim || !offs.take(a[4]) || !qi.take(a[5]) || !kl.take(a[6]) ||
+        kl.size() != qi.size() ||
         !pages(table = tensor(a[3]), offs, qi.size()) ||
         q->size(0) > std::numeric_limits<int32_t>::max() ||
         q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[7], scale) ||
-        (ws = tensor(a[10])) == nullptr)
+        !room(ws = tensor(a[10])))
       return nullptr;
     at::Tensor out, lse;
     const int64_t sizes[3] = {qi.size(), q->size(1), q->size(2)};
@@ -264,12 +269,12 @@ PyObject* chunk_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     float scale;
     void* stream;
     if (n != 13 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
-        !offs.take(a[4]) || !qr.take(a[5]) || !chk.take(a[6]) || !kl.take(a[7]) ||
+        q->size(2) != kv.head_dim || !offs.take(a[4]) || !qr.take(a[5]) || !chk.take(a[6]) || !kl.take(a[7]) ||
         !v0.take(a[8]) || chk.size() != qr.size() || kl.size() != qr.size() ||
         v0.size() != qr.size() || !pages(table = tensor(a[3]), offs, qr.size()) ||
         q->size(0) > std::numeric_limits<int32_t>::max() ||
         q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[9], scale) ||
-        (ws = tensor(a[12])) == nullptr)
+        !room(ws = tensor(a[12])))
       return nullptr;
     at::Tensor out, lse;
     const int64_t sizes[3] = {total(chk), q->size(1), q->size(2)};

@@ -62,6 +62,76 @@ def test_calls_without_a_device_are_refused_as_before():
                         b.page_table_offs, b.prefix_len, b.chunk_len)
 
 
+class _OnDevice(torch.Tensor):
+    """A host tensor that says it is on the device, for checks that come before any launch."""
+
+    is_cuda = property(lambda self: True)
+
+
+def _on_device(t):
+    return t.as_subclass(_OnDevice)
+
+
+@pytest.mark.parametrize("d_q,d_kv", [(64, 128), (128, 64)])
+def test_a_head_dim_that_is_not_the_caches_is_refused(monkeypatch, d_q, d_kv):
+    """The library knows the cache's head dim only: it would read past q and write past out."""
+    launched = []
+    monkeypatch.setattr(binding, "_stream", lambda: launched.append(1))
+    b = wl.make_prefill_batch("d", 2, 1, d_kv, [20], [4], seed=1)
+    q = _on_device(torch.zeros(4, 2, d_q, dtype=torch.bfloat16))
+    k, v, pt = _on_device(b.k_pool), _on_device(b.v_pool), _on_device(torch.from_numpy(b.page_table))
+    offs, pre, chk, kl = b.page_table_offs, b.prefix_len, b.chunk_len, b.prefix_len + b.chunk_len
+    out, lse = _on_device(torch.zeros(4, 2, d_q)), _on_device(torch.zeros(4, 2))
+    ws = _on_device(torch.zeros(1 << 20, dtype=torch.uint8))
+    for call in (
+            lambda: medha.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, 1.0, out, lse, ws),
+            lambda: medha.chunked_prefill_attn_noalloc(q, k, v, pt, offs, pre, chk, 1.0, out, lse),
+            lambda: medha.decode_partial_attn(q, k, v, pt, offs, [0], kl, 1.0, out[:1], lse[:1], ws),
+            lambda: medha.chunk_partial_attn(q, k, v, pt, offs, [0], chk, kl, pre + 1, 1.0, out, lse,
+                                             ws)):
+        with pytest.raises(AssertionError):
+            call()
+    assert not launched
+
+
+def test_memory_that_the_kernels_cannot_reach_is_refused(monkeypatch):
+    launched = []
+    monkeypatch.setattr(binding, "_stream", lambda: launched.append(1))
+    b = wl.make_prefill_batch("host", 2, 1, 64, [20], [4], seed=1)
+    good = dict(q=_on_device(b.q), k=_on_device(b.k_pool), v=_on_device(b.v_pool),
+                pt=_on_device(torch.from_numpy(b.page_table)),
+                out=_on_device(torch.zeros(4, 2, 64)), lse=_on_device(torch.zeros(4, 2)),
+                ws=_on_device(torch.zeros(1 << 20, dtype=torch.uint8)))
+    offs, pre, chk, kl = b.page_table_offs, b.prefix_len, b.chunk_len, b.prefix_len + b.chunk_len
+
+    def calls(q, k, v, pt, out, lse, ws):
+        yield lambda: medha.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, 1.0, out, lse, ws)
+        yield lambda: medha.decode_partial_attn(q, k, v, pt, offs, [0], kl, 1.0, out[:1], lse[:1],
+                                                ws)
+        yield lambda: medha.chunk_partial_attn(q, k, v, pt, offs, [0], chk, kl, pre + 1, 1.0, out,
+                                               lse, ws)
+
+    one = _on_device(torch.zeros(1, dtype=torch.uint8))
+    for bad in (dict(k=b.k_pool), dict(v=b.v_pool), dict(out=torch.zeros(4, 2, 64)),
+                dict(lse=torch.zeros(4, 2)), dict(ws=torch.zeros(1 << 20, dtype=torch.uint8)),
+                # one byte that says it is a megabyte, and every other byte of two
+                dict(ws=one.expand(1 << 20)), dict(ws=one.repeat(2 << 20)[::2])):
+        for call in calls(**dict(good, **bad)):
+            with pytest.raises(AssertionError):
+                call()
+    po, pl = _on_device(torch.zeros(2, 4, 2, 64)), _on_device(torch.zeros(2, 4, 2))
+    with pytest.raises(AssertionError):
+        medha.lse_merge(po, torch.zeros(2, 4, 2))
+    for out, lse in ((torch.zeros(4, 2, 64), good["lse"]), (good["out"], torch.zeros(4, 2)),
+                     (good["out"].bfloat16(), good["lse"])):
+        with pytest.raises(AssertionError):
+            medha.lse_merge(po, pl, out, lse)
+    assert not launched
+    # dense in another order, or nothing at all, is a workspace
+    binding._check_workspace(_on_device(torch.zeros(64, 32, dtype=torch.uint8)).t())
+    binding._check_workspace(torch.zeros(0, dtype=torch.uint8))
+
+
 @pytest.mark.gpu
 def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
     b = wl.make_prefill_batch("marshal", 8, 2, 128, [1500, 70, 0], [40, 1, 130], seed=11)
@@ -81,10 +151,10 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
     def prefill(offs=offs, pre=pre, chk=chk, q=q, k=k, v=v, pt=pt, scale=b.scale, **o):
         return lambda: medha.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, scale, **o)
 
-    def decode(qi=qi, kl=kl, **o):
+    def decode(qi=qi, kl=kl, q=q, **o):
         return lambda: medha.decode_partial_attn(q, k, v, pt, offs, qi, kl, b.scale, **o)
 
-    def chunk(rows=rows, chk=chk, kl=kl, v0=pre + 1, **o):
+    def chunk(rows=rows, chk=chk, kl=kl, v0=pre + 1, q=q, **o):
         return lambda: medha.chunk_partial_attn(q, k, v, pt, offs, rows, chk, kl, v0, b.scale, **o)
 
     def append(offs=offs, pre=pre, chk=chk, new=new):
@@ -125,6 +195,13 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
               chunk(v0=pre[:-1]), append(new=new[:-1]), append(new=new.float()),
               lambda: medha.lse_merge(po, pl[:-1]), lambda: medha.lse_merge(po.half(), pl),
               lambda: medha.lse_merge(po[..., :6].contiguous(), pl)]
+    # refused before any launch: another head dim than the cache's, workspaces that are no memory of
+    # the device's or less of it than they say
+    q64 = q[..., :64].contiguous()
+    for w in (ws, None):
+        calls += [prefill(q=q64, workspace=w), decode(q=q64, workspace=w), chunk(q=q64, workspace=w)]
+    for w in (torch.zeros(1 << 20, dtype=torch.uint8), small[:1].expand(1 << 20), ws[::2]):
+        calls += [prefill(workspace=w), decode(workspace=w), chunk(workspace=w)]
     refused = 0
     for i, call in enumerate(calls):
         native = _outcome(call)
@@ -134,7 +211,7 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
         print(f"call {i}", flush=True)
         _same(native, plain)
         refused += isinstance(native, tuple) and isinstance(native[0], type)
-    assert refused >= 28
+    assert refused >= 28 + 15
     # the module makes the ordinary calls itself, and hands back the caller's outputs
     n = binding._NATIVE
     out, lse = given((tokens,)).values()
