@@ -10,11 +10,13 @@
 
 #include <ATen/ATen.h>
 #include <c10/util/SmallVector.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <exception>
 #include <limits>
 
 #include "medha.h"
@@ -131,12 +133,12 @@ PyObject* pair(PyObject* a, const at::Tensor& ta, PyObject* b, const at::Tensor&
   return r;
 }
 
+// False without a Python error for what is no number (float() takes strings too).
 bool number(PyObject* o, float& x) {
+  const PyNumberMethods* as = Py_TYPE(o)->tp_as_number;
+  if (as == nullptr || (as->nb_float == nullptr && as->nb_index == nullptr)) return false;
   const double d = PyFloat_AsDouble(o);
-  if (d == -1.0 && PyErr_Occurred()) {
-    PyErr_Clear();
-    return false;
-  }
+  if (d == -1.0 && PyErr_Occurred()) return false;
   x = (float)d;
   return true;
 }
@@ -151,26 +153,27 @@ bool current_stream(void*& stream) {
 
 // Runs `call` as the binding's steps are run: a C++ error (a tensor without storage, memory that is
 // not there) leaves the call to binding.py.  `call` returns a result, null with a Python error set,
-// or null without one for "not from here".
+// or null without one for "not from here".  Python errors are the caller's: the scale and the
+// stream are asked for last, by Python code, where an interrupt or a signal handler's error can
+// come up as well, and those do not come again on the long way.
 template <class F>
 PyObject* ordinary(F&& call) {
   if (lib.stream == nullptr) Py_RETURN_NONE;
   PyObject* r = nullptr;
   try {
     r = call();
+  } catch (python_error& e) {
+    e.restore();
   } catch (const std::exception&) {
-    r = nullptr;
   }
-  if (r == nullptr) {
-    PyErr_Clear();  // (whatever it is comes again on the long way)
-    Py_RETURN_NONE;
-  }
+  if (r == nullptr && !PyErr_Occurred()) Py_RETURN_NONE;
   return r;
 }
 
 struct Workspace {
   at::Tensor bytes;
   at::TensorOptions options;
+  std::exception_ptr error;
 };
 
 void* allocate(size_t n, void* context) {
@@ -178,7 +181,8 @@ void* allocate(size_t n, void* context) {
   try {
     w->bytes = at::empty({(int64_t)std::max<size_t>(n, 256)}, w->options);
     return w->bytes.data_ptr();
-  } catch (const std::exception&) {
+  } catch (...) {
+    w->error = std::current_exception();
     return nullptr;
   }
 }
@@ -196,14 +200,15 @@ PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
         q->size(2) != kv.head_dim || !offs.take(a[4]) || !pre.take(a[5]) || !chk.take(a[6]) ||
         chk.size() != pre.size() ||
         !pages(table = tensor(a[3]), offs, pre.size()) || total(chk) != q->size(0) ||
-        q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[7], scale))
+        q->size(1) > std::numeric_limits<int32_t>::max())
       return nullptr;
     at::Tensor out, lse;
     if (!output(a[8], q->sizes(), *q, out) || !output(a[9], q->sizes().slice(0, 2), *q, lse))
       return nullptr;
     const at::Tensor* given = a[10] == Py_None ? nullptr : tensor(a[10]);
-    if ((a[10] != Py_None && !room(given)) || !current_stream(stream)) return nullptr;
-    Workspace ws{{}, q->options().dtype(at::kByte)};
+    if ((a[10] != Py_None && !room(given)) || !number(a[7], scale) || !current_stream(stream))
+      return nullptr;
+    Workspace ws{{}, q->options().dtype(at::kByte), nullptr};
     const void* qp = q->data_ptr();
     const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
     float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
@@ -217,6 +222,7 @@ PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
                : lib.prefill_alloc(qp, &kv, tp, offs.data(), pre.data(), chk.data(), batch, h_q,
                                    scale, op, lp, allocate, &ws, stream);
     }
+    if (ws.error) std::rethrow_exception(ws.error);
     return rc == MEDHA_OK ? pair(a[8], out, a[9], lse) : nullptr;
   });
 }
@@ -235,13 +241,13 @@ PyObject* decode_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
         kl.size() != qi.size() ||
         !pages(table = tensor(a[3]), offs, qi.size()) ||
         q->size(0) > std::numeric_limits<int32_t>::max() ||
-        q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[7], scale) ||
-        !room(ws = tensor(a[10])))
+        q->size(1) > std::numeric_limits<int32_t>::max() || !room(ws = tensor(a[10])))
       return nullptr;
     at::Tensor out, lse;
     const int64_t sizes[3] = {qi.size(), q->size(1), q->size(2)};
     if (!output(a[8], at::IntArrayRef(sizes, 3), *q, out) ||
-        !output(a[9], at::IntArrayRef(sizes, 2), *q, lse) || !current_stream(stream))
+        !output(a[9], at::IntArrayRef(sizes, 2), *q, lse) || !number(a[7], scale) ||
+        !current_stream(stream))
       return nullptr;
     const void* qp = q->data_ptr();
     const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
@@ -273,13 +279,13 @@ PyObject* chunk_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
         !v0.take(a[8]) || chk.size() != qr.size() || kl.size() != qr.size() ||
         v0.size() != qr.size() || !pages(table = tensor(a[3]), offs, qr.size()) ||
         q->size(0) > std::numeric_limits<int32_t>::max() ||
-        q->size(1) > std::numeric_limits<int32_t>::max() || !number(a[9], scale) ||
-        !room(ws = tensor(a[12])))
+        q->size(1) > std::numeric_limits<int32_t>::max() || !room(ws = tensor(a[12])))
       return nullptr;
     at::Tensor out, lse;
     const int64_t sizes[3] = {total(chk), q->size(1), q->size(2)};
     if (sizes[0] < 0 || !output(a[10], at::IntArrayRef(sizes, 3), *q, out) ||
-        !output(a[11], at::IntArrayRef(sizes, 2), *q, lse) || !current_stream(stream))
+        !output(a[11], at::IntArrayRef(sizes, 2), *q, lse) || !number(a[9], scale) ||
+        !current_stream(stream))
       return nullptr;
     const void* qp = q->data_ptr();
     const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());

@@ -291,6 +291,7 @@ int chunked_prefill(const void* q, const medha_kv_cache* kv, const int32_t* page
   if (alloc) {
     workspace_bytes = plan.workspace_bytes();
     workspace = alloc(workspace_bytes, context);
+    if (workspace == nullptr) return MEDHA_ERR_WORKSPACE;
   }
   return run_plan(plan, q, kv, page_table, num_q_heads, softmax_scale, out, lse, workspace,
                   workspace_bytes, hip_stream);

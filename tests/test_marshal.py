@@ -220,3 +220,56 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
     assert n.kv_append(new, new, k, v, pt, offs, pre, chk) is True
     assert n.lse_merge(po, pl, None, None) is not None
     assert n.chunked_prefill_attn(q, k, v, pt, offs, pre.tolist(), chk, b.scale, None, None, None) is None
+
+
+def _five_calls():
+    """scale -> the tensor calls, each of the form that the module makes itself."""
+    b = wl.make_prefill_batch("five", 2, 1, 64, [20], [4], seed=1)
+    q, k, v, pt = b.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.page_table).cuda()
+    offs, pre, chk, kl = b.page_table_offs, b.prefix_len, b.chunk_len, b.prefix_len + b.chunk_len
+    zero = np.zeros(1, np.int32)
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    new = wl.randn_bf16((4, 1, 64), 2, "cuda")
+    po, pl = torch.randn(2, 4, 2, 64, device="cuda"), torch.randn(2, 4, 2, device="cuda")
+    return {
+        "prefill": lambda s=b.scale: medha.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, s),
+        "decode": lambda s=b.scale: medha.decode_partial_attn(q, k, v, pt, offs, zero, kl, s,
+                                                              workspace=ws),
+        "chunk": lambda s=b.scale: medha.chunk_partial_attn(q, k, v, pt, offs, zero, chk, kl, pre + 1,
+                                                            s, workspace=ws),
+        "merge": lambda: medha.lse_merge(po, pl),
+        "append": lambda: medha.kv_append(new, new, k, v, pt, offs, pre, chk)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("error", [KeyboardInterrupt, TimeoutError])
+def test_what_is_raised_inside_a_call_reaches_the_caller(monkeypatch, error):
+    """Interrupts and signal handlers' errors come up where Python code runs: in the conversion of
+    the scale and in the search for the stream.  They come up once."""
+    raised = []
+
+    def once(value):
+        if not raised:
+            raised.append(1)
+            raise error()
+        return value
+
+    class Scale:
+        def __float__(self):
+            return once(0.125)
+
+    device = torch.cuda.current_device
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: once(device()))
+    for name, call in _five_calls().items():
+        raised[:] = [1]
+        call()  # (nothing raises: the module makes the call)
+        raised.clear()
+        with pytest.raises(error):
+            call()
+        call()
+        if name in ("prefill", "decode", "chunk"):
+            raised.clear()
+            with pytest.raises(error):
+                call(Scale())
+            call(Scale())
+    torch.cuda.synchronize()
