@@ -115,7 +115,7 @@ def load_library():
     calls = ("medha_chunked_prefill_attn", "medha_chunked_prefill_attn_alloc",
              "medha_decode_partial_attn", "medha_chunk_partial_attn", "medha_lse_merge",
              "medha_kv_append")
-    _marshal.bind(_stream, *(ctypes.cast(getattr(lib, name), vp).value for name in calls))
+    _marshal.bind(_stream, _check, *(ctypes.cast(getattr(lib, name), vp).value for name in calls))
     _LIB, _NATIVE = lib, _marshal
     return lib
 

@@ -2,7 +2,8 @@
 // arguments, in native code.  An ordinary call (plain tensors, arrays of the right types, everything
 // in order) is made from here; every other one is answered with None, with nothing enqueued, and
 // binding.py then goes through it step by step, converts what can be converted and raises what has
-// to be raised.  (Host time of one decode at 2048 tokens, its append and its attention: 23.9 us in
+// to be raised.  Only an error of the HIP runtime, with which some of a call may be enqueued, is
+// raised from here, and the call not made again.  (Host time of one decode at 2048 tokens, its append and its attention: 23.9 us in
 // Python, of which 7 us were the three launches and 5 us the three allocations; no more than the
 // 16 us of its kernels from here.)
 #define PY_SSIZE_T_CLEAN
@@ -24,7 +25,8 @@
 
 namespace {
 
-// Entry points of libmedha.so (bind()), and the binding's function for torch's current stream.
+// Entry points of libmedha.so (bind()), and the binding's functions for torch's current stream and
+// for error codes.
 struct Library {
   decltype(&medha_chunked_prefill_attn) prefill = nullptr;
   decltype(&medha_chunked_prefill_attn_alloc) prefill_alloc = nullptr;
@@ -33,6 +35,7 @@ struct Library {
   decltype(&medha_lse_merge) merge = nullptr;
   decltype(&medha_kv_append) append = nullptr;
   PyObject* stream = nullptr;
+  PyObject* check = nullptr;  // raises an error code of the library's
 } lib;
 
 // A host array of the caller's, copied: the call runs without the interpreter's lock.
@@ -170,6 +173,16 @@ PyObject* ordinary(F&& call) {
   return r;
 }
 
+// Whether a library call has been made.  Its refusals come before any launch and are found again on
+// the long way; other errors are raised.
+bool made(int rc) {
+  if (rc == MEDHA_OK) return true;
+  if (rc == MEDHA_ERR_INVALID_ARG || rc == MEDHA_ERR_UNSUPPORTED || rc == MEDHA_ERR_WORKSPACE)
+    return false;
+  Py_XDECREF(PyObject_CallFunction(lib.check, "i", rc));
+  return false;
+}
+
 struct Workspace {
   at::Tensor bytes;
   at::TensorOptions options;
@@ -223,7 +236,7 @@ PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
                                    scale, op, lp, allocate, &ws, stream);
     }
     if (ws.error) std::rethrow_exception(ws.error);
-    return rc == MEDHA_OK ? pair(a[8], out, a[9], lse) : nullptr;
+    return made(rc) ? pair(a[8], out, a[9], lse) : nullptr;
   });
 }
 
@@ -260,7 +273,7 @@ PyObject* decode_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
                     (int32_t)qi.size(), (int32_t)q->size(1), scale, op, lp, wp, (size_t)ws->numel(),
                     stream);
     }
-    return rc == MEDHA_OK ? pair(a[8], out, a[9], lse) : nullptr;
+    return made(rc) ? pair(a[8], out, a[9], lse) : nullptr;
   });
 }
 
@@ -298,7 +311,7 @@ PyObject* chunk_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
                    v0.data(), (int32_t)qr.size(), (int32_t)q->size(1), scale, op, lp, wp,
                    (size_t)ws->numel(), stream);
     }
-    return rc == MEDHA_OK ? pair(a[10], out, a[11], lse) : nullptr;
+    return made(rc) ? pair(a[10], out, a[11], lse) : nullptr;
   });
 }
 
@@ -326,7 +339,7 @@ PyObject* lse_merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
       rc = lib.merge(pop, plp, (int32_t)po->size(0), po->size(1), (int32_t)po->size(2),
                    (int32_t)po->size(3), op, lp, stream);
     }
-    return rc == MEDHA_OK ? pair(a[2], out, a[3], lse) : nullptr;
+    return made(rc) ? pair(a[2], out, a[3], lse) : nullptr;
   });
 }
 
@@ -353,18 +366,19 @@ PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
       rc = lib.append(kp, vp, &kv, tp, offs.data(), pre.data(), chk.data(), (int32_t)pre.size(),
                     stream);
     }
-    return rc == MEDHA_OK ? Py_NewRef(Py_True) : nullptr;
+    return made(rc) ? Py_NewRef(Py_True) : nullptr;
   });
 }
 
-// bind(stream, prefill, prefill_alloc, decode, chunk, merge, append): the entry points' addresses
+// bind(stream, check, prefill, prefill_alloc, decode, chunk, merge, append): two functions, then the
+// entry points' addresses
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 7) {
-    PyErr_SetString(PyExc_TypeError, "bind() takes 7 arguments");
+  if (n != 8) {
+    PyErr_SetString(PyExc_TypeError, "bind() takes 8 arguments");
     return nullptr;
   }
   void* p[6];
-  for (int i = 0; i < 6; ++i) p[i] = PyLong_AsVoidPtr(a[i + 1]);
+  for (int i = 0; i < 6; ++i) p[i] = PyLong_AsVoidPtr(a[i + 2]);
   if (PyErr_Occurred()) return nullptr;
   lib.prefill = reinterpret_cast<decltype(lib.prefill)>(p[0]);
   lib.prefill_alloc = reinterpret_cast<decltype(lib.prefill_alloc)>(p[1]);
@@ -373,6 +387,7 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   lib.merge = reinterpret_cast<decltype(lib.merge)>(p[4]);
   lib.append = reinterpret_cast<decltype(lib.append)>(p[5]);
   Py_XSETREF(lib.stream, Py_NewRef(a[0]));
+  Py_XSETREF(lib.check, Py_NewRef(a[1]));
   Py_RETURN_NONE;
 }
 

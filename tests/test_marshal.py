@@ -1,5 +1,7 @@
 """The extension module that makes ordinary tensor calls does what the binding's own steps do:
 the same results, outputs and errors for every form of the arguments."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -272,4 +274,33 @@ def test_what_is_raised_inside_a_call_reaches_the_caller(monkeypatch, error):
             with pytest.raises(error):
                 call(Scale())
             call(Scale())
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("code", [-1, -2, -3, -4])
+def test_an_error_with_work_enqueued_is_raised_and_not_tried_again(code):
+    """Entry points that answer with an error code: a refusal goes the long way, to the library, and
+    the call is made; a runtime error is the call's."""
+    calls = []
+    entry = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: calls.append(1) or code)
+    address = ctypes.cast(entry, ctypes.c_void_p).value
+    five = _five_calls()
+    binding.load_library()
+    try:
+        binding._NATIVE.bind(binding._stream, binding._check, *[address] * 6)
+        for i, call in enumerate(five.values()):
+            if code == -4:
+                with pytest.raises(medha.MedhaError) as e:
+                    call()
+                assert e.value.code == code
+            else:
+                call()
+            assert len(calls) == i + 1
+    finally:
+        binding._LIB = None
+        binding.load_library()  # binds the library's own again
+    for call in five.values():
+        call()
+    assert len(calls) == 5
     torch.cuda.synchronize()
