@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 import numpy as np
@@ -17,8 +18,9 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libmedha.so")
 _LIB = None
-# The extension module that makes ordinary tensor calls (csrc/marshal.cpp), once the library is
-# loaded.  It answers None, with nothing enqueued, for a call that it leaves to the code here.
+# The extension module that makes ordinary tensor calls (csrc/marshal.cpp), or _LongWay, once the
+# library is loaded.  It answers None, with nothing enqueued, for a call that it leaves to the code
+# here.
 _NATIVE = None
 
 EXPORTS = (
@@ -70,8 +72,6 @@ def load_library():
     if not os.path.exists(_LIB_PATH):
         raise FileNotFoundError(
             f"{_LIB_PATH} is missing: build it with `python -m paper_2409_17264_amd.build`")
-    from . import _marshal  # built with the library
-
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f32, sz = (ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float,
                              ctypes.c_size_t)
@@ -112,12 +112,41 @@ def load_library():
     lib.medha_strerror.argtypes = [ctypes.c_int]
     lib.medha_abi_version.restype = ctypes.c_int
     lib.medha_abi_version.argtypes = []
+    _NATIVE = _extension_module(lib)
+    _LIB = lib
+    return lib
+
+
+class _LongWay:
+    """Stands for the extension module where there is none: every call is made from here."""
+
+    @staticmethod
+    def _none(*args):
+        return None
+
+    chunked_prefill_attn = decode_partial_attn = chunk_partial_attn = lse_merge = kv_append = _none
+
+
+def _extension_module(lib):
+    """The extension module, bound to the library.  It works with one interpreter and one torch (see
+    build.py); the library, its plans and sizes need neither, so without it tensor calls are only
+    slower (one decode of 2048 tokens with its append: 24 us of host time, not 16)."""
+    try:
+        from . import _marshal
+        built_for = getattr(_marshal, "torch_version", None)
+        if built_for != torch.__version__:
+            raise ImportError(f"built for torch {built_for}")
+    except ImportError as e:
+        warnings.warn(f"calls take the slower way through ctypes, without the extension module: {e} "
+                      "(build it with `python -m paper_2409_17264_amd.build`)", RuntimeWarning,
+                      stacklevel=3)
+        return _LongWay
     calls = ("medha_chunked_prefill_attn", "medha_chunked_prefill_attn_alloc",
              "medha_decode_partial_attn", "medha_chunk_partial_attn", "medha_lse_merge",
              "medha_kv_append")
-    _marshal.bind(_stream, _check, *(ctypes.cast(getattr(lib, name), vp).value for name in calls))
-    _LIB, _NATIVE = lib, _marshal
-    return lib
+    _marshal.bind(_stream, _check,
+                  *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in calls))
+    return _marshal
 
 
 def _check(code: int):

@@ -1,6 +1,10 @@
 """Compile the HIP libraries for gfx950: csrc/medha.hip into libmedha.so (the product)
 and csrc/yardstick.hip into libmedha_yardstick.so (the benchmark's yardsticks), and the
-binding's host code, csrc/marshal.cpp, into the extension module _marshal.so.
+binding's host code, csrc/marshal.cpp, into the extension module _marshal.
+
+The libraries need hipcc alone.  The module needs g++, the headers of this interpreter (Python 3.10
+or later) and of torch, and works with the interpreter and the torch that it is built with: its
+file name carries the one's tag and its torch_version names the other.
 
 Run as ``python -m paper_2409_17264_amd.build``; also called by
 ``__graft_entry__.build()``.  hipcc cross-compiles without a GPU.
@@ -18,7 +22,7 @@ LIB = os.path.join(HERE, "libmedha.so")
 # source file -> shared library
 TARGETS = {"medha.hip": LIB, "yardstick.hip": os.path.join(HERE, "libmedha_yardstick.so")}
 
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -46,6 +50,7 @@ def _marshal_command():
     include, lib = os.path.join(root, "include"), os.path.join(root, "lib")
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DMEDHA_TORCH_VERSION="{torch.__version__}"',
             "-I", INCLUDE, "-I", CSRC, "-isystem", include,
             "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
             "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"),

@@ -1,6 +1,8 @@
 """The extension module that makes ordinary tensor calls does what the binding's own steps do:
 the same results, outputs and errors for every form of the arguments."""
 import ctypes
+import sys
+import types
 
 import numpy as np
 import pytest
@@ -9,13 +11,6 @@ import torch
 import paper_2409_17264_amd as medha
 from paper_2409_17264_amd import binding
 from paper_2409_17264_amd import workloads as wl
-
-
-class _Nothing:
-    """Leaves every call to the binding."""
-
-    def __getattr__(self, name):
-        return lambda *a: None
 
 
 def _outcome(call):
@@ -62,6 +57,30 @@ def test_calls_without_a_device_are_refused_as_before():
     with pytest.raises(AssertionError):
         medha.kv_append(b.q[:, :1].contiguous(), b.q[:, :1].contiguous(), b.k_pool, b.v_pool, pt,
                         b.page_table_offs, b.prefix_len, b.chunk_len)
+
+
+@pytest.mark.parametrize("module", [None, types.SimpleNamespace(torch_version="0.1")])
+def test_plans_and_sizes_need_no_extension_module(monkeypatch, module):
+    """A module that is not there, or was built for another torch, leaves the library usable."""
+    package = sys.modules[medha.__name__]
+    size = medha.chunked_prefill_workspace_bytes([20000], [500], 8, 1, 128)
+    plan = medha.describe_plan([20000], [500], 8, 1, 128, 256)[1:]
+    try:
+        with monkeypatch.context() as m:
+            m.setitem(sys.modules, medha.__name__ + "._marshal", module)
+            m.delattr(package, "_marshal", raising=False)
+            if module is not None:
+                m.setattr(package, "_marshal", module, raising=False)
+            m.setattr(binding, "_LIB", None)
+            m.setattr(binding, "_NATIVE", None)
+            with pytest.warns(RuntimeWarning, match="extension module"):
+                assert medha.chunked_prefill_workspace_bytes([20000], [500], 8, 1, 128) == size
+            assert medha.describe_plan([20000], [500], 8, 1, 128, 256)[1:] == plan
+            assert binding._NATIVE.kv_append(*range(8)) is None
+    finally:
+        binding._LIB = None
+        binding.load_library()
+    assert binding._NATIVE.torch_version == torch.__version__
 
 
 class _OnDevice(torch.Tensor):
@@ -208,7 +227,7 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
     for i, call in enumerate(calls):
         native = _outcome(call)
         with monkeypatch.context() as m:
-            m.setattr(binding, "_NATIVE", _Nothing())
+            m.setattr(binding, "_NATIVE", binding._LongWay)
             plain = _outcome(call)
         print(f"call {i}", flush=True)
         _same(native, plain)
