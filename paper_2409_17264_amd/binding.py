@@ -142,7 +142,8 @@ def _extension_module(lib):
                       stacklevel=3)
         return _LongWay
     calls = ("medha_chunked_prefill_attn", "medha_chunked_prefill_attn_alloc",
-             "medha_decode_partial_attn", "medha_chunk_partial_attn", "medha_lse_merge",
+             "medha_decode_partial_attn", "medha_decode_partial_workspace_bytes",
+             "medha_chunk_partial_attn", "medha_chunk_partial_workspace_bytes", "medha_lse_merge",
              "medha_kv_append")
     _marshal.bind(_stream, _check,
                   *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in calls))
@@ -255,8 +256,12 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
-def _check_output(t: torch.Tensor, shape) -> None:
+def _output(t: Optional[torch.Tensor], shape, device=None) -> torch.Tensor:
+    """An output: the caller's tensor, checked, or a new one."""
+    if t is None and device is not None:
+        return torch.empty(shape, dtype=torch.float32, device=device)
     assert _reachable(t) and t.dtype == torch.float32 and t.is_contiguous() and t.shape == shape
+    return t
 
 
 def _check_workspace(t: torch.Tensor) -> None:
@@ -289,16 +294,13 @@ def chunked_prefill_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Te
     batch = len(pre)
     assert len(chk) == batch and len(offs) == batch + 1 and _total(chk) == tokens
     assert int(offs[-1]) <= page_table.numel()
-    if out is None:
-        out = torch.empty((tokens, h_q, d), dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty((tokens, h_q), dtype=torch.float32, device=q.device)
-    _check_output(out, (tokens, h_q, d))
-    _check_output(lse, (tokens, h_q))
+    out = _output(out, (tokens, h_q, d), q.device)
+    lse = _output(lse, (tokens, h_q), q.device)
     if workspace is None:
         workspace = _workspace(lib.medha_chunked_prefill_workspace_bytes(
             _hp(pre), _hp(chk), batch, h_q, kv.num_kv_heads, d), q.device)
-    _check_workspace(workspace)
+    else:
+        _check_workspace(workspace)
     _check(lib.medha_chunked_prefill_attn(
         _dp(q), ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(pre), _hp(chk), batch, h_q,
         float(softmax_scale), _dp(out), _dp(lse), _dp(workspace), workspace.numel(), _stream()))
@@ -324,8 +326,8 @@ def chunked_prefill_attn_noalloc(q: torch.Tensor, k_pool: torch.Tensor, v_pool: 
     batch = len(pre)
     assert len(chk) == batch and len(offs) == batch + 1 and _total(chk) == tokens
     assert int(offs[-1]) <= page_table.numel()
-    _check_output(out, (tokens, h_q, d))
-    _check_output(lse, (tokens, h_q))
+    _output(out, (tokens, h_q, d))
+    _output(lse, (tokens, h_q))
     _check(lib.medha_chunked_prefill_attn_noalloc(
         _dp(q), ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(pre), _hp(chk), batch, h_q,
         float(softmax_scale), _dp(out), _dp(lse), _stream()))
@@ -354,16 +356,13 @@ def decode_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Ten
     items = len(qi)
     assert len(kl) == items and len(offs) == items + 1
     assert int(offs[-1]) <= page_table.numel()
-    if out_partial is None:
-        out_partial = torch.empty((items, h_q, d), dtype=torch.float32, device=q.device)
-    if lse_partial is None:
-        lse_partial = torch.empty((items, h_q), dtype=torch.float32, device=q.device)
-    _check_output(out_partial, (items, h_q, d))
-    _check_output(lse_partial, (items, h_q))
+    out_partial = _output(out_partial, (items, h_q, d), q.device)
+    lse_partial = _output(lse_partial, (items, h_q), q.device)
     if workspace is None:
         workspace = _workspace(lib.medha_decode_partial_workspace_bytes(
             _hp(kl), items, h_q, kv.num_kv_heads, d), q.device)
-    _check_workspace(workspace)
+    else:
+        _check_workspace(workspace)
     _check(lib.medha_decode_partial_attn(
         _dp(q), num_queries, ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(qi), _hp(kl), items,
         h_q, float(softmax_scale), _dp(out_partial), _dp(lse_partial), _dp(workspace),
@@ -405,16 +404,13 @@ def chunk_partial_attn(q: torch.Tensor, k_pool: torch.Tensor, v_pool: torch.Tens
     assert len(chk) == items and len(kl) == items and len(v0) == items and len(offs) == items + 1
     assert int(offs[-1]) <= page_table.numel()
     rows = _total(chk)
-    if out_partial is None:
-        out_partial = torch.empty((rows, h_q, d), dtype=torch.float32, device=q.device)
-    if lse_partial is None:
-        lse_partial = torch.empty((rows, h_q), dtype=torch.float32, device=q.device)
-    _check_output(out_partial, (rows, h_q, d))
-    _check_output(lse_partial, (rows, h_q))
+    out_partial = _output(out_partial, (rows, h_q, d), q.device)
+    lse_partial = _output(lse_partial, (rows, h_q), q.device)
     if workspace is None:
         workspace = _workspace(lib.medha_chunk_partial_workspace_bytes(
             _hp(chk), _hp(kl), items, h_q, kv.num_kv_heads, d), q.device)
-    _check_workspace(workspace)
+    else:
+        _check_workspace(workspace)
     _check(lib.medha_chunk_partial_attn(
         _dp(q), tokens, ctypes.byref(kv), _dp(page_table), _hp(offs), _hp(qr), _hp(chk), _hp(kl),
         _hp(v0), items, h_q, float(softmax_scale), _dp(out_partial), _dp(lse_partial),
@@ -434,12 +430,8 @@ def lse_merge(out_partial: torch.Tensor, lse_partial: torch.Tensor,
     assert out_partial.is_contiguous() and lse_partial.is_contiguous() and out_partial.dim() == 4
     s, rows, h_q, d = out_partial.shape
     assert lse_partial.shape == (s, rows, h_q)
-    if out is None:
-        out = torch.empty((rows, h_q, d), dtype=torch.float32, device=out_partial.device)
-    if lse is None:
-        lse = torch.empty((rows, h_q), dtype=torch.float32, device=out_partial.device)
-    _check_output(out, (rows, h_q, d))
-    _check_output(lse, (rows, h_q))
+    out = _output(out, (rows, h_q, d), out_partial.device)
+    lse = _output(lse, (rows, h_q), out_partial.device)
     _check(lib.medha_lse_merge(_dp(out_partial), _dp(lse_partial), s, rows, h_q, d, _dp(out),
                                _dp(lse), _stream()))
     return out, lse

@@ -1,6 +1,6 @@
 // Argument marshalling of the Python binding's tensor calls: what binding.py does with a call's
-// arguments, in native code.  An ordinary call (plain tensors, arrays of the right types, everything
-// in order) is made from here; every other one is answered with None, with nothing enqueued, and
+// arguments, in native code.  An ordinary call (plain tensors, lengths as int32 or int64 arrays or as
+// lists of integers, everything in order) is made from here; every other one is answered with None, with nothing enqueued, and
 // binding.py then goes through it step by step, converts what can be converted and raises what has
 // to be raised.  Only an error of the HIP runtime, with which some of a call may be enqueued, is
 // raised from here, and the call not made again.  (Host time of one decode at 2048 tokens, its append and its attention: 23.9 us in
@@ -31,7 +31,9 @@ struct Library {
   decltype(&medha_chunked_prefill_attn) prefill = nullptr;
   decltype(&medha_chunked_prefill_attn_alloc) prefill_alloc = nullptr;
   decltype(&medha_decode_partial_attn) decode = nullptr;
+  decltype(&medha_decode_partial_workspace_bytes) decode_bytes = nullptr;
   decltype(&medha_chunk_partial_attn) chunk = nullptr;
+  decltype(&medha_chunk_partial_workspace_bytes) chunk_bytes = nullptr;
   decltype(&medha_lse_merge) merge = nullptr;
   decltype(&medha_kv_append) append = nullptr;
   PyObject* stream = nullptr;
@@ -42,28 +44,66 @@ struct Library {
 template <class T>
 class HostArray {
  public:
-  // False unless `o` is a C-contiguous buffer of T.
+  // Takes C-contiguous buffers of int32 and int64 and lists and tuples of Python's integers, as long
+  // as T holds their values; false for anything else.  (The arrays are a call's first checks: what
+  // has to go the long way is most often found here, and costs least to find out.)
   bool take(PyObject* o) {
+    if (PyList_CheckExact(o) || PyTuple_CheckExact(o)) return take_sequence(o);
+    if (!PyObject_CheckBuffer(o)) return false;
     Py_buffer view;
     if (PyObject_GetBuffer(o, &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) != 0) {
       PyErr_Clear();
       return false;
     }
-    const char* f = view.format;
-    const bool type = f != nullptr && f[0] != 0 && f[1] == 0 &&
-                      (sizeof(T) == 4 ? f[0] == 'i' : f[0] == 'l' || f[0] == 'q') &&
-                      view.itemsize == (Py_ssize_t)sizeof(T);
-    if (type) {
-      values_.resize(view.len / sizeof(T));
-      if (view.len > 0) std::memcpy(values_.data(), view.buf, view.len);
-    }
+    const char format = view.format != nullptr && view.format[0] != 0 && view.format[1] == 0
+                            ? view.format[0] : 0;
+    bool taken = false;
+    if (format == 'i' && view.itemsize == 4)
+      taken = take_values<int32_t>(view);
+    else if ((format == 'l' || format == 'q') && view.itemsize == 8)
+      taken = take_values<int64_t>(view);
     PyBuffer_Release(&view);
-    return type;
+    return taken;
   }
   const T* data() const { return values_.data(); }
   int64_t size() const { return (int64_t)values_.size(); }
 
  private:
+  static bool holds(int64_t x) { return x == (int64_t)(T)x; }
+
+  // (a buffer need not be aligned to its type)
+  template <class From>
+  bool take_values(const Py_buffer& view) {
+    const int64_t n = view.len / (int64_t)sizeof(From);
+    const char* from = static_cast<const char*>(view.buf);
+    values_.resize(n);
+    if (sizeof(From) == sizeof(T)) {
+      if (n > 0) std::memcpy(values_.data(), from, n * sizeof(T));
+      return true;
+    }
+    for (int64_t i = 0; i < n; ++i) {
+      From x;
+      std::memcpy(&x, from + i * sizeof(From), sizeof(From));
+      if (!holds(x)) return false;
+      values_[i] = (T)x;
+    }
+    return true;
+  }
+
+  bool take_sequence(PyObject* o) {
+    const Py_ssize_t n = PySequence_Fast_GET_SIZE(o);
+    PyObject** items = PySequence_Fast_ITEMS(o);
+    values_.resize(n);
+    for (Py_ssize_t i = 0; i < n; ++i) {
+      if (!PyLong_CheckExact(items[i])) return false;
+      int overflow;
+      const long long x = PyLong_AsLongLongAndOverflow(items[i], &overflow);
+      if (overflow != 0 || !holds(x)) return false;
+      values_[i] = (T)x;
+    }
+    return true;
+  }
+
   c10::SmallVector<T, 72> values_;
 };
 
@@ -112,8 +152,14 @@ bool pages(const at::Tensor* table, const HostArray<int64_t>& offs, int64_t n) {
          offs.size() == n + 1 && offs.data()[n] <= table->numel();
 }
 
-// A caller's workspace (of any type: its elements are counted as bytes).
-bool room(const at::Tensor* t) { return t != nullptr && t->is_cuda() && t->is_contiguous(); }
+// The caller's workspace, if there is one (of any type: its elements are counted as bytes).
+bool room(PyObject* o, at::Tensor& t) {
+  if (o == Py_None) return true;
+  const at::Tensor* given = tensor(o);
+  if (given == nullptr || !given->is_cuda() || !given->is_contiguous()) return false;
+  t = *given;
+  return true;
+}
 
 // An output: the caller's tensor, checked, or a new one.
 bool output(PyObject* o, at::IntArrayRef sizes, const at::Tensor& like, at::Tensor& t) {
@@ -183,6 +229,10 @@ bool made(int rc) {
   return false;
 }
 
+at::Tensor new_workspace(size_t n, const at::TensorOptions& options) {
+  return at::empty({(int64_t)std::max<size_t>(n, 256)}, options.dtype(at::kByte));
+}
+
 struct Workspace {
   at::Tensor bytes;
   at::TensorOptions options;
@@ -192,7 +242,7 @@ struct Workspace {
 void* allocate(size_t n, void* context) {
   Workspace* w = static_cast<Workspace*>(context);
   try {
-    w->bytes = at::empty({(int64_t)std::max<size_t>(n, 256)}, w->options);
+    w->bytes = new_workspace(n, w->options);
     return w->bytes.data_ptr();
   } catch (...) {
     w->error = std::current_exception();
@@ -209,29 +259,29 @@ PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HostArray<int32_t> pre, chk;
     float scale;
     void* stream;
-    if (n != 11 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
-        q->size(2) != kv.head_dim || !offs.take(a[4]) || !pre.take(a[5]) || !chk.take(a[6]) ||
-        chk.size() != pre.size() ||
+    if (n != 11 || !pre.take(a[5]) || !chk.take(a[6]) || !offs.take(a[4]) ||
+        !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
+        q->size(2) != kv.head_dim || chk.size() != pre.size() ||
         !pages(table = tensor(a[3]), offs, pre.size()) || total(chk) != q->size(0) ||
         q->size(1) > std::numeric_limits<int32_t>::max())
       return nullptr;
     at::Tensor out, lse;
     if (!output(a[8], q->sizes(), *q, out) || !output(a[9], q->sizes().slice(0, 2), *q, lse))
       return nullptr;
-    const at::Tensor* given = a[10] == Py_None ? nullptr : tensor(a[10]);
-    if ((a[10] != Py_None && !room(given)) || !number(a[7], scale) || !current_stream(stream))
-      return nullptr;
-    Workspace ws{{}, q->options().dtype(at::kByte), nullptr};
+    at::Tensor given;
+    if (!room(a[10], given) || !number(a[7], scale) || !current_stream(stream)) return nullptr;
+    Workspace ws{{}, q->options(), nullptr};
     const void* qp = q->data_ptr();
     const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
     float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
-    void* wp = given ? given->data_ptr() : nullptr;
+    void* wp = given.defined() ? given.data_ptr() : nullptr;
     const int32_t batch = (int32_t)pre.size(), h_q = (int32_t)q->size(1);
     int rc;
     {
       Unlocked unlocked;
-      rc = given ? lib.prefill(qp, &kv, tp, offs.data(), pre.data(), chk.data(), batch, h_q, scale, op,
-                             lp, wp, (size_t)given->numel(), stream)
+      rc = given.defined()
+               ? lib.prefill(qp, &kv, tp, offs.data(), pre.data(), chk.data(), batch, h_q, scale, op,
+                             lp, wp, (size_t)given.numel(), stream)
                : lib.prefill_alloc(qp, &kv, tp, offs.data(), pre.data(), chk.data(), batch, h_q,
                                    scale, op, lp, allocate, &ws, stream);
     }
@@ -243,34 +293,37 @@ PyObject* chunked_prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (q, k_pool, v_pool, page_table, offs, q_index, kv_len, scale, out, lse, workspace)
 PyObject* decode_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return ordinary([&]() -> PyObject* {
-    const at::Tensor *q, *table, *ws;
+    const at::Tensor *q, *table;
     medha_kv_cache kv;
     HostArray<int64_t> offs;
     HostArray<int32_t> qi, kl;
     float scale;
     void* stream;
-    if (n != 11 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
-        q->size(2) != kv.head_dim || !offs.take(a[4]) || !qi.take(a[5]) || !kl.take(a[6]) ||
-        kl.size() != qi.size() ||
+    if (n != 11 || !kl.take(a[6]) || !qi.take(a[5]) || !offs.take(a[4]) ||
+        !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
+        q->size(2) != kv.head_dim || kl.size() != qi.size() ||
         !pages(table = tensor(a[3]), offs, qi.size()) ||
         q->size(0) > std::numeric_limits<int32_t>::max() ||
-        q->size(1) > std::numeric_limits<int32_t>::max() || !room(ws = tensor(a[10])))
+        q->size(1) > std::numeric_limits<int32_t>::max())
       return nullptr;
-    at::Tensor out, lse;
+    at::Tensor out, lse, ws;
     const int64_t sizes[3] = {qi.size(), q->size(1), q->size(2)};
     if (!output(a[8], at::IntArrayRef(sizes, 3), *q, out) ||
-        !output(a[9], at::IntArrayRef(sizes, 2), *q, lse) || !number(a[7], scale) ||
-        !current_stream(stream))
+        !output(a[9], at::IntArrayRef(sizes, 2), *q, lse) || !room(a[10], ws) ||
+        !number(a[7], scale) || !current_stream(stream))
       return nullptr;
+    if (!ws.defined())
+      ws = new_workspace(lib.decode_bytes(kl.data(), (int32_t)kl.size(), (int32_t)q->size(1),
+                                          kv.num_kv_heads, kv.head_dim), q->options());
     const void* qp = q->data_ptr();
     const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
     float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
-    void* wp = ws->data_ptr();
+    void* wp = ws.data_ptr();
     int rc;
     {
       Unlocked unlocked;
       rc = lib.decode(qp, (int32_t)q->size(0), &kv, tp, offs.data(), qi.data(), kl.data(),
-                    (int32_t)qi.size(), (int32_t)q->size(1), scale, op, lp, wp, (size_t)ws->numel(),
+                    (int32_t)qi.size(), (int32_t)q->size(1), scale, op, lp, wp, (size_t)ws.numel(),
                     stream);
     }
     return made(rc) ? pair(a[8], out, a[9], lse) : nullptr;
@@ -281,35 +334,40 @@ PyObject* decode_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // workspace)
 PyObject* chunk_partial_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return ordinary([&]() -> PyObject* {
-    const at::Tensor *q, *table, *ws;
+    const at::Tensor *q, *table;
     medha_kv_cache kv;
     HostArray<int64_t> offs;
     HostArray<int32_t> qr, chk, kl, v0;
     float scale;
     void* stream;
-    if (n != 13 || !device_array(q = tensor(a[0]), at::kBFloat16, 3) || !cache(a[1], a[2], kv) ||
-        q->size(2) != kv.head_dim || !offs.take(a[4]) || !qr.take(a[5]) || !chk.take(a[6]) || !kl.take(a[7]) ||
-        !v0.take(a[8]) || chk.size() != qr.size() || kl.size() != qr.size() ||
+    if (n != 13 || !chk.take(a[6]) || !kl.take(a[7]) || !v0.take(a[8]) ||
+        !qr.take(a[5]) || !offs.take(a[4]) || !device_array(q = tensor(a[0]), at::kBFloat16, 3) ||
+        !cache(a[1], a[2], kv) || q->size(2) != kv.head_dim || chk.size() != qr.size() ||
+        kl.size() != qr.size() ||
         v0.size() != qr.size() || !pages(table = tensor(a[3]), offs, qr.size()) ||
         q->size(0) > std::numeric_limits<int32_t>::max() ||
-        q->size(1) > std::numeric_limits<int32_t>::max() || !room(ws = tensor(a[12])))
+        q->size(1) > std::numeric_limits<int32_t>::max())
       return nullptr;
-    at::Tensor out, lse;
+    at::Tensor out, lse, ws;
     const int64_t sizes[3] = {total(chk), q->size(1), q->size(2)};
     if (sizes[0] < 0 || !output(a[10], at::IntArrayRef(sizes, 3), *q, out) ||
-        !output(a[11], at::IntArrayRef(sizes, 2), *q, lse) || !number(a[9], scale) ||
-        !current_stream(stream))
+        !output(a[11], at::IntArrayRef(sizes, 2), *q, lse) || !room(a[12], ws) ||
+        !number(a[9], scale) || !current_stream(stream))
       return nullptr;
+    if (!ws.defined())
+      ws = new_workspace(lib.chunk_bytes(chk.data(), kl.data(), (int32_t)chk.size(),
+                                         (int32_t)q->size(1), kv.num_kv_heads, kv.head_dim),
+                         q->options());
     const void* qp = q->data_ptr();
     const int32_t* tp = static_cast<const int32_t*>(table->data_ptr());
     float *op = static_cast<float*>(out.data_ptr()), *lp = static_cast<float*>(lse.data_ptr());
-    void* wp = ws->data_ptr();
+    void* wp = ws.data_ptr();
     int rc;
     {
       Unlocked unlocked;
       rc = lib.chunk(qp, (int32_t)q->size(0), &kv, tp, offs.data(), qr.data(), chk.data(), kl.data(),
                    v0.data(), (int32_t)qr.size(), (int32_t)q->size(1), scale, op, lp, wp,
-                   (size_t)ws->numel(), stream);
+                   (size_t)ws.numel(), stream);
     }
     return made(rc) ? pair(a[10], out, a[11], lse) : nullptr;
   });
@@ -351,10 +409,11 @@ PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HostArray<int64_t> offs;
     HostArray<int32_t> pre, chk;
     void* stream;
-    if (n != 8 || !device_array(k = tensor(a[0]), at::kBFloat16, 3) ||
+    if (n != 8 || !pre.take(a[6]) || !chk.take(a[7]) || !offs.take(a[5]) ||
+        !device_array(k = tensor(a[0]), at::kBFloat16, 3) ||
         !device_array(v = tensor(a[1]), at::kBFloat16, 3) || k->sizes() != v->sizes() ||
         !cache(a[2], a[3], kv) || k->size(1) != kv.num_kv_heads || k->size(2) != kv.head_dim ||
-        !offs.take(a[5]) || !pre.take(a[6]) || !chk.take(a[7]) || chk.size() != pre.size() ||
+        chk.size() != pre.size() ||
         !pages(table = tensor(a[4]), offs, pre.size()) || total(chk) != k->size(0) ||
         !current_stream(stream))
       return nullptr;
@@ -370,22 +429,24 @@ PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// bind(stream, check, prefill, prefill_alloc, decode, chunk, merge, append): two functions, then the
-// entry points' addresses
+// bind(stream, check, entry points' addresses in the order below)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 8) {
-    PyErr_SetString(PyExc_TypeError, "bind() takes 8 arguments");
+  constexpr int kEntries = 8;
+  if (n != 2 + kEntries) {
+    PyErr_Format(PyExc_TypeError, "bind() takes %d arguments", 2 + kEntries);
     return nullptr;
   }
-  void* p[6];
-  for (int i = 0; i < 6; ++i) p[i] = PyLong_AsVoidPtr(a[i + 2]);
+  void* p[kEntries];
+  for (int i = 0; i < kEntries; ++i) p[i] = PyLong_AsVoidPtr(a[i + 2]);
   if (PyErr_Occurred()) return nullptr;
   lib.prefill = reinterpret_cast<decltype(lib.prefill)>(p[0]);
   lib.prefill_alloc = reinterpret_cast<decltype(lib.prefill_alloc)>(p[1]);
   lib.decode = reinterpret_cast<decltype(lib.decode)>(p[2]);
-  lib.chunk = reinterpret_cast<decltype(lib.chunk)>(p[3]);
-  lib.merge = reinterpret_cast<decltype(lib.merge)>(p[4]);
-  lib.append = reinterpret_cast<decltype(lib.append)>(p[5]);
+  lib.decode_bytes = reinterpret_cast<decltype(lib.decode_bytes)>(p[3]);
+  lib.chunk = reinterpret_cast<decltype(lib.chunk)>(p[4]);
+  lib.chunk_bytes = reinterpret_cast<decltype(lib.chunk_bytes)>(p[5]);
+  lib.merge = reinterpret_cast<decltype(lib.merge)>(p[6]);
+  lib.append = reinterpret_cast<decltype(lib.append)>(p[7]);
   Py_XSETREF(lib.stream, Py_NewRef(a[0]));
   Py_XSETREF(lib.check, Py_NewRef(a[1]));
   Py_RETURN_NONE;

@@ -43,7 +43,9 @@ def _forms(x):
     odd[:] = x
     return [x, x.tolist(), tuple(x.tolist()), x.astype(np.int64), x.astype(np.int32),
             x.astype(np.float64), wide[::2], x.reshape(1, -1), odd, torch.from_numpy(x.copy()),
-            x.astype(x.dtype.newbyteorder(">"))]
+            x.astype(x.dtype.newbyteorder(">")), [x.tolist()], list(x), x.astype(np.uint32),
+            # numpy keeps the low half of what int32 does not hold
+            x.astype(np.int64) + (1 << 32), (x.astype(np.int64) + (1 << 32)).tolist()]
 
 
 def test_calls_without_a_device_are_refused_as_before():
@@ -240,7 +242,23 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
     assert r[0] is out and r[1] is lse
     assert n.kv_append(new, new, k, v, pt, offs, pre, chk) is True
     assert n.lse_merge(po, pl, None, None) is not None
-    assert n.chunked_prefill_attn(q, k, v, pt, offs, pre.tolist(), chk, b.scale, None, None, None) is None
+    # with lengths as lists, tuples and 64-bit arrays, and with or without a workspace
+    for form in (lambda x: x, lambda x: x.tolist(), lambda x: tuple(x.tolist()),
+                 lambda x: x.astype(np.int64)):
+        for w in (ws, None):
+            lengths = [form(x) for x in (offs, rows, chk, kl, pre + 1, pre, qi)]
+            o, r, c, n_keys, v0, p, i = lengths
+            made = (n.chunked_prefill_attn(q, k, v, pt, o, p, c, b.scale, None, None, w),
+                    n.decode_partial_attn(q, k, v, pt, o, i, n_keys, b.scale, None, None, w),
+                    n.chunk_partial_attn(q, k, v, pt, o, r, c, n_keys, v0, b.scale, None, None, w))
+            with monkeypatch.context() as m:
+                m.setattr(binding, "_NATIVE", binding._LongWay)
+                plain = (prefill(workspace=w)(), decode(workspace=w)(), chunk(workspace=w)())
+            torch.cuda.synchronize()
+            for x, y in zip(made, plain):
+                _same(x, y)
+    for bad in ([True, 1, 1], [1.0, 1, 1], [1 << 40, 1, 1], pre.astype(np.int64) + (1 << 32)):
+        assert n.chunked_prefill_attn(q, k, v, pt, offs, bad, chk, b.scale, None, None, None) is None
 
 
 def _five_calls():
@@ -307,7 +325,7 @@ def test_an_error_with_work_enqueued_is_raised_and_not_tried_again(code):
     five = _five_calls()
     binding.load_library()
     try:
-        binding._NATIVE.bind(binding._stream, binding._check, *[address] * 6)
+        binding._NATIVE.bind(binding._stream, binding._check, *[address] * 8)
         for i, call in enumerate(five.values()):
             if code == -4:
                 with pytest.raises(medha.MedhaError) as e:
