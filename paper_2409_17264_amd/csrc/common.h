@@ -145,13 +145,27 @@ __host__ __device__ inline SlotItem decode_slot_dealt(int u, int h_kv, int n_spl
   return r;
 }
 
-// A sequence of few items (one or two KV heads, short) has items for its first few dies only, and
-// the next one as well.  So the dies are counted from another one for every sequence, the one behind
-// the last item before: slot u stands for the slot that this returns.  (100 decodes of 1K median
-// at 8/1 heads, one to four items each, on dies 0 to 3 without it: 59.8 -> 47.4 us; 128 of 4K,
-// 103.0 -> 93.1.)
+// A sequence whose items do not fill a round of the dies leaves its last dies idle, and the next one
+// as well.  So the dies are counted from another one for every sequence, the one behind the last that
+// the sequence before keeps busy (dies_taken): slot u stands for the slot that this returns.  (100
+// decodes of 1K median at 8/1 heads, one to four items each, on dies 0 to 3 without it: 59.8 -> 47.4
+// us; 128 of 4K, 103.0 -> 93.1.  20 decodes of 5000 at 8/1 heads, ten items each, two a die, 19.1
+// us, 25.8 if the count goes on by items; 24 of 2600 at 8/4, twenty items each, 28.9 and 36.6.)
 __host__ __device__ inline int turned_slot(int u, int first_die) {
   return (u & ~(kXcds - 1)) | ((u - first_die) & (kXcds - 1));
+}
+
+// Dies by which the next sequence's first lies behind this one's.  decode_slot's equal runs of items
+// end on die (items - 1) / run, the only one that may hold less than a run among those that hold any,
+// and so do decode_slot_dealt's last groups, unless they deal single row tiles: then items % 8 dies
+// hold one more than the others.
+inline int dies_taken(const SeqDesc& sd, int h_kv) {
+  const int64_t groups = (int64_t)h_kv * sd.n_split, n = sd.n_row_tiles;
+  const int64_t items = (sd.dealt ? groups % kXcds : groups) * n;
+  if (items == 0) return 0;
+  if (sd.dealt && n >= 2 * kXcds) return (int)(items % kXcds);
+  const int64_t run = (items + kXcds - 1) / kXcds;
+  return (int)((items - 1) / run + 1) % kXcds;
 }
 
 // Work item of slot `u` (counted from the sequence's first) of a key-split launch: one row tile, so

@@ -430,7 +430,7 @@ inline void plan_launch(LaunchPlan& lp, int h_kv, int gqa, int64_t steps, int mi
     }
     const int64_t items = (int64_t)h_kv * sd.n_split * sd.n_row_tiles;
     slot += (int)(kXcds * ceil_div(items, kXcds));
-    die = (int)((die + items) % kXcds);
+    die = (die + dies_taken(sd, h_kv)) % kXcds;
     rank += sd.chunk_len;
   }
   lp.n_slots = slot;

@@ -60,12 +60,21 @@ def test_dealt_slots_cover_every_item_once_and_evenly(tmp_path):
     assert run.returncode == 0 and "ok" in run.stdout, run.stdout + run.stderr
 
 
-@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,mode", [
-    ([900 + 31 * i for i in range(40)], [1] * 40, 8, 1, 1),      # one to four ranges of one head
-    ([300 * (1 + i % 5) for i in range(33)], [1] * 33, 8, 2, 1),
-    ([0] * 12, [90 + 16 * i for i in range(12)], 8, 1, 0),       # prompts of 3 to 9 row tiles
+@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,mode,per_seq", [
+    ([900 + 31 * i for i in range(40)], [1] * 40, 8, 1, 1, None),  # one to four ranges of one head
+    ([300 * (1 + i % 5) for i in range(33)], [1] * 33, 8, 2, 1, None),
+    ([0] * 12, [90 + 16 * i for i in range(12)], 8, 1, 0, None),   # prompts of 3 to 9 row tiles
+    ([6143] * 24, [1] * 24, 8, 1, 1, 12),                          # two items on each of six dies
+    ([1535] * 32, [1] * 32, 32, 4, 1, 12),
+    ([2600] * 24, [1] * 24, 8, 4, 1, 20),                          # three on six dies, two on one
+    ([3583] * 24, [1] * 24, 8, 4, 1, 28),                          # four on each of seven dies
+    ([5000] * 20, [1] * 20, 8, 1, 1, 10),
+    ([0] * 14, [300] * 14, 8, 1, 0, 10),                           # prompts: runs of items
+    ([0] * 14, [620] * 14, 8, 1, 0, 20),                           # prompts: single row tiles in turn
+    ([0] * 13, [830] * 13, 8, 1, 0, 26),
+    ([0] * 13, [600] * 13, 20, 10, 0, 50),                         # a group a die, and two groups
 ])
-def test_sequences_of_few_items_are_spread_over_the_dies(prefix, chunk, h_q, h_kv, mode):
+def test_sequences_of_few_items_are_spread_over_the_dies(prefix, chunk, h_q, h_kv, mode, per_seq):
     entries, grid_rows, grid_keys, _ = medha.describe_plan(prefix, chunk, h_q, h_kv, 128, 256)
     items, dies = 0, [0] * 8
     for s in range(grid_keys if mode else grid_rows):
@@ -73,6 +82,8 @@ def test_sequences_of_few_items_are_spread_over_the_dies(prefix, chunk, h_q, h_k
         if it is not None:
             items += 1
             dies[s % 8] += 1
-    assert items == sum(h_kv * e.n_split * e.n_row_tiles for e in entries)
-    # equal runs of a sequence differ by one item, and those of more than 8 items by their last run
-    assert max(dies) <= items / 8 + len(entries) / 2 + 1, dies
+    each = [h_kv * e.n_split * e.n_row_tiles for e in entries]
+    assert items == sum(each) and per_seq in (None, min(each)) and per_seq in (None, max(each))
+    # however many sequences there are: an item more than the mean, and a twentieth for the dies
+    # that a sequence's last run leaves short
+    assert max(dies) <= 1.05 * items / 8 + 1, dies
