@@ -83,7 +83,16 @@ inline WalkCost walk_cost(int head_dim, int q_blocks) {
 }
 
 // Small workgroups (128 rows) where that is not their only form: alone on a compute unit (head dims 64
-// and 128), and in pairs with the short ring (head dim 128).
+// and 128), and in pairs with the short ring (head dim 128).  Equal walks of 8, 16, 32, 64 and 128
+// tiles, one round of the device, 8 K/V streams, take
+//   alone, d 64      13.4, 19.5, 31.8, 54.1,  98.8 us: 0.71 us a tile and 7.5 us outside the walk
+//   alone, d 128     18.8, 27.7, 46.1, 81.1, 148.7: 1.09 and 10
+//   in pairs, d 128  27.4, 42.5, 74.4, 132.7, 250.2 for two: 1.86 and 12
+//   256 rows, d 128  26.9, 41.9, 72.9, 127.7, 239.4: 1.77 and 12.5 (d 64: 17.0 .. 146.9)
+// Against the large form's constants above, these ask for the small ones what they measure at 8 to
+// 16 tiles (alone 18.0 and 28.0 us at d 128, 14.2 and 19.4 at 64; a pair 1.04 of a large one at 16,
+// measured 1.02) and a twelfth more at 128 (a pair 1.11, measured 1.05): where walks are long, a
+// small form wins by the whole round that it saves or not at all.
 constexpr WalkCost kAloneCost[2] = {{0.65, 9.0, 1}, {1.25, 8.0, 1}}, kPairedCost{1.85, 8.0, 2};
 
 // What partials cost: a launch, then their bytes.  The merge kernel takes 8 us for 31 MB and 17
@@ -570,13 +579,15 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
       // at 96 and 288 tiles where both fill the device).
       if (head_dim == 64 && big) try_small(walk_cost(64, 1), false, 0.97, num_cus + 1, INT64_MAX);
       // A launch that leaves compute units idle spreads over twice as many of them: a small
-      // workgroup has its SIMDs to itself, one wavefront each, and takes three quarters of the
-      // time a tile (64 tokens at 2000, 8/1 heads, d 128, 18.3 -> 15.2 us; 300 at 1000, 32/8, 29.4
-      // -> 25.9; 200 at 8000, 8/1, 29.6 -> 26.5; d 64: 100 at 2000, 32/8, 15.8 -> 14.4; 64 at 3000,
-      // 8/2, 14.5 -> 12.9; with one KV head, where a handful of workgroups is all there is either
-      // way, 256 at 1024, 2/1, 13.4 -> 13.1: left as it is).  Prompts and chunks longer than their prefix keep the large
-      // ones: alone they gain as well (1300 tokens at 8/1 27.4 -> 25.4), eight together lose 3 %.
-      if (behind && big && (head_dim == 128 || h_kv > 1))
+      // workgroup has its SIMDs to itself, one wavefront each, and takes two thirds to three quarters
+      // of the time a tile (64 tokens at 2000, 8/1 heads, d 128, 18.3 -> 15.2 us; 300 at 1000, 32/8,
+      // 29.4 -> 25.9; 200 at 8000, 8/1, 29.6 -> 26.5; d 64: 256 at 1024, 2/1, 13.4 -> 12.7; 200 at
+      // 2000, 4/1, 15.4 -> 13.8; 100 at 2000, 32/8, 15.5 -> 14.4; 500 at 6000, 2/1, 17.9 -> 16.6).
+      // 16 launches estimated below 0.97 at 128 take 8 to 16 % less, 25 below 0.90 at 64 (all at
+      // 0.79 to 0.84) 2 to 20; at 64 from 0.94 on it is 9 % less to 7 more.  Prompts and chunks
+      // longer than their prefix keep the large ones: alone they gain as well (1300 tokens at 8/1
+      // 27.4 -> 25.4), eight together lose 3 %.
+      if (behind && big)
         try_small(kAloneCost[head_dim == 128], false, head_dim == 128 ? 0.97 : 0.90, 1, num_cus);
       // In pairs at head dim 128 (see run_tiles): 900 tokens at 2000, 8/2 heads, 35.6 -> 31.0 us.
       // Where 129 to 255 rows have no large form, two row tiles that share a K/V stream beat one

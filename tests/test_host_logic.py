@@ -143,7 +143,7 @@ def test_plans_of_the_named_workloads():
     assert all(x.mode == 1 and x.n_split == 64 for x in e) and gk == 2048
     # cfg1
     e, gr, _ = _check_plan([1024], [256], 2, 1, 64, 256)
-    assert e[0].n_row_tiles == 2 and e[0].n_split > 1
+    assert e[0].n_row_tiles == 4 and e[0].n_split > 1
 
 
 def test_plans_of_ragged_batches():
@@ -188,6 +188,16 @@ def test_row_split_launches_fill_whole_rounds_of_the_device(prefix, chunk, h_q, 
     rounds = -(-grid // slots)
     tiles = sum(h_kv * x.n_row_tiles * -(-(p + c) // 64) for x, p, c in zip(e, prefix, chunk))
     assert rounds * max(x.tiles_per_split for x in e) <= 1.15 * tiles / slots + 12 * rounds
+
+
+@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,d,rows,most", [
+    # small workgroups alone on a compute unit, whatever the number of KV heads
+    ([1024], [256], 2, 1, 64, 128, 256), ([2000], [64], 8, 1, 64, 128, 256),
+    ([2000], [200], 4, 1, 64, 128, 256), ([6000], [512], 2, 1, 64, 128, 256),
+])
+def test_small_workgroups_where_they_are_faster(prefix, chunk, h_q, h_kv, d, rows, most):
+    e, grid, _, _ = medha.describe_plan(prefix, chunk, h_q, h_kv, d, 256)
+    assert e[0].rows_per_wg == rows and (256 < grid <= 512 if most == 512 else grid <= most)
 
 
 def test_stream_handle_without_the_private_function(monkeypatch):
