@@ -95,6 +95,8 @@ inline WalkCost walk_cost(int head_dim, int q_blocks) {
 // small form wins by the whole round that it saves or not at all.
 constexpr WalkCost kAloneCost[2] = {{0.65, 9.0, 1}, {1.25, 8.0, 1}}, kPairedCost{1.85, 8.0, 2};
 
+constexpr int64_t kShortPairedTiles = 10;
+
 // What partials cost: a launch, then their bytes.  The merge kernel takes 8 us for 31 MB and 17
 // to 18 us for 99 MB; the constants ask 10 and 25, since partials are written and held as well.
 constexpr double kMergeLaunchUs = 3.0, kMergeBytesPerUs = 4.5e6;
@@ -546,9 +548,9 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
                                 walk_cost(head_dim, plan.rows.q_blocks), rows_steps, kMinTiles,
                                 row_bytes, fit - keys_rows, us);
       // The small workgroups as an alternative, `least` to `most` of them, where the estimate falls
-      // below `worth` of the plan so far.
+      // below `worth` of the plan so far (`worth_short`: with ranges of up to `short_tiles`).
       auto try_small = [&](const WalkCost& cost, bool paired, double worth, int64_t least,
-                           int64_t most) {
+                           int64_t most, int64_t short_tiles = 0, double worth_short = 0.0) {
         LaunchPlan small = plan.rows;
         small.q_blocks = 1;
         small.paired = paired;
@@ -559,6 +561,7 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
         const int64_t steps = choose_steps(small, walks, h_kv, num_cus, cost, INT32_MAX, kMinTiles,
                                            row_bytes, fit - keys_rows, small_us);
         const int64_t slots = split_size(small, h_kv, steps, kMinTiles).slots;
+        if (steps <= short_tiles) worth = worth_short;
         if (small_us < worth * us && slots >= least && slots <= most) {
           plan.rows = std::move(small);
           rows_steps = steps;
@@ -589,13 +592,24 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
       // 27.4 -> 25.4), eight together lose 3 %.
       if (behind && big)
         try_small(kAloneCost[head_dim == 128], false, head_dim == 128 ? 0.97 : 0.90, 1, num_cus);
-      // In pairs at head dim 128 (see run_tiles): 900 tokens at 2000, 8/2 heads, 35.6 -> 31.0 us.
+      // In pairs at head dim 128 (see run_tiles), where the walks are long enough for one's end to
+      // hide behind the other's.  Of 187 launches of 1 to 5 chunks, measured in each form, those with
+      // ranges of more than 10 tiles gain 1 to 30 %, 4 in the middle, at estimates below 0.98 (1353
+      // tokens at 19556, 16/2 heads, 246 -> 219 us; 95 at 35111, 32/8, 85.8 -> 82.2; two of 52 lose
+      // 3 and 9), and nothing in the middle above; with shorter ranges they lose 2 %, and up to 16,
+      // unless it is below 0.90 (405 tokens at 5443, 8/2 heads, 27.8 -> 32.1; 214 at 6376, 16/4,
+      // 32.5 -> 35.0; 950 at 1900, 8/2, 29.9 -> 40.0).
       // Where 129 to 255 rows have no large form, two row tiles that share a K/V stream beat one
-      // after the other by 3 to 14 % at estimates of 0.78 to 0.87 (31 tokens at 1M, 8/1 heads, 179
-      // -> 162 us; 60 at 500K, 32/8, 644 -> 556) and lose 3 % at 0.91 (20 at 100K, 8/1 heads); a
-      // stream of one row tile alone wants the long ring (16 tokens at 1M 114 us, 127 in pairs).
-      if (head_dim == 128 && behind && shared)
-        try_small(kPairedCost, true, big ? 0.98 : 0.90, num_cus + 1, INT64_MAX);
+      // after the other by 4 to 13 % at estimates of 0.75 to 0.83 (52 tokens at 579341, 32/8 heads,
+      // 726 -> 640 us; 31 at 853404, 8/1, 152 -> 138), and lose up to 7 % from 0.84 on (33 at 45708,
+      // 8/2, 27.9 -> 29.7); a stream of one row tile alone wants the long ring (16 tokens at 1M 114
+      // us, 127 in pairs).
+      if (head_dim == 128 && behind && shared) {
+        if (big)
+          try_small(kPairedCost, true, 0.98, num_cus + 1, INT64_MAX, kShortPairedTiles, 0.90);
+        else
+          try_small(kPairedCost, true, 0.83, num_cus + 1, INT64_MAX);
+      }
     }
   }
   if (!plan.rows.descs.empty())

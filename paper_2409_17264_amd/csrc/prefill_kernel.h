@@ -656,8 +656,8 @@ __device__ __forceinline__ void forget(T (&x)[N]) {
 //   2 V stages: V tile cur+1, into the stage of V tile cur-1, and K tile cur+3 into that of K tile
 //     cur, read for the last time in the iteration before.  5/8 of the LDS, so that at head dim
 //     128 two workgroups of 4 wavefronts fit a compute unit (80 KiB each) and one's start and end
-//     hide behind the other's walk; the V tile has one iteration to land.  (900 tokens at 2000,
-//     8/2 heads, 35.7 -> 31.2 us; 60 tokens at 500K, 32/8 heads, 644 -> 556.  Long walks of many
+//     hide behind the other's walk; the V tile has one iteration to land.  (95 tokens at 35111,
+//     32/8 heads, 85.8 -> 82.2 us; 60 tokens at 500K, 32/8 heads, 644 -> 556.  Long walks of many
 //     row tiles take 4 % longer so: each pair fetches K and V twice, which costs clock.)
 //
 // The masked tiles follow the unmasked ones in the same pipeline.  Ring stages are

@@ -590,12 +590,13 @@ def test_prompts_whose_walks_differ(h_q, h_kv, d, prefix, chunk, layout):
 
 # ------------------------------------------------------------ small workgroups behind a prefix
 @pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk,n_split,paired", [
-    # pairs on a compute unit, short ring: ranges of 6 and 5 tiles whose last one is shorter, rows
-    # that see none, some or all of the last range; the masked tiles at several ring positions
-    (8, 2, 128, 2000, 900, 8, True), (8, 2, 128, 2049, 870, 8, True), (8, 2, 128, 1950, 901, 9, True),
+    # pairs on a compute unit, short ring: ranges of 9, 11 and 12 tiles whose last one is shorter,
+    # rows that see none, some or all of the last range; the masked tiles at several ring positions
+    (16, 16, 128, 5339, 322, 10, True), (16, 4, 128, 3218, 649, 6, True),
+    (16, 4, 128, 3543, 652, 6, True), (16, 8, 128, 4641, 545, 7, True),
     # two row tiles, the second with 32 of 128 rows and with 4: 30-tile ranges, which leave the exact
     # route, and a ragged last page
-    (32, 8, 128, 60000, 40, 32, True), (32, 8, 128, 61237, 33, 32, True), (16, 16, 128, 9000, 140, 16, True),
+    (32, 8, 128, 60000, 40, 32, True), (32, 8, 128, 61237, 33, 32, True), (16, 16, 128, 30000, 140, 16, True),
     # alone on a compute unit: the smallest prefix, one range and several
     (32, 8, 128, 49, 49, 1, False), (16, 16, 128, 300, 260, 2, False), (8, 1, 128, 2000, 64, 7, False),
     (32, 8, 128, 1000, 300, 3, False), (32, 8, 64, 2000, 100, 7, False), (8, 2, 64, 3000, 64, 12, False),

@@ -194,6 +194,13 @@ def test_row_split_launches_fill_whole_rounds_of_the_device(prefix, chunk, h_q, 
     # small workgroups alone on a compute unit, whatever the number of KV heads
     ([1024], [256], 2, 1, 64, 128, 256), ([2000], [64], 8, 1, 64, 128, 256),
     ([2000], [200], 4, 1, 64, 128, 256), ([6000], [512], 2, 1, 64, 128, 256),
+    # in pairs where the walks are long; with short ranges the large ones are faster
+    ([19556], [1353], 16, 2, 128, 128, 512), ([35111], [95], 32, 8, 128, 128, 512),
+    ([5443], [405], 8, 2, 128, 256, 256), ([6376], [214], 16, 4, 128, 256, 256),
+    ([1900], [950], 8, 2, 128, 256, 256), ([865], [695], 16, 2, 128, 256, 256),
+    # 129 to 255 rows: pairs for long streams, one after the other for the rest
+    ([579341], [52], 32, 8, 128, 128, 512), ([853404], [31], 8, 1, 128, 128, 512),
+    ([45708], [33], 8, 2, 128, 128, 256), ([31761], [60], 32, 8, 128, 128, 256),
 ])
 def test_small_workgroups_where_they_are_faster(prefix, chunk, h_q, h_kv, d, rows, most):
     e, grid, _, _ = medha.describe_plan(prefix, chunk, h_q, h_kv, d, 256)
