@@ -258,12 +258,13 @@ int medha_kv_append(const void* k_new, const void* v_new, const medha_kv_cache* 
  * says what the workgroup in slot `slot` (0 <= slot < grid) of the launches of one
  * mode works on: the sequence (its place in the batch), KV head, KV range and row
  * tile; it returns 1, or 0 for an idle padding slot (only the sequence is set).
+ * Key-split launches have no idle workgroups: theirs are the other slots, in order.
  * medha_describe_slot knows the sizes of one sequence only (0 <= slot < n_slots) and
  * gives the order of a launch's first sequence if its row tiles walk about the same
- * number of keys: key-split ones and row-split ones with a long prefix.  Later sequences
- * count the dies from another one; prompts and first chunks are handed out in another
- * order.  These calls exist for tests and tuning;
- * they launch nothing.
+ * number of keys: row-split ones with a long prefix, and key-split ones of a multiple of
+ * 8 work items.  Later sequences of a row-split launch count the dies from another one;
+ * prompts and first chunks are handed out in another order.  These calls exist for tests
+ * and tuning; they launch nothing.
  */
 typedef struct medha_plan_entry {
   int32_t mode;            /* 0: row-split prefill kernel, 1: key-split decode kernel */

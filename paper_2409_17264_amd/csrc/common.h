@@ -50,7 +50,7 @@ struct SeqDesc {
   int32_t row_rank;         // rank of the sequence's first token row among the launch's rows
   int32_t kv_len;           // keys the page-table slice describes
   int16_t dealt;            // slots are handed out by decode_slot_dealt
-  int16_t first_die;        // die its first items go to (see turned_slot)
+  int16_t first_die;        // row-split launches: die its first items go to (see turned_slot)
 };
 static_assert(sizeof(SeqDesc) == 56, "SeqDesc layout");
 
@@ -145,33 +145,32 @@ __host__ __device__ inline SlotItem decode_slot_dealt(int u, int h_kv, int n_spl
   return r;
 }
 
-// A sequence whose items do not fill a round of the dies leaves its last dies idle, and the next one
-// as well.  So the dies are counted from another one for every sequence, the one behind the last that
-// the sequence before keeps busy (dies_taken): slot u stands for the slot that this returns.  (100
-// decodes of 1K median at 8/1 heads, one to four items each, on dies 0 to 3 without it: 59.8 -> 47.4
-// us; 128 of 4K, 103.0 -> 93.1.  20 decodes of 5000 at 8/1 heads, ten items each, two a die, 19.1
-// us, 25.8 if the count goes on by items; 24 of 2600 at 8/4, twenty items each, 28.9 and 36.6.)
+// Work item of a key-split launch's workgroup `u` (counted from the sequence's first).  One row tile,
+// so nothing is shared, and the launch has no idle workgroups: one of these would hold a compute unit
+// for itself on its way out, and where they come at regular intervals the others meet on some of a
+// die's units.  (100 decodes of 1000 at 8/1 heads 38.7 us with the sequences' slots in eights, 27.1
+// without; 20 of 5000 25.3 and 18.0; 45 of 577 at 16/4, d 128, 22.2 and 13.6; 26 of 11127 at 8/2,
+// d 64, 35.4 and 32.4.)  Sequences follow one another over the dies, and each gives a die one of 8
+// contiguous runs that differ by one item at most: the heads of a page are read near each other
+// (item u for workgroup u: 4 shards of 262144, 8 KV heads, 640 -> 647 us; 16 decodes of 8000 at 32/8,
+// d 64, 48.7 -> 50.7).
+struct KeySplitItem {
+  int kv_head, split;
+};
+__host__ __device__ inline KeySplitItem key_split_item(const SeqDesc& sd, int u, int h_kv) {
+  const int items = h_kv * sd.n_split, die = u % kXcds, longer = items % kXcds;
+  const int item = die * (items / kXcds) + (die < longer ? die : longer) + u / kXcds;
+  return KeySplitItem{item % h_kv, item / h_kv};
+}
+
+// A sequence of few items has items for its first few dies only, and the next one as well.  So the
+// dies of a row-split launch are counted from another one for every sequence, items % 8 further on:
+// slot u stands for the slot that this returns.  Equal runs of several items reach less far than
+// that (10 items lie two each on five dies), but counting by the dies reached is no better: 90
+// launches of 2 to 24 prompts or chunks take 0.25 % more in the mean, 14 prompts of 300 at 8/1 heads
+// the same, 12 chunks of 200 at 40000, 8/2 heads, 1.4 % less, 6 prompts at 16/4 heads 7 % more.
 __host__ __device__ inline int turned_slot(int u, int first_die) {
   return (u & ~(kXcds - 1)) | ((u - first_die) & (kXcds - 1));
-}
-
-// Dies by which the next sequence's first lies behind this one's.  decode_slot's equal runs of items
-// end on die (items - 1) / run, the only one that may hold less than a run among those that hold any,
-// and so do decode_slot_dealt's last groups, unless they deal single row tiles: then items % 8 dies
-// hold one more than the others.
-inline int dies_taken(const SeqDesc& sd, int h_kv) {
-  const int64_t groups = (int64_t)h_kv * sd.n_split, n = sd.n_row_tiles;
-  const int64_t items = (sd.dealt ? groups % kXcds : groups) * n;
-  if (items == 0) return 0;
-  if (sd.dealt && n >= 2 * kXcds) return (int)(items % kXcds);
-  const int64_t run = (items + kXcds - 1) / kXcds;
-  return (int)((items - 1) / run + 1) % kXcds;
-}
-
-// Work item of slot `u` (counted from the sequence's first) of a key-split launch: one row tile, so
-// a slot is a (KV head, range).
-__host__ __device__ inline SlotItem key_split_item(const SeqDesc& sd, int u, int h_kv) {
-  return decode_slot(turned_slot(u, sd.first_die), h_kv, sd.n_split, 1);
 }
 
 // Work item of slot `u` (counted from the sequence's first) of a row-split launch.  The launch's

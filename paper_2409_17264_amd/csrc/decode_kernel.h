@@ -120,8 +120,7 @@ decode_kernel(const AttnArgs args) {
   }
   const int seq = find_seq_slot(descs, args.n_seq, blockIdx.x);
   const SeqDesc sd = uniform(descs[seq]);
-  const SlotItem it = key_split_item(sd, blockIdx.x - sd.work_start, args.h_kv);
-  if (!it.valid) return;
+  const KeySplitItem it = key_split_item(sd, blockIdx.x - sd.work_start, args.h_kv);
   const int kv_head = it.kv_head, split = it.split;
 
   const int gqa = args.h_q / args.h_kv;

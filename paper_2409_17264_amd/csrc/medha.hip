@@ -123,14 +123,12 @@ hipError_t launch_plan(const LaunchPlan& lp, bool split_keys, int d, AttnArgs& a
     if (split_keys) {
       // short walks: the small ring, two workgroups per compute unit (see decode_kernel), unless
       // there is no second one (8 decodes of 2000 at 8/1 heads 20.4 -> 18.2 us a pass)
-      int64_t steps = 0, workgroups = 0;
-      for (int i = 0; i < n; ++i) {
-        workgroups += (int64_t)a.h_kv * a.inline_descs[i].n_split;
+      int64_t steps = 0;
+      for (int i = 0; i < n; ++i)
         steps = std::max<int64_t>(steps, std::min<int64_t>(
             a.inline_descs[i].tiles_per_split,
             ceil_div(a.inline_descs[i].kv_len, lp.shape.tile_keys)));
-      }
-      if (steps <= kShortWalkTiles && workgroups > lp.num_cus)
+      if (steps <= kShortWalkTiles && grid > lp.num_cus)
         e = d == 128 ? launch_decode<128, 1>(a, grid, stream) : launch_decode<64, 1>(a, grid, stream);
       else
         e = d == 128 ? launch_decode<128, 2>(a, grid, stream) : launch_decode<64, 2>(a, grid, stream);
@@ -255,6 +253,16 @@ int described_plan(const int32_t* prefix_len, const int32_t* chunk_len, int32_t 
   plan = make_plan(seqs.data(), batch, num_q_heads, num_kv_heads, head_dim,
                    num_cus > 0 ? num_cus : current_num_cus());
   return MEDHA_OK;
+}
+
+// First slot of every sequence of a mode's launches, and the end, as the introspection calls count
+// them: in eights, also where the launch has no idle workgroups.
+std::vector<int32_t> slots_in_eights(const LaunchPlan& lp, int h_kv) {
+  std::vector<int32_t> starts(1, 0);
+  for (const SeqDesc& sd : lp.descs)
+    starts.push_back(starts.back() + (int32_t)(kXcds * ceil_div((int64_t)h_kv * sd.n_split *
+                                                                    sd.n_row_tiles, kXcds)));
+  return starts;
 }
 
 // A chunked-prefill call; `alloc`: asked for a workspace of the reported size instead of the
@@ -483,6 +491,7 @@ int medha_describe_plan(const int32_t* prefix_len, const int32_t* chunk_len, int
   if (rc != MEDHA_OK) return rc;
   for (int mode = 0; mode < 2; ++mode) {
     const LaunchPlan& lp = mode == 0 ? plan.rows : plan.keys;
+    const std::vector<int32_t> starts = slots_in_eights(lp, num_kv_heads);
     for (size_t i = 0; i < lp.descs.size(); ++i) {
       const SeqDesc& sd = lp.descs[i];
       medha_plan_entry& e = entries[lp.seq_index[i]];
@@ -492,13 +501,12 @@ int medha_describe_plan(const int32_t* prefix_len, const int32_t* chunk_len, int
       e.n_row_tiles = sd.n_row_tiles;
       e.n_split = sd.n_split;
       e.tiles_per_split = sd.tiles_per_split;
-      e.work_start = sd.work_start;
-      e.n_slots = (i + 1 < lp.descs.size() ? lp.descs[i + 1].work_start : lp.n_slots) -
-                  sd.work_start;
+      e.work_start = starts[i];
+      e.n_slots = starts[i + 1] - starts[i];
     }
+    int32_t* grid = mode == 0 ? grid_rows : grid_keys;
+    if (grid) *grid = starts.back();
   }
-  if (grid_rows) *grid_rows = plan.rows.n_slots;
-  if (grid_keys) *grid_keys = plan.keys.n_slots;
   if (workspace_bytes) *workspace_bytes = plan.workspace_bytes();
   return MEDHA_OK;
 }
@@ -512,14 +520,20 @@ int medha_describe_plan_slot(const int32_t* prefix_len, const int32_t* chunk_len
                                 num_cus, plan);
   if (rc != MEDHA_OK) return rc;
   const LaunchPlan& lp = mode == 0 ? plan.rows : plan.keys;
-  if (mode < 0 || mode > 1 || slot < 0 || slot >= lp.n_slots) return MEDHA_ERR_INVALID_ARG;
+  const std::vector<int32_t> starts = slots_in_eights(lp, num_kv_heads);
+  if (mode < 0 || mode > 1 || slot < 0 || slot >= starts.back()) return MEDHA_ERR_INVALID_ARG;
   size_t i = 0;
-  while (i + 1 < lp.descs.size() && lp.descs[i + 1].work_start <= slot) ++i;
+  while (starts[i + 1] <= slot) ++i;
   const SeqDesc& sd = lp.descs[i];
   const bool last = i + 1 == lp.descs.size() || (i + 1) % kMaxInlineSeq == 0;  // of its launch
-  const int u = slot - sd.work_start;
-  const SlotItem it = mode == 0 ? row_split_item(sd, u, num_kv_heads, last)
-                                : key_split_item(sd, u, num_kv_heads);
+  const int u = slot - starts[i];
+  SlotItem it;
+  if (mode == 0) {
+    it = row_split_item(sd, u, num_kv_heads, last);
+  } else {
+    const KeySplitItem k = key_split_item(sd, u, num_kv_heads);
+    it = SlotItem{u < num_kv_heads * sd.n_split, k.kv_head, k.split, 0};
+  }
   if (seq) *seq = lp.seq_index[i];
   if (it.valid) {
     if (kv_head) *kv_head = it.kv_head;

@@ -22,9 +22,10 @@ struct LaunchPlan {
   ModeShape shape{0, 0};
   int q_blocks = 1;   // 32-row blocks per wavefront (row-split mode)
   bool paired = false;  // two workgroups to a compute unit, with the short ring (head dim 128)
-  int n_slots = 0;    // grid size
+  int n_slots = 0;    // grid size: key-split, the items; row-split, every sequence's in eights
   int total_rows = 0; // token rows of the launch
   int num_cus = 0;    // compute units planned for
+  bool key_split = false;
   bool any_split = false;
 };
 
@@ -440,8 +441,8 @@ inline void plan_launch(LaunchPlan& lp, int h_kv, int gqa, int64_t steps, int mi
       lp.any_split = true;
     }
     const int64_t items = (int64_t)h_kv * sd.n_split * sd.n_row_tiles;
-    slot += (int)(kXcds * ceil_div(items, kXcds));
-    die = (die + dies_taken(sd, h_kv)) % kXcds;
+    slot += (int)(lp.key_split ? items : kXcds * ceil_div(items, kXcds));
+    die = (int)((die + items) % kXcds);
     rank += sd.chunk_len;
   }
   lp.n_slots = slot;
@@ -491,6 +492,7 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
     if (n_rows > 32) max_rows = std::max(max_rows, (int)std::min<int64_t>(n_rows, 1 << 30));
   }
   plan.rows.num_cus = plan.keys.num_cus = num_cus;
+  plan.keys.key_split = true;
   // Row-split mode: 4 wavefronts x (32 * q_blocks) rows, 64-key tiles.
   plan.rows.q_blocks = max_rows >= 256 ? 2 : 1;
   plan.rows.shape = ModeShape{kWaves * 32 * plan.rows.q_blocks, 64};

@@ -41,6 +41,26 @@ int main() {
           for (int d = 0; d < 8; ++d)
             if (work[d] > all / 8 + 2L * h * n) { std::printf("uneven: h %d ns %d n %d\n", h, ns, n); return 1; }
       }
+  // key-split launches: workgroup u of a sequence that starts at workgroup `start`
+  for (int h : {1, 2, 3, 4, 8, 10, 12})
+    for (int ns = 1; ns <= 70; ++ns) {
+      SeqDesc sd{};
+      sd.n_split = ns;
+      std::set<int> seen;
+      int count[8] = {}, before[8];
+      for (int u = 0; u < h * ns; ++u) {
+        const KeySplitItem k = key_split_item(sd, u, h);
+        const int item = k.split * h + k.kv_head, die = u % 8;
+        if (k.kv_head < 0 || k.kv_head >= h || k.split < 0 || k.split >= ns ||
+            !seen.insert(item).second || (count[die]++ > 0 && item != before[die] + 1)) {
+          std::printf("bad workgroup %d of h %d ns %d\n", u, h, ns);
+          return 1;
+        }
+        before[die] = item;
+      }
+      for (int d = 0; d < 8; ++d)
+        if (count[d] != h * ns / 8 + (d < h * ns % 8)) { std::printf("run: h %d ns %d\n", h, ns); return 1; }
+    }
   std::puts("ok");
 }
 """
@@ -60,30 +80,34 @@ def test_dealt_slots_cover_every_item_once_and_evenly(tmp_path):
     assert run.returncode == 0 and "ok" in run.stdout, run.stdout + run.stderr
 
 
-@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,mode,per_seq", [
-    ([900 + 31 * i for i in range(40)], [1] * 40, 8, 1, 1, None),  # one to four ranges of one head
-    ([300 * (1 + i % 5) for i in range(33)], [1] * 33, 8, 2, 1, None),
-    ([0] * 12, [90 + 16 * i for i in range(12)], 8, 1, 0, None),   # prompts of 3 to 9 row tiles
-    ([6143] * 24, [1] * 24, 8, 1, 1, 12),                          # two items on each of six dies
-    ([1535] * 32, [1] * 32, 32, 4, 1, 12),
-    ([2600] * 24, [1] * 24, 8, 4, 1, 20),                          # three on six dies, two on one
-    ([3583] * 24, [1] * 24, 8, 4, 1, 28),                          # four on each of seven dies
-    ([5000] * 20, [1] * 20, 8, 1, 1, 10),
-    ([0] * 14, [300] * 14, 8, 1, 0, 10),                           # prompts: runs of items
-    ([0] * 14, [620] * 14, 8, 1, 0, 20),                           # prompts: single row tiles in turn
-    ([0] * 13, [830] * 13, 8, 1, 0, 26),
-    ([0] * 13, [600] * 13, 20, 10, 0, 50),                         # a group a die, and two groups
+@pytest.mark.parametrize("prefix,chunk,h_q,h_kv,mode", [
+    ([900 + 31 * i for i in range(40)], [1] * 40, 8, 1, 1),      # one to four ranges of one head
+    ([300 * (1 + i % 5) for i in range(33)], [1] * 33, 8, 2, 1),
+    ([6143] * 24, [1] * 24, 8, 1, 1),                            # 12, 12, 20, 28 and 10 items each
+    ([1535] * 32, [1] * 32, 32, 4, 1),
+    ([2600] * 24, [1] * 24, 8, 4, 1),
+    ([3583] * 24, [1] * 24, 8, 4, 1),
+    ([5000] * 20, [1] * 20, 8, 1, 1),
+    ([999] * 100, [1] * 100, 8, 1, 1),                           # two launches
+    ([0] * 12, [90 + 16 * i for i in range(12)], 8, 1, 0),       # prompts of 3 to 9 row tiles
 ])
-def test_sequences_of_few_items_are_spread_over_the_dies(prefix, chunk, h_q, h_kv, mode, per_seq):
+def test_sequences_of_few_items_are_spread_over_the_dies(prefix, chunk, h_q, h_kv, mode):
     entries, grid_rows, grid_keys, _ = medha.describe_plan(prefix, chunk, h_q, h_kv, 128, 256)
     items, dies = 0, [0] * 8
+    order = sorted(range(len(entries)), key=lambda i: entries[i].work_start)
+    launch = {seq: i // 64 for i, seq in enumerate(order)}  # 64 sequences each
+    rank = [0] * 2
     for s in range(grid_keys if mode else grid_rows):
         it = medha.describe_plan_slot(prefix, chunk, h_q, h_kv, 128, 256, mode, s)
         if it is not None:
             items += 1
-            dies[s % 8] += 1
-    each = [h_kv * e.n_split * e.n_row_tiles for e in entries]
-    assert items == sum(each) and per_seq in (None, min(each)) and per_seq in (None, max(each))
-    # however many sequences there are: an item more than the mean, and a twentieth for the dies
-    # that a sequence's last run leaves short
-    assert max(dies) <= 1.05 * items / 8 + 1, dies
+            # workgroup -> die: a row-split launch has a workgroup per slot, a key-split one leaves
+            # the idle ones out
+            dies[(rank[launch[it[0]]] if mode else s) % 8] += 1
+            rank[launch[it[0]]] += 1
+    assert items == sum(h_kv * e.n_split * e.n_row_tiles for e in entries)
+    if mode:
+        assert max(dies) - min(dies) <= 1 + max(launch.values()), dies
+    else:
+        # equal runs of a sequence differ by one item, and those of more than 8 items by their last run
+        assert max(dies) <= items / 8 + len(entries) / 2 + 1, dies
