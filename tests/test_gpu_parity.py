@@ -512,13 +512,14 @@ def test_small_chunk_long_prefix_many_way_split(h_q, h_kv, d, prefix, chunk):
 
 
 @pytest.mark.parametrize("h_q,h_kv,d,prefix,chunk", [(8, 2, 128, 400_001, 32), (32, 8, 64, 200_003, 64),
-                                                     (32, 8, 64, 200_003, 31)])
+                                                     (32, 8, 64, 200_003, 31), (8, 1, 128, 800_011, 32)])
 def test_streams_too_long_for_the_caches(h_q, h_kv, d, prefix, chunk):
-    """One row tile against 410 MB of K/V: the tile loads with the non-temporal hint (at head dim
-    128 and 256 rows, one GPU's share of the 70B-sized layer at 32 tokens takes them too)."""
+    """One row tile of 128 or 256 rows against 410 MB of K/V: the tile loads with the non-temporal
+    hint, in all four kernels that have it."""
     b = wl.make_prefill_batch("once", h_q, h_kv, d, [prefix], [chunk], 3 * chunk + d, "cuda")
     e, _, _, _ = medha.describe_plan(b.prefix_len, b.chunk_len, h_q, h_kv, d, 256)
     assert e[0].n_row_tiles == 1 and prefix * h_kv * 4 * d > 3 * (128 << 20)
+    assert e[0].rows_per_wg == (256 if chunk * h_q // h_kv == 256 else 128)
     rows = np.array([0, chunk // 2, chunk - 1], np.int64)
     ro, rl = oracle_prefill(b, rows)
     out, lse = gpu_prefill(b)

@@ -2,6 +2,7 @@
 the same results, outputs and errors for every form of the arguments."""
 import ctypes
 import sys
+import threading
 import types
 
 import numpy as np
@@ -13,13 +14,16 @@ from paper_2409_17264_amd import binding
 from paper_2409_17264_amd import workloads as wl
 
 
-def _outcome(call):
+def _outcome(call, buffers):
+    """What a call returns, copied, or raises; the callers' outputs hold NaN before it."""
+    for t in buffers:
+        t.fill_(float("nan"))
     try:
         r = call()
     except Exception as e:  # noqa: BLE001
         return type(e), getattr(e, "code", None)
     torch.cuda.synchronize()
-    return r
+    return tuple(t.clone() for t in r)
 
 
 def _same(a, b):
@@ -187,9 +191,15 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
             return kk, vv
         return run
 
-    def given(shape, **bad):
-        return dict(out=torch.empty(shape + (8, 128), **dict(f32, **bad)),
-                    lse=torch.empty(shape + (8,), **f32))
+    buffers = []
+
+    def given(shape, names=("out", "lse"), **bad):
+        buffers.extend((torch.empty(shape + (8, 128), **dict(f32, **bad)),
+                        torch.empty(shape + (8,), **f32)))
+        return dict(zip(names, buffers[-2:]))
+
+    def partial(shape):
+        return given(shape, names=("out_partial", "lse_partial"))
 
     calls = [prefill(), decode(), chunk(), append(), lambda: medha.lse_merge(po, pl)]
     for form in _forms(offs):
@@ -204,8 +214,8 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
         calls.append(prefill(scale=s))
     for w in (ws, small, None):
         calls += [prefill(workspace=w), decode(workspace=w), chunk(workspace=w),
-                  prefill(workspace=w, **given((tokens,))), decode(workspace=w, **given((3,))),
-                  chunk(workspace=w, **given((tokens,)))]
+                  prefill(workspace=w, **given((tokens,))), decode(workspace=w, **partial((3,))),
+                  chunk(workspace=w, **partial((tokens,)))]
     calls.append(lambda: medha.lse_merge(po, pl, **given((5,))))
     # refused, by the binding or by the library
     calls += [prefill(q=q.float()), prefill(q=q[:, ::2]), prefill(q=q[:-1]), prefill(k=k[:-1]),
@@ -214,7 +224,7 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
               prefill(pre=pre[:-1]), prefill(pre=-pre - 1), prefill(pre="x"), prefill(pre=None),
               prefill(scale=float("nan")), prefill(scale="x"), prefill(scale=None),
               prefill(**given((tokens + 1,))), prefill(**given((tokens,), dtype=torch.float64)),
-              decode(qi=qi + 1000), decode(kl=-kl), decode(**given((2,))), chunk(rows=rows + 1000),
+              decode(qi=qi + 1000), decode(kl=-kl), decode(**partial((2,))), chunk(rows=rows + 1000),
               chunk(v0=pre[:-1]), append(new=new[:-1]), append(new=new.float()),
               lambda: medha.lse_merge(po, pl[:-1]), lambda: medha.lse_merge(po.half(), pl),
               lambda: medha.lse_merge(po[..., :6].contiguous(), pl)]
@@ -227,10 +237,10 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
         calls += [prefill(workspace=w), decode(workspace=w), chunk(workspace=w)]
     refused = 0
     for i, call in enumerate(calls):
-        native = _outcome(call)
+        native = _outcome(call, buffers)
         with monkeypatch.context() as m:
             m.setattr(binding, "_NATIVE", binding._LongWay)
-            plain = _outcome(call)
+            plain = _outcome(call, buffers)
         print(f"call {i}", flush=True)
         _same(native, plain)
         refused += isinstance(native, tuple) and isinstance(native[0], type)
@@ -239,6 +249,15 @@ def test_results_outputs_and_errors_are_those_of_the_binding(monkeypatch):
     n = binding._NATIVE
     out, lse = given((tokens,)).values()
     r = n.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, b.scale, out, lse, None)
+    assert r[0] is out and r[1] is lse
+    out, lse = given((3,)).values()
+    r = n.decode_partial_attn(q, k, v, pt, offs, qi, kl, b.scale, out, lse, ws)
+    assert r[0] is out and r[1] is lse
+    out, lse = given((tokens,)).values()
+    r = n.chunk_partial_attn(q, k, v, pt, offs, rows, chk, kl, pre + 1, b.scale, out, lse, ws)
+    assert r[0] is out and r[1] is lse
+    out, lse = given((5,)).values()
+    r = n.lse_merge(po, pl, out, lse)
     assert r[0] is out and r[1] is lse
     assert n.kv_append(new, new, k, v, pt, offs, pre, chk) is True
     assert n.lse_merge(po, pl, None, None) is not None
@@ -269,7 +288,9 @@ def _five_calls():
     zero = np.zeros(1, np.int32)
     ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
     new = wl.randn_bf16((4, 1, 64), 2, "cuda")
-    po, pl = torch.randn(2, 4, 2, 64, device="cuda"), torch.randn(2, 4, 2, device="cuda")
+    po = wl.randn_bf16((2, 4, 2, 64), 3, "cuda").float()
+    pl = wl.randn_bf16((2, 4, 2), 4, "cuda").float()
+    medha.kv_append(new, new, k, v, pt, offs, pre, chk)  # the later ones write the same again
     return {
         "prefill": lambda s=b.scale: medha.chunked_prefill_attn(q, k, v, pt, offs, pre, chk, s),
         "decode": lambda s=b.scale: medha.decode_partial_attn(q, k, v, pt, offs, zero, kl, s,
@@ -278,6 +299,79 @@ def _five_calls():
                                                             s, workspace=ws),
         "merge": lambda: medha.lse_merge(po, pl),
         "append": lambda: medha.kv_append(new, new, k, v, pt, offs, pre, chk)}
+
+
+def _as_one(results):
+    """The five calls' results as one list of tensors (the append has none)."""
+    return [t.clone() for r in results if r is not None for t in r]
+
+
+@pytest.mark.gpu
+def test_calls_go_to_the_current_stream_of_their_thread():
+    """From another stream, and from threads with a stream each, over and over: the results of the
+    default stream, behind work that the stream still has before it."""
+    five = _five_calls()
+    want = _as_one(call() for call in five.values())
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work():
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            five = _five_calls()  # (a workspace of its own for every thread)
+            for _ in range(20):
+                got = _as_one(call() for call in five.values())
+                stream.synchronize()
+                if not all(map(torch.equal, got, want)):
+                    wrong.append(1)
+
+    work()
+    threads = [threading.Thread(target=work) for _ in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    # the call waits for what its own stream has before it
+    b = wl.make_prefill_batch("order", 8, 1, 128, [5000], [300], seed=3)
+    q, k, v, pt = b.q.cuda(), b.k_pool.cuda(), b.v_pool.cuda(), torch.from_numpy(b.page_table).cuda()
+    args = (k, v, pt, b.page_table_offs, b.prefix_len, b.chunk_len, b.scale)
+    want = _as_one([medha.chunked_prefill_attn(q, *args)])
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        late = torch.zeros_like(q)
+        busy = torch.randn(4096, 4096, device="cuda")
+        for _ in range(20):
+            busy = busy @ busy * 1e-3
+        late.copy_(q)
+        got = medha.chunked_prefill_attn(late, *args)
+    stream.synchronize()
+    assert all(map(torch.equal, got, want))
+
+
+@pytest.mark.gpu
+def test_calls_can_be_captured():
+    """A graph of the five calls, replayed between eager work on other inputs."""
+    five = _five_calls()
+    want = _as_one(call() for call in five.values())
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = [call() for call in five.values()]
+    outputs = [t for r in captured if r is not None for t in r]
+    other = wl.make_prefill_batch("other", 8, 2, 128, [900, 40], [30, 1], seed=9)
+    q, k, v = other.q.cuda(), other.k_pool.cuda(), other.v_pool.cuda()
+    pt = torch.from_numpy(other.page_table).cuda()
+    for _ in range(5):
+        for t in outputs:
+            t.fill_(float("nan"))
+        medha.chunked_prefill_attn(q, k, v, pt, other.page_table_offs, other.prefix_len,
+                                   other.chunk_len, other.scale)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(map(torch.equal, outputs, want))
 
 
 @pytest.mark.gpu
@@ -297,9 +391,10 @@ def test_what_is_raised_inside_a_call_reaches_the_caller(monkeypatch, error):
         def __float__(self):
             return once(0.125)
 
+    five = _five_calls()
     device = torch.cuda.current_device
     monkeypatch.setattr(torch.cuda, "current_device", lambda: once(device()))
-    for name, call in _five_calls().items():
+    for name, call in five.items():
         raised[:] = [1]
         call()  # (nothing raises: the module makes the call)
         raised.clear()
