@@ -25,7 +25,6 @@ constexpr int kMaxInlineSeq = 64; // sequence descriptors per kernel launch (the
 constexpr int kShortWalkTiles = 24;   // key-split launches walking at most this many 128-key tiles per workgroup use the small ring
 constexpr int kWideMergeSplits = 16;  // more KV ranges per row than this: the wide merge kernel
 constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;
-constexpr float kRescaleSlack = 8.f;  // log2 units a row maximum may exceed the softmax reference
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
