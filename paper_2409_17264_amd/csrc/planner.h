@@ -517,10 +517,12 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
     const int64_t rows_min = min_rows;
     min_rows += simple.part_rows;
     // About 8 workgroups a compute unit are what a call has to bring scratch for.  Walks of 6 to 24
-    // tiles are cut into about 6: a workgroup's start and end weigh more than a finer last round (64
-    // decodes of 2K median, 32/8 heads, 116.7 -> 114.2 us a pass, at d 64 72.5 -> 70.8; 1M in 8 shards,
-    // 8/1 heads, 99.9 -> 98.9).  Ranges of 5 instead of 4 tiles are 1 to 2
-    // % longer (24 decodes of 4K, 32/8 heads, 87.2 -> 88.9); long walks fill their rounds with 8.
+    // tiles are cut into about 6: a workgroup's start and end weigh more than a finer last round
+    // (the timed batch of 64 decodes of 2K median, 32/8 heads, 113.0 -> 110.6 us; 178 of 1130, 32/8,
+    // 166.5 -> 145.6; 183 of 8192, 8/1, 168.9 -> 145.4).  How full the last round gets decides each
+    // batch: 66 of them take 0.86 to 1.07 of the time, 0.99 in the mean (35 of 4096 at 32/8, d 64,
+    // 54.6 -> 56.5).  Ranges of 5 instead of 4 tiles are 1 to 2 % longer (24 decodes of 4K, 32/8
+    // heads, 87.2 -> 88.9); long walks fill their rounds with 8.
     const int64_t six = simple_steps(plan.keys, h_kv, gqa, num_cus * 6);
     if (six >= 6 && six <= kShortWalkTiles) keys_steps = six;
     keys_rows = split_size(plan.keys, h_kv, keys_steps, kMinTiles).part_rows;

@@ -417,8 +417,8 @@ struct RowBlock {
   // exponentials fill that wait instead of coming after it.  The loads of the tile three ahead are
   // issued in slot kLoadSlot, their twenty scalar instructions between two MFMAs and not between
   // the barrier and the first one.  (Both together, against none and slot 0: head dim 64, 777
-  // tokens at 20K, 32/8 heads, 163.3 -> 158.1 us; 5000 tokens, 8/1 heads, 99.8 -> 98.2; 32 tokens
-  // at 1M 160.9 -> 159.2; the long walks at head dim 128 -0.4 %, where fewer idle cycles cost
+  // tokens at 20K, 32/8 heads, 156.2 -> 152.8 us; 5000 tokens, 8/1 heads, 99.8 -> 98.2; 32 tokens
+  // at 1M 160.9 -> 159.2; the long walks at head dim 128 the same, where fewer idle cycles cost
   // clock.  A lead of 2 or 4 and the loads in slot 2, 3, 6 or 8 are 0.1 to 0.6 % longer.)
   static constexpr int kLead = 3, kLoadSlot = 4;
 
