@@ -40,9 +40,8 @@ struct Plan {
   // depends on the sizes alone
   int64_t min_part_rows = 0;
   size_t min_bytes = 0;
-  size_t reserve_bytes = 0;  // what the choice of fine ranges for the key-split launch asks for
   // what callers are told to bring
-  size_t workspace_bytes() const { return std::max({bytes, min_bytes, reserve_bytes}); }
+  size_t workspace_bytes() const { return std::max(bytes, min_bytes); }
 };
 
 struct SeqInput {
@@ -469,12 +468,19 @@ inline int64_t simple_steps(LaunchPlan& lp, int h_kv, int gqa, int target_wgs) {
                                   : longest;
 }
 
-// Plans a batch.  `budget` is the size of the workspace at hand: the plan takes the KV ranges
-// that are expected to be fastest among those whose partials fit it; the simple rule's need
-// (`min_bytes`) is the least a call has to bring.
+// Plans a batch.  `budget` is the size of the workspace at hand: the plan is the one without a limit
+// if its partials fit it (so that every workspace of the reported size gives the same plan, whatever
+// the choices on the way to it look at), and otherwise takes the KV ranges that are expected to be
+// fastest among those whose partials do; the simple rule's need (`min_bytes`) is the least a call has
+// to bring.
 inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int head_dim,
                       int num_cus, size_t budget = SIZE_MAX) {
   Plan plan;
+  if (budget != SIZE_MAX) {
+    plan = make_plan(seqs, batch, h_q, h_kv, head_dim, num_cus);
+    if (plan.part_rows == 0 || plan.bytes <= budget) return plan;
+    plan = Plan{};
+  }
   const int gqa = h_q / h_kv;
   int max_rows = 0;
   for (int b = 0; b < batch; ++b) {
@@ -501,7 +507,7 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
   plan.keys.shape = ModeShape{32, 32 * kWaves};
   constexpr int kMinTiles = 4;
   const int64_t row_bytes = (int64_t)h_q * (head_dim + 1) * sizeof(float);
-  int64_t keys_steps = 1, rows_steps = 1, keys_rows = 0, min_rows = 0, reserve_rows = 0;
+  int64_t keys_steps = 1, rows_steps = 1, keys_rows = 0, min_rows = 0;
   int keys_min_tiles = kMinTiles;
   if (!plan.rows.descs.empty()) {
     rows_steps = simple_steps(plan.rows, h_kv, gqa, num_cus);
@@ -540,7 +546,6 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
           keys_steps = steps;
           keys_min_tiles = steps;
           keys_rows = fine.part_rows;
-          reserve_rows = fine.part_rows + rows_min;
         }
         break;
       }
@@ -625,7 +630,6 @@ inline Plan make_plan(const SeqInput* seqs, int batch, int h_q, int h_kv, int he
   plan.off_part_lse = partial_o_bytes(plan.part_rows, h_q, head_dim);
   plan.bytes = partial_bytes(plan.part_rows, h_q, head_dim);
   plan.min_bytes = partial_bytes(min_rows, h_q, head_dim);
-  plan.reserve_bytes = partial_bytes(reserve_rows, h_q, head_dim);
   plan.min_part_rows = min_rows;
   return plan;
 }

@@ -122,40 +122,71 @@ int main() {
 """
 
 BUDGET = PRELUDE + r"""
+// chunks behind a prefix, which choose between three forms of workgroups
+static std::vector<SeqInput> draw_behind(int n) {
+  std::vector<SeqInput> s;
+  int row = 0;
+  for (int i = 0; i < n; ++i) {
+    const int chunk = log_int(20, 2500), prefix = log_int(chunk, 80000);
+    s.push_back({0, row, row, chunk, prefix, -1});
+    row += chunk;
+  }
+  return s;
+}
 static bool same(const Plan& a, const Plan& b) {
   for (auto pair : {std::make_pair(&a.rows, &b.rows), std::make_pair(&a.keys, &b.keys)}) {
     const LaunchPlan &x = *pair.first, &y = *pair.second;
-    if (x.n_slots != y.n_slots || x.q_blocks != y.q_blocks || x.seq_index != y.seq_index) return false;
+    if (x.n_slots != y.n_slots || x.q_blocks != y.q_blocks || x.paired != y.paired ||
+        x.seq_index != y.seq_index) return false;
     for (size_t i = 0; i < x.descs.size(); ++i)
       if (x.descs[i].n_split != y.descs[i].n_split || x.descs[i].part_row != y.descs[i].part_row ||
           x.descs[i].tiles_per_split != y.descs[i].tiles_per_split) return false;
   }
   return a.bytes == b.bytes;
 }
+static int less = 0;
+static bool check(const std::vector<SeqInput>& seqs, int h_q, int h_kv, int d) {
+  auto plan = [&](size_t budget) {
+    return make_plan(seqs.data(), (int)seqs.size(), h_q, h_kv, d, 256, budget);
+  };
+  const Plan full = plan(SIZE_MAX);
+  const size_t need = full.workspace_bytes();
+  // any workspace of the reported size or more: one plan
+  for (size_t b : {need, need + 1, 2 * need, need + 4096})
+    if (!same(full, plan(b))) {
+      std::printf("another plan with %zu of %zu: heads %d/%d d %d, %d tokens at %d\n", b, need, h_q, h_kv,
+                  d, seqs[0].chunk_len, seqs[0].prefix_len);
+      return false;
+    }
+  // less, down to what a call has to bring: a plan that fits
+  if (full.min_bytes < need)
+    for (size_t b : {full.min_bytes, (full.min_bytes + need) / 2, need - 1}) {
+      const Plan p = plan(b);
+      if (p.bytes > b || p.min_bytes != full.min_bytes) { std::printf("%zu of %zu\n", p.bytes, b); return false; }
+      less += !same(full, p);
+    }
+  // less still: the simple rule's plan or one without more partials, for the call to refuse
+  if (plan(0).bytes > std::max(full.min_bytes, full.bytes)) { std::puts("grew"); return false; }
+  return true;
+}
 int main() {
-  const int heads[][2] = {{1, 1}, {8, 1}, {8, 2}, {32, 8}, {12, 3}};
-  int less = 0;
-  for (int it = 0; it < 4000; ++it) {
-    const auto& hh = heads[rng() % 5];
+  const int heads[][2] = {{1, 1}, {8, 1}, {8, 2}, {32, 8}, {12, 3}, {16, 2}, {16, 4}};
+  for (int it = 0; it < 30000; ++it) {
+    const auto& hh = heads[rng() % 7];
     const int d = rng() & 1 ? 64 : 128;
-    const auto seqs = draw(1 + rng() % (it % 3 ? 3 : 24));
-    auto plan = [&](size_t budget) {
-      return make_plan(seqs.data(), (int)seqs.size(), hh[0], hh[1], d, 256, budget);
-    };
-    const Plan full = plan(SIZE_MAX);
-    const size_t need = full.workspace_bytes();
-    // any workspace of the reported size or more: one plan
-    for (size_t b : {need, need + 1, 2 * need, need + 4096})
-      if (!same(full, plan(b))) { std::printf("another plan with %zu of %zu\n", b, need); return 1; }
-    // less, down to what a call has to bring: a plan that fits
-    if (full.min_bytes < need)
-      for (size_t b : {full.min_bytes, (full.min_bytes + need) / 2, need - 1}) {
-        const Plan p = plan(b);
-        if (p.bytes > b || p.min_bytes != full.min_bytes) { std::printf("%zu of %zu\n", p.bytes, b); return 1; }
-        less += !same(full, p);
-      }
-    // less still: the simple rule's plan or one without more partials, for the call to refuse
-    if (plan(0).bytes > std::max(full.min_bytes, full.bytes)) { std::puts("grew"); return 1; }
+    if (!check(it % 6 ? draw_behind(1 + rng() % 3) : draw(1 + rng() % (it % 3 ? 3 : 24)), hh[0], hh[1], d))
+      return 1;
+  }
+  // (of 5 million draws: the form of the workgroups changed with the workspace)
+  const int rare[][3][2] = {{{583, 21}, {934, 319}, {78031, 22}}, {{55830, 27}, {448, 336}, {552, 73}}};
+  for (const auto& r : rare) {
+    std::vector<SeqInput> s;
+    int row = 0;
+    for (const auto& x : r) {
+      s.push_back({0, row, row, x[1], x[0], -1});
+      row += x[1];
+    }
+    if (!check(s, 32, 8, 128)) return 1;
   }
   std::printf("ok %d\n", less);
   return less > 200 ? 0 : 1;
