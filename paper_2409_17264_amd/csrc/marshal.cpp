@@ -1,11 +1,11 @@
 // Argument marshalling of the Python binding's tensor calls: what binding.py does with a call's
 // arguments, in native code.  An ordinary call (plain tensors, lengths as int32 or int64 arrays or as
-// lists of integers, everything in order) is made from here; every other one is answered with None, with nothing enqueued, and
-// binding.py then goes through it step by step, converts what can be converted and raises what has
-// to be raised.  Only an error of the HIP runtime, with which some of a call may be enqueued, is
-// raised from here, and the call not made again.  (Host time of one decode at 2048 tokens, its append and its attention: 23.9 us in
-// Python, of which 7 us were the three launches and 5 us the three allocations; no more than the
-// 16 us of its kernels from here.)
+// lists of integers, everything in order) is made from here; every other one is answered with None,
+// with nothing enqueued, and binding.py then goes through it step by step, converts what can be
+// converted and raises what has to be raised.  Only an error of the HIP runtime, with which some of a
+// call may be enqueued, is raised from here, and the call not made again.  (Host time of one decode at
+// 2048 tokens, its append and its attention: 23.9 us in Python, of which 7 us were the three launches
+// and 5 us the three allocations; 12 us from here.)
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -19,6 +19,7 @@
 #include <cstring>
 #include <exception>
 #include <limits>
+#include <type_traits>
 
 #include "medha.h"
 #include "medha_internal.h"
@@ -107,16 +108,19 @@ class HostArray {
   c10::SmallVector<T, 72> values_;
 };
 
-// The interpreter's lock is given back in this scope, as ctypes does around a call.
+// The interpreter's lock is given back in this scope, as ctypes does around a call.  (A daemon thread
+// that wants it back while the interpreter is ending is ended there, by unwinding its stack: that has
+// to get through the destructor, and through ordinary().)
 class Unlocked {
  public:
   Unlocked() : state_(PyEval_SaveThread()) {}
-  ~Unlocked() { PyEval_RestoreThread(state_); }
+  ~Unlocked() noexcept(false) { PyEval_RestoreThread(state_); }
   Unlocked(const Unlocked&) = delete;
 
  private:
   PyThreadState* state_;
 };
+static_assert(!std::is_nothrow_destructible<Unlocked>::value, "unwinding ends in an abort");
 
 int64_t total(const HostArray<int32_t>& a) {
   int64_t sum = 0;
@@ -244,7 +248,7 @@ void* allocate(size_t n, void* context) {
   try {
     w->bytes = new_workspace(n, w->options);
     return w->bytes.data_ptr();
-  } catch (...) {
+  } catch (const std::exception&) {
     w->error = std::current_exception();
     return nullptr;
   }
